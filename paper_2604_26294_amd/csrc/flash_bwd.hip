@@ -229,7 +229,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   const int v_last = min(kKvTile, kv_len - k0) - 1;
   if (v_last >= 0)
     for (int part = 0; part < kKvTile / 64; ++part)
-      load_tile64<D, kKvWaves>(vvbase + (size_t)(k0 + 64 * part) * kv_stride,
+      load_tile64<D, kKvWaves>(vvbase + (size_t)(k0 + min(64 * part, v_last)) * kv_stride,
                                2u * (uint32_t)kv_stride, max(v_last - 64 * part, 0),
                                Ls + VO + part * T64, wave, lane);
   // K fragments of this lane's key (B operand of S): d slots 16 s + 8 hh.
@@ -244,9 +244,11 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
 #pragma unroll
   for (int s = 0; s < C::KS; ++s) asm volatile("" ::"v"(kf[s]));
 
-  // Query tiles of 64 rows that can see key k0 or later: per segment, tiles from tf.
+  // Query tiles of 64 rows that can see key k0 or later: per segment, tiles from tf (none
+  // of a segment that ends before k0, though its last tile, if partial, may reach past it).
   int tf[2] = {0, 0}, nv[2] = {0, 0};
   for (int sg = 0; sg < P.n_seg; ++sg) {
+    if (P.seg_pos0[sg] + P.seg_rows[sg] <= k0) continue;
     const int nt = (P.seg_rows[sg] + kQStage - 1) / kQStage;
     const int num = k0 - P.seg_pos0[sg] - (kQStage - 1);
     tf[sg] = num <= 0 ? 0 : (num + kQStage - 1) / kQStage;

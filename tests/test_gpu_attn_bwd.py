@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 from oracle import tsp_oracle as O  # noqa: E402
 from paper_2604_26294_amd import inputs as I  # noqa: E402
 from paper_2604_26294_amd.harness import RankProblem, local_rows, to_device_bf16  # noqa: E402
-from paper_2604_26294_amd.workloads import TINY  # noqa: E402
+from paper_2604_26294_amd.workloads import TINY, Workload  # noqa: E402
 from tests.gpu_common import (MID_GQA64, MID_GQA8, MID_MHA128, ODD3, SINGLE,  # noqa: E402
                               assert_close, f64)
 
@@ -112,6 +112,38 @@ def test_attention_backward_second_stage(wl, p):
         g = dw[r].double().cpu().numpy()
         assert_close(g[qd:qd + kd], ref_dwk[r], f"{wl.name} r{p} dW_K[{r}]")
         assert_close(g[qd + kd:qd + 2 * kd], ref_dwv[r], f"{wl.name} r{p} dW_V[{r}]")
+
+
+# Sequence lengths that no tile size divides, S % 256 <= 192, and partial last query tiles
+# that reach past the last readable key: across a key tile's edge (contiguous rank 2:
+# queries 170 .. 254), at the end of the buffer (rank 3), and within a key tile (zigzag).
+ODD_SEQ = Workload("odd-seq-340", 1, 340, 256, 512, 4, 4, 64, 4, 0, w_std=0.06)
+ODD_ZZ = Workload("odd-seq-580", 2, 580, 256, 512, 2, 2, 128, 2, 0, w_std=0.06, layout=1)
+
+
+@pytest.mark.parametrize("wl,p", [(ODD_SEQ, 2), (ODD_SEQ, 3), (ODD_ZZ, 1)],
+                         ids=["contiguous-r2", "contiguous-r3", "zigzag-r1"])
+def test_first_stage_reads_no_key_past_the_last_visible_one(wl, p):
+    """K/V rows past the last visible key hold NaN here; the contributions to their
+    gradients are exactly zero all the same, and the others meet the oracle."""
+    print(f"[attn bwd odd] {wl.name} {wl.layout_name} rank {p}", flush=True)
+    x_bits, w_bits, dy_bits = _inputs(wl)
+    prob = RankProblem(wl, x_bits, w_bits, p)
+    prob.prefill_kv(include_self=True)
+    D = wl.degree
+    kv_len = (p + 1) * wl.s_loc if wl.layout == 0 else (2 * D - p) * (wl.s_loc // 2)
+    prob.k_buf[:, kv_len:] = float("nan")
+    prob.v_buf[:, kv_len:] = float("nan")
+    dx, _, dk, dv = prob.attn_bwd(to_device_bf16(local_rows(dy_bits, wl, p)))
+    torch.cuda.synchronize()
+    ref = _reference_stage1(wl, p)
+    assert_close(dx.double().cpu().numpy(), ref["dx"], f"{wl.name} r{p} dX")
+    ks = wl.n_kv_heads // D
+    for name, got in (("dk", dk), ("dv", dv)):
+        assert not torch.any(got[:, kv_len:] != 0), f"{name} past the last visible key"
+        for r in range(D):
+            assert_close(got[:, :, r * ks:(r + 1) * ks].double().cpu().numpy(), ref[name][r],
+                         f"{wl.name} r{p} {name}[{r}]")
 
 
 def test_two_stages_accumulate_into_one_dx():
