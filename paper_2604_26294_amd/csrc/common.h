@@ -29,6 +29,13 @@ __device__ __forceinline__ f32x16 mfma32(const u32x4& a, const u32x4& b, const f
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// MFMA v_mfma_f32_16x16x32_bf16: A / B operand lane l: row / column l % 16 at contraction
+// slots 8 (l / 16) .. +7; C/D element r: row 4 (l / 16) + r, column l % 16.
+__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 // Two fp32 -> one dword of two bf16 (round to nearest even; low half = first).
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));

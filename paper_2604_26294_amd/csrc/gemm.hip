@@ -11,10 +11,12 @@
 //                   reorder folded in)  Algorithm 1
 //
 // One workgroup = WGM x WGN wavefronts (8 by default: two per SIMD); each wavefront owns
-// a (BM/WGM) x (BN/WGN) block of C as 32 x 32 MFMA tiles.  K advances in steps of 64.
-// Operand panels go from HBM straight into LDS (buffer loads with an LDS destination, no
-// register staging), in a ring of STAGES slots: while the MFMAs consume step k the loads
-// fill the steps up to k + STAGES - 1.
+// a (BM/WGM) x (BN/WGN) block of C.  K advances in steps of 64.  Operand panels go from HBM
+// straight into LDS (buffer loads with an LDS destination, no register staging).  Two main
+// loops: PpTile, 256 x 256 accumulators of 16 x 16 x 32 MFMAs with the two wavefronts of a
+// SIMD alternating between MFMAs and memory (products that fill the chip with such tiles),
+// and gemm_tile, 32 x 32 x 16 MFMAs on smaller tiles with a ring of STAGES slots: while the
+// MFMAs consume step k the loads fill the steps up to k + STAGES - 1.
 //
 // LDS layouts.  LDS has 64 banks of 4 bytes, so a byte address maps to bank window
 // position (address mod 256).  A [M, K] and "NT" B [N, K] panels are rows of 64 bf16
@@ -28,7 +30,9 @@
 // columns base + 4 (s % 4), and lane t receives column base + t of rows kbase..kbase+3,
 // i.e. four consecutive contraction indices of one output column -- no transpose pass
 // over HBM and no register shuffles.  Every LDS address is a per-lane base XOR a
-// wave-uniform constant plus an immediate offset.
+// wave-uniform constant plus an immediate offset.  (PpTile's 16-column blocks read 8 rows x
+// 32 bytes per half-wave, rows r .. r + 3 and r + 8 .. r + 11: its chunk XOR takes bit 3 of
+// the row too.)
 //
 // Tails.  Rows or columns past M / N are clamped to the last valid one on load (finite
 // values, results never stored).  K must be a multiple of 64: the gated product Hs is
@@ -46,6 +50,8 @@ namespace tsp {
 namespace {
 
 constexpr int BK = 64;
+template <int N>
+using Ic = std::integral_constant<int, N>;
 enum { EPI_SWIGLU = 0, EPI_ACC = 1, EPI_QKV = 2, EPI_SWIGLU_BWD = 3 };
 
 // Wait until at most N of this wavefront's operand loads are still in flight (loads
@@ -61,7 +67,9 @@ struct Cfg {
   static constexpr int WAVES = WGM * WGN, THREADS = kWave * WAVES;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int TM = WM / 32, TN = WN / 32;
-  static constexpr bool BWD = EPI == EPI_SWIGLU_BWD;
+  // Output columns of a wavefront: 32-column block j starts at wn COL_WN + j COL_BLK.
+  static constexpr int COL_WN = WN, COL_BLK = 32;
+  static constexpr bool BWD = EPI == EPI_SWIGLU_BWD, MFMA16 = false;
   static constexpr int NAP = BWD ? 2 : 1;                                  // A panels
   static constexpr int NBP = EPI == EPI_SWIGLU ? 2 : (BWD ? 3 : 1);        // B panels
   static constexpr int TNB = NBP * TN;
@@ -101,6 +109,7 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 // Chunk swizzles of the NT and NN panels (physical chunk = logical chunk XOR swz(row)).
 __device__ __forceinline__ int nt_swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int nn_swz(int row) { return 4 * (row & 3); }
+__device__ __forceinline__ int nn_swz16(int row) { return 4 * (row & 3) + 2 * ((row >> 3) & 1); }
 
 // Operand panels go HBM -> LDS through buffer loads with an LDS destination (lds_dma.h):
 // address = resource base (the matrix) + scalar offset (the stage's K position) + a
@@ -181,9 +190,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Epilogue of one C tile (configuration C: WAVES, WM, WN, TM, TN, TNB, LDS_BYTES, BWD)
 // from the accumulators of each wavefront, staged through the workgroup's LDS (free:
 // every operand read has completed).
-template <class C, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmParams& P, f32x16 (&acc)[C::TM][C::TNB],
-                                              char* L, const int wave, const int lane,
+template <class C, int EPI, class Acc>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, char* L, const int wave, const int lane,
                                               const int m0, const int n0, const int wm,
                                               const int wn, const int split = 0) {
   constexpr int TM = C::TM, TN = C::TN;
@@ -197,7 +205,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, f32x16 (&acc)
   constexpr int PER_LANE = 32 * CPR / kWave;
   static_assert(C::WAVES * 32 * EST * 4 <= C::LDS_BYTES, "epilogue staging fits");
   float* E = reinterpret_cast<float*>(L) + wave * 32 * EST;
-  const int ncol0 = n0 + wn * C::WN;
+  const int ncol0 = n0 + wn * C::COL_WN;
   if constexpr (C::BWD) {
     // SwiGLU backward.  Per 32-row block: dG, dU and Hs replace G, U and dHs in the
     // accumulators, then each goes through LDS once: dG and dU to their row-major
@@ -257,17 +265,29 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, f32x16 (&acc)
     }
     return;
   }
+  auto value = [](float v, float up) __attribute__((always_inline)) {
+    if constexpr (EPI == EPI_SWIGLU) v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * up;
+    return v;
+  };
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
+    if constexpr (C::MFMA16) {  // 16 x 16 blocks [row block][column block], TNB / 2 panels wide
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float v = acc[i][j][e];
-        if constexpr (EPI == EPI_SWIGLU)
-          v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * acc[i][j + TN][e];
-        E[(8 * (e >> 2) + 4 * hh + (e & 3)) * EST + 32 * j + l32] = v;
-      }
+        for (int j = 0; j < 2 * TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            E[(16 * q + 4 * (lane >> 4) + e) * EST + 16 * j + (lane & 15)] =
+                value(acc[2 * i + q][j][e], EPI == EPI_SWIGLU ? acc[2 * i + q][j + 2 * TN][e] : 0.f);
+    } else {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          E[(8 * (e >> 2) + 4 * hh + (e & 3)) * EST + 32 * j + l32] =
+              value(acc[i][j][e], EPI == EPI_SWIGLU ? acc[i][j + TN][e] : 0.f);
+    }
     wave_lds_sync();
     const int mrow0 = m0 + wm * C::WM + 32 * i;
     // Q/K/V scatter: batch entry and token of the block's first row, once per block (a row
@@ -285,7 +305,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, f32x16 (&acc)
       const int idx = q * kWave + lane, row = idx / CPR, c4 = idx % CPR;
       v[q] = *reinterpret_cast<const f32x4*>(E + row * EST + 4 * c4);
       mm[q] = mrow0 + row;
-      nn[q] = ncol0 + 4 * c4;
+      nn[q] = ncol0 + (c4 / 8) * C::COL_BLK + 4 * (c4 % 8);
       ok[q] = mm[q] < P.M && nn[q] < P.N;
     }
     if constexpr (EPI == EPI_ACC) {
@@ -593,11 +613,347 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
   gemm_epilogue<C, EPI>(P, acc, L, wave, lane, m0, n0, wm, wn, split);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
-__global__ __launch_bounds__(kWave * WGM * WGN) void gemm_kernel(const GemmParams P) {
-  const int tiles = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
-  const int items = EPI == EPI_ACC && P.k_splits > 1 ? tiles * P.k_splits : tiles;
-  gemm_tile<BM, BN, WGM, WGN, NN, EPI, STAGES>(P, xcd_work_index(blockIdx.x, items));
+// The tiles of gemm_tile as a kernel configuration.
+template <int BM_, int BN_, int WGM, int WGN, bool NN_, int EPI_, int STAGES>
+struct Tile {
+  static constexpr int BM = BM_, BN = BN_, EPI = EPI_, THREADS = kWave * WGM * WGN;
+  static constexpr bool NN = NN_;
+  static __device__ __forceinline__ void run(const GemmParams& P, int w) {
+    gemm_tile<BM, BN, WGM, WGN, NN, EPI, STAGES>(P, w);
+  }
+};
+
+// ------------------------------------------------------------------ alternating tiles
+// 256 x 256 accumulators (SwiGLU: 256 x 128 gate and as many up) on 8 wavefronts, each
+// 128 x 64, in which the two wavefronts of a SIMD take turns: while one issues the MFMAs
+// of a quarter of its K step (64 x 32 of its output, 256 matrix cycles), the other reads
+// the operands of its next quarter and issues loads, and a barrier swaps the roles.  With
+// both free to run (gemm_tile) they stop together at the step's barrier, at its wait for
+// the next stage and at its first operand reads, and the matrix pipe stops with them.
+//
+// What bounds it: on operands of zeros it is the issue schedule (gate+up 4096 x 57344 x
+// 8192: 1674 TFLOP/s with gemm_tile, 1979 with this schedule on 32 x 32 x 16 MFMAs, 1941 on
+// 16 x 16 x 32), on real data the power limit, which lowers the clock: there the schedule
+// alone gained nothing (1309 and 1310) and the MFMA shape decides.  A 16 x 16 x 32 MFMA
+// reads and writes half the accumulator bytes per product of a 32 x 32 x 16 one: 1458
+// TFLOP/s.  Same for the [K, N] operand (down, 4096 x 8192 x 28672): 1148, 1278, 1325.
+//
+// LDS: every operand panel of a 64-deep stage is two units of 16 KB (A0, A1: the first and
+// second 64 rows of each wavefront row's 128; B0, B1: each wavefront's first and second 32
+// columns), two stages of each.  A unit is refilled as soon as both wavefront groups
+// hold it in registers, one unit per quarter, so a load has five quarters (1.25 steps,
+// about 2600 cycles) to arrive and the CU's load path is asked for 16 KB at a time instead
+// of a whole stage at once.
+//
+// Quarters of step k, with F = B(k mod 2) and S the other B unit (alternating, so that the
+// F of the next step can be read into registers while the last quarter still uses S's
+// successor):
+//            operands   MEM reads   MEM loads (unit of stage)
+//   Q0       A0 x F     A0          A1 of k + 1
+//   Q1       A0 x S     S           F  of k + 2
+//   Q2       A1 x S     A1          A0 of k + 2
+//   Q3       A1 x F     F' of k+1   S  of k + 2
+// where F' = B((k + 1) mod 2).  Order of the slots (X: wavefronts 0-3, Y: 4-7, one of each
+// per SIMD): X MEM(Q0) | X MFMA(Q0), Y MEM(Q0) | X MEM(Q1), Y MFMA(Q0) | ...  A unit read
+// in X's slot t and Y's slot t + 1 is in registers by the barrier that ends slot t + 2 (both
+// wait for their LDS reads before their MFMAs), and its refill is issued in slot t + 4 at
+// the earliest.  A unit read in slot t (X) was waited for by every wavefront in its MEM
+// slot before, i.e. ahead of the barrier that ends slot t - 1: five units are issued after
+// it by then, two loads each per wavefront, hence vmcnt(10).
+template <bool NN_, int EPI_>
+struct PpTile {
+  static constexpr bool NN = NN_;
+  static constexpr int EPI = EPI_;
+  static constexpr bool SW = EPI == EPI_SWIGLU;
+  static constexpr int BM = 256, BN = SW ? 128 : 256, WGM = 2, WGN = 4;
+  static constexpr int WAVES = 8, THREADS = kWave * WAVES;
+  static constexpr int WM = 128, WN = SW ? 32 : 64, TM = 4, TN = WN / 32, TNB = 2;
+  // NN units are 128 consecutive columns, so a wavefront's second 32 columns are 128 on.
+  static constexpr int COL_WN = NN ? 32 : WN, COL_BLK = NN ? 128 : 32;
+  static constexpr bool BWD = false, MFMA16 = true;
+  static constexpr int UNIT = 128 * BK * 2;
+  static constexpr int LDS_BYTES = 8 * UNIT;  // A units [stage parity][half], then B units
+  static __device__ __forceinline__ void run(const GemmParams& P, int w);
+};
+
+template <bool NN_, int EPI_>
+__device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, const int w) {
+  using C = PpTile<NN_, EPI_>;
+  __shared__ __attribute__((aligned(1024))) char L[C::LDS_BYTES];
+  lds_char* Ls = (lds_char*)L;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int l32 = lane & 31, hh = lane >> 5;
+
+  const int tiles_n = (P.N + BN - 1) / BN;
+  int split = 0, wt = w;
+  if (EPI == EPI_ACC && P.k_splits > 1) {
+    const int tiles = ((P.M + BM - 1) / BM) * tiles_n;
+    split = w / tiles;
+    wt = w - split * tiles;
+  }
+  int tm, tn;
+  tile_coords(wt, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  // Contraction steps [kb, kb + nk); step kt of the tile lives in slot kt mod 2.
+  int kb = 0, nk = P.K / BK;
+  if (EPI == EPI_ACC && P.k_splits > 1) {
+    const int all = nk;
+    kb = split * all / P.k_splits;
+    nk = (split + 1) * all / P.k_splits - kb;
+  }
+
+  // Per-lane load offsets.  Load i (of two) of a unit: LDS rows 8 (8 i + wave) + lane / 8
+  // for 128-byte rows, 4 (8 i + wave) + lane / 16 for the 256-byte rows of an NN unit.
+  uint32_t off_a[2][2], off_b[2][2];
+  int kr[2];  // NN: this lane's k row in the unit
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = 8 * (8 * i + wave) + (lane >> 3), pc = (lane & 7) ^ nt_swz(r);
+    const int rn = 4 * (8 * i + wave) + (lane >> 4), pn = (lane & 15) ^ nn_swz16(rn);
+    kr[i] = rn;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t ga = (uint32_t)min(m0 + (r >> 6) * 128 + u * 64 + (r & 63), P.M - 1);
+      off_a[u][i] = 2u * (ga * (uint32_t)P.lda + 8u * (uint32_t)pc);
+      if constexpr (NN) {
+        const uint32_t gn = (uint32_t)min(n0 + 128 * u + 8 * pn, P.N - 8);
+        off_b[u][i] = 2u * ((uint32_t)rn * (uint32_t)P.ldb + gn);
+      } else {
+        const int col = SW ? r : (r >> 5) * 64 + u * 32 + (r & 31);
+        const uint32_t gb = (uint32_t)min(n0 + col, P.N - 1);
+        off_b[u][i] = 2u * (gb * (uint32_t)P.ldb + 8u * (uint32_t)pc);
+      }
+    }
+  }
+  // The stages in load order: a cursor over the parts of a multi-part contraction (operand
+  // pair and column within it), whose operands are chosen from scalar registers whenever a
+  // part ends.  A1 of a stage is loaded after the cursor has moved on for the other units,
+  // so the stage's A resource and column are kept for it.
+  int k_part = INT_MAX, cur_part = 0, cur_k = kb * BK;
+  rsrc_t rs_a = make_rsrc(P.A), rs_b = make_rsrc(P.B);
+  const rsrc_t rs_b2 = make_rsrc(SW ? P.B2 : P.B);
+  rsrc_t cur_a = rs_a;
+  uint32_t a_k0 = 0;
+  int b_k0 = 0;
+  auto set_part = [&]() __attribute__((always_inline)) {
+    if constexpr (NN) {
+      const uint16_t* pa = P.A_part[0];
+      const uint16_t* pb = P.B_part[0];
+#pragma unroll
+      for (int i = 1; i < kGemmPartsMax; ++i) {
+        pa = cur_part == i ? P.A_part[i] : pa;
+        pb = cur_part == i ? P.B_part[i] : pb;
+      }
+      cur_a = make_rsrc(pa);
+      rs_b = make_rsrc(pb);
+    }
+  };
+  if (NN && P.n_parts > 1) {
+    k_part = P.k_part;
+    cur_part = cur_k / k_part;
+    cur_k -= cur_part * k_part;
+    set_part();
+  }
+  auto next_stage = [&]() __attribute__((always_inline)) {
+    if (NN && cur_k >= k_part) {
+      cur_k = 0;
+      ++cur_part;
+      set_part();
+    }
+    rs_a = cur_a;
+    a_k0 = (uint32_t)cur_k;
+    b_k0 = cur_k;
+    cur_k += BK;
+  };
+  // Unit u of the stage into slot S.
+  auto load_a = [&](auto slot, auto half) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value, U = decltype(half)::value;
+    lds_char* dst = Ls + (2 * S + U) * UNIT + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) dma16(rs_a, off_a[U][i], 2u * a_k0, dst + i * 8192);
+  };
+  auto load_b = [&](auto slot, auto half) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value, U = decltype(half)::value;
+    lds_char* dst = Ls + (4 + 2 * S + U) * UNIT + wave * 1024;
+    if constexpr (NN) {
+      if (b_k0 + BK <= P.Kb_rows) {
+        const uint32_t soff = 2u * (uint32_t)b_k0 * (uint32_t)P.ldb;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dma16(rs_b, off_b[U][i], soff, dst + i * 8192);
+      } else {  // rows past Kb_rows repeat the last one
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int gk = min(b_k0 + kr[i], P.Kb_rows - 1);
+          dma16(rs_b, off_b[U][i] + 2u * (uint32_t)(gk - kr[i]) * (uint32_t)P.ldb, 0u,
+                dst + i * 8192);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        dma16(SW && U == 1 ? rs_b2 : rs_b, off_b[U][i], 2u * (uint32_t)b_k0, dst + i * 8192);
+    }
+  };
+
+  // Operand reads (slots and units are immediates).  A and NT B: row 16 x + lane % 16 of a
+  // unit, chunk 4 t + lane / 16 of contraction step t (32 indices).  NN B: transpose reads
+  // of k rows 32 t + 8 (lane / 16) + .. at 16 columns.
+  int ra[2], rb[2], nb[2][2];
+  {
+    const int l16 = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int op = l16 * 128 + 16 * ((4 * t + g) ^ nt_swz(l16));
+      ra[t] = wm * 64 * 128 + op;
+      rb[t] = 4 * UNIT + wn * 32 * 128 + op;
+    }
+    if constexpr (NN) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = 8 * g + 4 * h + (l16 >> 2), cl = (l16 & 3) >> 1;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          nb[j][h] = 4 * UNIT + r * 256 + 16 * ((4 * wn + 2 * j + cl) ^ nn_swz16(r)) + 8 * (l16 & 1);
+      }
+    }
+  }
+  u32x4 a[2][4][2], b[2][2][2];  // [unit][16-row / column block][contraction step]
+  auto read_a = [&](auto slot, auto half) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value, U = decltype(half)::value;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a[U][i][t] = lds_read16(Ls + ra[t] + ((2 * S + U) * UNIT + i * 16 * 128));
+  };
+  auto read_b = [&](auto slot, auto half) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value, U = decltype(half)::value;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if constexpr (NN) {
+          const u32x2 lo = lds_read_tr(Ls + nb[j][0] + ((2 * S + U) * UNIT + t * 32 * 256));
+          const u32x2 hi = lds_read_tr(Ls + nb[j][1] + ((2 * S + U) * UNIT + t * 32 * 256));
+          b[U][j][t] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        } else {
+          b[U][j][t] = lds_read16(Ls + rb[t] + ((2 * S + U) * UNIT + j * 16 * 128));
+        }
+      }
+  };
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+
+  auto swap_slot = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Ends a MEM slot, issues the quarter's MFMAs and ends their slot.  The wait for the LDS
+  // reads comes before the MFMAs in every quarter, also where they are for the next step:
+  // the units' refills rely on it.
+  auto quarter = [&](auto half_a, auto half_b) __attribute__((always_inline)) {
+    constexpr int UA = decltype(half_a)::value, UB = decltype(half_b)::value;
+    swap_slot();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[4 * UA + i][2 * UB + j] =
+              mfma16(a[UA][i][t], b[UB][j][t], acc[4 * UA + i][2 * UB + j]);
+    __builtin_amdgcn_s_setprio(0);
+    swap_slot();
+  };
+  // Step in slot S (F = B unit S) with `left` steps left, this one included: the last two
+  // have nothing (or only A1 of the last) to load and wait for what is still in flight.
+  auto step = [&](auto slot, const int left) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value;
+    constexpr Ic<S> s{};
+    constexpr Ic<1 - S> o{};
+    constexpr Ic<0> i0{};
+    constexpr Ic<1> i1{};
+    read_a(s, i0);
+    if (left >= 2) {
+      load_a(o, i1);
+      wait_dma<10>();
+    } else {
+      wait_dma<0>();
+    }
+    quarter(i0, s);
+    read_b(s, o);
+    if (left >= 3) {
+      next_stage();
+      load_b(s, s);
+      wait_dma<10>();
+    } else if (left == 2) {
+      wait_dma<8>();
+    }
+    quarter(i0, o);
+    read_a(s, i1);
+    if (left >= 3) {
+      load_a(s, i0);
+      wait_dma<10>();
+    } else if (left == 2) {
+      wait_dma<6>();
+    }
+    quarter(i1, o);
+    read_b(o, o);  // (the last step reads a unit it does not use)
+    if (left >= 3) {
+      load_b(s, o);
+      wait_dma<10>();
+    } else if (left == 2) {
+      wait_dma<4>();
+    }
+    quarter(i1, s);
+  };
+
+  constexpr Ic<0> s0{};
+  constexpr Ic<1> s1{};
+  next_stage();
+  load_b(s0, s0);
+  load_a(s0, s0);
+  load_b(s0, s1);
+  load_a(s0, s1);
+  if (nk > 1) {
+    next_stage();
+    load_b(s1, s1);
+    load_a(s1, s0);
+    load_b(s1, s0);
+    wait_dma<10>();
+  } else {
+    wait_dma<4>();
+  }
+  swap_slot();  // B0 and A0 of step 0 resident
+  read_b(s0, s0);
+  if (wave >= 4) swap_slot();  // Y runs one slot behind X
+  for (int left = nk; left > 0; left -= 2) {
+    step(s0, left);
+    if (left > 1) step(s1, left - 1);
+  }
+  if (wave < 4) swap_slot();
+  __syncthreads();  // operand units are free for the epilogue
+
+  gemm_epilogue<C, EPI>(P, acc, L, wave, lane, m0, n0, wm, wn, split);
+}
+
+template <class K>
+__global__ __launch_bounds__(K::THREADS) void gemm_kernel(const GemmParams P) {
+  const int tiles = ((P.M + K::BM - 1) / K::BM) * ((P.N + K::BN - 1) / K::BN);
+  const int items = K::EPI == EPI_ACC && P.k_splits > 1 ? tiles * P.k_splits : tiles;
+  K::run(P, xcd_work_index(blockIdx.x, items));
 }
 
 // Y = base + sum of the k_splits partial products in range order (base and U as in the
@@ -633,12 +989,12 @@ struct GemmGroup {
   int n;
 };
 static_assert(sizeof(GemmGroup) <= 4096, "kernel argument size limit");
-template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
-__global__ __launch_bounds__(kWave * WGM * WGN) void gemm_group_kernel(const GemmGroup G) {
+template <class K>
+__global__ __launch_bounds__(K::THREADS) void gemm_group_kernel(const GemmGroup G) {
   int tiles[kGemmGroupMax], total = 0;
 #pragma unroll
   for (int i = 0; i < kGemmGroupMax; ++i) {
-    tiles[i] = i < G.n ? ((G.p[i].M + BM - 1) / BM) * ((G.p[i].N + BN - 1) / BN) : 0;
+    tiles[i] = i < G.n ? ((G.p[i].M + K::BM - 1) / K::BM) * ((G.p[i].N + K::BN - 1) / K::BN) : 0;
     total += tiles[i];
   }
   int w = xcd_work_index(blockIdx.x, total), i = 0;
@@ -647,21 +1003,21 @@ __global__ __launch_bounds__(kWave * WGM * WGN) void gemm_group_kernel(const Gem
   // arguments), the compiler reloads every field after each global store of the epilogue
   // (it cannot rule out aliasing), hundreds of serialized scalar loads per tile.
   const GemmParams P = G.p[i];
-  gemm_tile<BM, BN, WGM, WGN, NN, EPI, STAGES>(P, w);
+  K::run(P, w);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
+template <class K>
 hipError_t check_params(const GemmParams& p) {
   if (p.K <= 0 || p.K % BK != 0) return hipErrorInvalidValue;
   // The operand loads address each operand with 32-bit byte offsets from its base.
   constexpr long long kMaxBytes = 1LL << 32;
-  const long long b_rows = NN ? (long long)p.Kb_rows : (long long)p.N;
+  const long long b_rows = K::NN ? (long long)p.Kb_rows : (long long)p.N;
   if ((long long)p.M * p.lda * 2 >= kMaxBytes || b_rows * p.ldb * 2 >= kMaxBytes)
     return hipErrorInvalidValue;
-  if (p.k_splits > 1 && (EPI != EPI_ACC || !p.part || p.N % 4 != 0 || p.k_splits > p.K / BK))
+  if (p.k_splits > 1 && (K::EPI != EPI_ACC || !p.part || p.N % 4 != 0 || p.k_splits > p.K / BK))
     return hipErrorInvalidValue;
   if (p.n_parts > 1) {
-    if (!NN || p.n_parts > kGemmPartsMax || p.k_part <= 0 || p.k_part % BK != 0 ||
+    if (!K::NN || p.n_parts > kGemmPartsMax || p.k_part <= 0 || p.k_part % BK != 0 ||
         (long long)p.n_parts * p.k_part != p.K)
       return hipErrorInvalidValue;
     for (int i = 0; i < p.n_parts; ++i)
@@ -670,41 +1026,38 @@ hipError_t check_params(const GemmParams& p) {
   return hipSuccess;
 }
 
-template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
+template <class K>
 hipError_t launch_group(const GemmParams* ps, int n, hipStream_t s) {
-  using C = Cfg<BM, BN, WGM, WGN, NN, EPI, STAGES>;
   if (n < 1 || n > kGemmGroupMax) return hipErrorInvalidValue;
   GemmGroup g = {};
   long long total = 0;
   for (int i = 0; i < n; ++i) {
     const GemmParams& p = ps[i];
     if (p.M <= 0 || p.N <= 0) return hipErrorInvalidValue;
-    const hipError_t e = check_params<BM, BN, WGM, WGN, NN, EPI, STAGES>(p);
+    const hipError_t e = check_params<K>(p);
     if (e != hipSuccess) return e;
     g.p[i] = p;
-    total += (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
+    total += (long long)((p.M + K::BM - 1) / K::BM) * ((p.N + K::BN - 1) / K::BN);
   }
   g.n = n;
   if (total > INT32_MAX) return hipErrorInvalidValue;
   void* args[] = {&g};
-  return hipLaunchKernel(
-      reinterpret_cast<const void*>(&gemm_group_kernel<BM, BN, WGM, WGN, NN, EPI, STAGES>),
-      dim3((unsigned)total), dim3(C::THREADS), args, 0, s);
+  return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_group_kernel<K>),
+                         dim3((unsigned)total), dim3(K::THREADS), args, 0, s);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
+template <class K>
 hipError_t launch(const GemmParams& p, hipStream_t s) {
-  using C = Cfg<BM, BN, WGM, WGN, NN, EPI, STAGES>;
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  const hipError_t e = check_params<BM, BN, WGM, WGN, NN, EPI, STAGES>(p);
+  const hipError_t e = check_params<K>(p);
   if (e != hipSuccess) return e;
-  long long tiles = (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-  if (EPI == EPI_ACC && p.k_splits > 1) tiles *= p.k_splits;
+  long long tiles = (long long)((p.M + K::BM - 1) / K::BM) * ((p.N + K::BN - 1) / K::BN);
+  if (K::EPI == EPI_ACC && p.k_splits > 1) tiles *= p.k_splits;
   if (tiles > INT32_MAX) return hipErrorInvalidValue;
   // hipLaunchKernel returns the status of this launch only (not an earlier error).
   void* args[] = {const_cast<GemmParams*>(&p)};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, NN, EPI, STAGES>),
-                         dim3((unsigned)tiles), dim3(C::THREADS), args, 0, s);
+  return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_kernel<K>),
+                         dim3((unsigned)tiles), dim3(K::THREADS), args, 0, s);
 }
 
 long long tiles_of(const GemmParams* ps, int n, int bm, int bn) {
@@ -718,11 +1071,11 @@ long long tiles_of(const GemmParams* ps, int n, int bm, int bn) {
 
 // Tile shapes are chosen for the grouped shard products of the 7B-class layer on 256
 // CUs (one workgroup per CU).  Gate+up (M = S_loc, N = F/D = 1376 per shard, 8 shards
-// per launch) takes 256 x 128 tiles (256 x 256 accumulators: gate and up) with a 2-slot
-// ring when they make at least 4 rounds (S_loc = 8192: 2816 tiles), else 128 x 128 tiles
+// per launch) takes the alternating tiles of 256 x 128 (256 x 256 accumulators: gate and
+// up) when they make at least 4 rounds (S_loc = 8192: 2816 tiles), else 128 x 128 tiles
 // with a 3-slot ring;
-// Q/K/V (N = 3 d H_s = 1536 per shard) 256 x 256 tiles when they make two rounds or more
-// (S_loc = 8192: 1536 tiles), else 256 x 192 (S_loc = 1024: 256 tiles, one per CU) or,
+// Q/K/V (N = 3 d H_s = 1536 per shard) 256 x 256 alternating tiles when they make two
+// rounds or more (S_loc = 8192: 1536 tiles), else 256 x 192 (S_loc = 1024: 256 tiles, one per CU) or,
 // below one tile per CU, 128 x 128; down / O-proj (N = h = 4096)
 // 256 x 256 tiles (512 at S_loc = 8192), their contraction split when that makes fewer
 // tiles than CUs.
@@ -734,11 +1087,11 @@ hipError_t launch_gemm_swiglu(const GemmParams& p, hipStream_t s) {
 
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s) {
   if (tiles_of(ps, n, 256, 128) >= 4 * kCus) {
-    if (n == 1) return launch<256, 128, 2, 4, false, EPI_SWIGLU, 2>(ps[0], s);
-    return launch_group<256, 128, 2, 4, false, EPI_SWIGLU, 2>(ps, n, s);
+    if (n == 1) return launch<PpTile<false, EPI_SWIGLU>>(ps[0], s);
+    return launch_group<PpTile<false, EPI_SWIGLU>>(ps, n, s);
   }
-  if (n == 1) return launch<128, 128, 2, 4, false, EPI_SWIGLU, 3>(ps[0], s);
-  return launch_group<128, 128, 2, 4, false, EPI_SWIGLU, 3>(ps, n, s);
+  if (n == 1) return launch<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps[0], s);
+  return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, s);
 }
 
 // Below one 256 x 256 output tile per CU (short sequences: M = S_loc = 1024 and N = h =
@@ -760,17 +1113,17 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
   if (splits == 1) {
     GemmParams q = p;
     q.k_splits = 1;
-    return launch<256, 256, 2, 4, true, EPI_ACC, 2>(q, s);
+    return launch<PpTile<true, EPI_ACC>>(q, s);
   }
   if (!part) {  // no workspace: the whole contraction per tile, on 128 x 128 tiles
     GemmParams q = p;
     q.k_splits = 1;
-    return launch<128, 128, 2, 4, true, EPI_ACC, 2>(q, s);
+    return launch<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(q, s);
   }
   GemmParams q = p;
   q.k_splits = splits;
   q.part = part;
-  hipError_t e = launch<256, 256, 2, 4, true, EPI_ACC, 2>(q, s);
+  hipError_t e = launch<PpTile<true, EPI_ACC>>(q, s);
   if (e != hipSuccess) return e;
   const long long threads = (long long)p.M * (p.N / 4);
   void* args[] = {&q};
@@ -782,18 +1135,18 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
 // per K step (X, dY; W1, W3, W2), two slots = 160 KB.
 hipError_t launch_gemm_swiglu_bwd(const GemmParams& p, hipStream_t s) {
   if (p.ldt % 8 != 0 || p.ldt < p.M) return hipErrorInvalidValue;
-  return launch<128, 128, 2, 4, false, EPI_SWIGLU_BWD, 2>(p, s);
+  return launch<Tile<128, 128, 2, 4, false, EPI_SWIGLU_BWD, 2>>(p, s);
 }
 
 // Weight gradients (M = F/D, N = h, K = tokens): 128 x 128 tiles make 352 at the 7B
 // shape where 256 x 256 would make 96.
 hipError_t launch_gemm_nn_acc_small(const GemmParams& p, hipStream_t s) {
-  return launch<128, 128, 2, 4, true, EPI_ACC, 2>(p, s);
+  return launch<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(p, s);
 }
 
 // Several weight-gradient products in one launch (each with M = F/D or H_s d rows).
 hipError_t launch_gemm_nn_acc_small_group(const GemmParams* ps, int n, hipStream_t s) {
-  return launch_group<128, 128, 2, 4, true, EPI_ACC, 2>(ps, n, s);
+  return launch_group<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(ps, n, s);
 }
 
 // Projections with few output tiles (the backward's Q and dA products, N = H_s d; GQA
@@ -806,15 +1159,15 @@ hipError_t launch_gemm_qkv(const GemmParams& p, hipStream_t s) {
 
 hipError_t launch_gemm_qkv_group(const GemmParams* ps, int n, hipStream_t s) {
   if (tiles_of(ps, n, 256, 256) >= 2 * kCus) {
-    if (n == 1) return launch<256, 256, 2, 4, false, EPI_QKV, 2>(ps[0], s);
-    return launch_group<256, 256, 2, 4, false, EPI_QKV, 2>(ps, n, s);
+    if (n == 1) return launch<PpTile<false, EPI_QKV>>(ps[0], s);
+    return launch_group<PpTile<false, EPI_QKV>>(ps, n, s);
   }
   if (tiles_of(ps, n, 256, 192) < kCus) {
-    if (n == 1) return launch<128, 128, 2, 4, false, EPI_QKV, 2>(ps[0], s);
-    return launch_group<128, 128, 2, 4, false, EPI_QKV, 2>(ps, n, s);
+    if (n == 1) return launch<Tile<128, 128, 2, 4, false, EPI_QKV, 2>>(ps[0], s);
+    return launch_group<Tile<128, 128, 2, 4, false, EPI_QKV, 2>>(ps, n, s);
   }
-  if (n == 1) return launch<256, 192, 4, 2, false, EPI_QKV, 2>(ps[0], s);
-  return launch_group<256, 192, 4, 2, false, EPI_QKV, 2>(ps, n, s);
+  if (n == 1) return launch<Tile<256, 192, 4, 2, false, EPI_QKV, 2>>(ps[0], s);
+  return launch_group<Tile<256, 192, 4, 2, false, EPI_QKV, 2>>(ps, n, s);
 }
 
 }  // namespace tsp

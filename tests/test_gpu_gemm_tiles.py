@@ -1,0 +1,59 @@
+"""The GEMM tile variants at the edges of their ranges, through the C ABI, against 64-bit
+products of the same bf16 operands on the GPU: contractions of one, two, three and more
+64-deep stages, ragged rows and columns, contraction widths padded to a stage.
+
+Bound: one bf16 rounding (relative error at most 2^-9) of the gated product, or of the
+result for Q/K/V, and fp32 sums of at most a few thousand terms (relative error far below
+it) keep the 2-norm of the difference below 2^-8 of the result's."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2604_26294_amd import tsp as T  # noqa: E402
+
+BOUND = 2.0 ** -8
+
+
+def _normal(seed, *shape, std=1.0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+
+
+def _rel(got, ref):
+    return ((got.double() - ref).norm() / ref.norm()).item()
+
+
+# 16387 rows make 65 row tiles of 256.  Gate+up in alternating tiles (>= 1024 tiles of 256 x
+# 128) with contractions of 1, 2, 3 and 5 stages; down projections in them (>= 256 tiles of
+# 256 x 256) with 1, 2, 3, 4 (200 columns padded to 256) stages.
+@pytest.mark.parametrize("m,h,f", [(16387, 64, 2056), (16387, 128, 2056), (16387, 192, 2056),
+                                   (16387, 320, 2056), (16387, 1024, 64), (16387, 1024, 128),
+                                   (16387, 1024, 192), (16387, 1024, 200)])
+def test_mlp_tiles(m, h, f):
+    print(f"[mlp tiles] {m} x {h} x {f}", flush=True)
+    sh = T.make_shape(1, m, h, f, h // 64, h // 64, 64, 1, 0)
+    x = _normal(1, m, h)
+    g, u, d = (_normal(k, f, h, std=h ** -0.5) for k in (2, 3, 4))
+    y = torch.full((m, h), float("nan"), device="cuda")
+    ws = torch.empty(T.workspace_bytes(sh, T.OP_MLP), dtype=torch.uint8, device="cuda")
+    T.tsp_mlp_rank_fwd(sh, x, [g], [u], [d], y, False, ws)
+    xd = x.double()
+    ref = (torch.nn.functional.silu(xd @ g.double().T) * (xd @ u.double().T)) @ d.double()
+    assert _rel(y, ref) < BOUND
+
+
+@pytest.mark.parametrize("m,heads", [(16387, 16), (8200, 16)])
+def test_kv_projection_tiles(m, heads):
+    """K and V rows of one rank (D = 1): 256 x 256 tiles from two rounds, 256 x 192 below."""
+    print(f"[kv tiles] {m} x {heads} heads", flush=True)
+    h = 64 * heads
+    sh = T.make_shape(1, m, h, 64, heads, heads, 64, 1, 0)
+    x, wa = _normal(1, m, h), _normal(2, 4 * h, h, std=h ** -0.5)
+    k = torch.full((1, m, heads, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    v = torch.full_like(k, float("nan"))
+    T.tsp_kv_rank_fwd(sh, x, [wa], k, v)
+    for got, w in ((k, wa[h:2 * h]), (v, wa[2 * h:3 * h])):
+        assert _rel(got.view(m, h), x.double() @ w.double().T) < BOUND
