@@ -239,7 +239,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
           for (int r = 0; r < PER_LANE; ++r) {
             const int idx = r * kWave + lane, row = idx / CPR, c4 = idx % CPR;
             const int mm = mrow0 + row, nn = ncol0 + 4 * c4;
-            if (mm >= P.M || nn >= P.ldh) continue;  // columns N..ldh: zero padding
+            if (mm >= P.M || nn >= P.h_cols) continue;  // columns N..h_cols: zero padding
             const f32x4 v = *reinterpret_cast<const f32x4*>(E + row * EST + 4 * c4);
             *reinterpret_cast<u32x2*>(H + (size_t)mm * P.ldh + nn) =
                 nn < P.N ? u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}
@@ -660,7 +660,9 @@ struct Tile {
 // the earliest.  A unit read in slot t (X) was waited for by every wavefront in its MEM
 // slot before, i.e. ahead of the barrier that ends slot t - 1: five units are issued after
 // it by then, two loads each per wavefront, hence vmcnt(10).
-template <bool NN_, int EPI_>
+// MULTI: the contraction may have several parts or be split into ranges ([K, N] operands,
+// accumulate epilogue).
+template <bool NN_, int EPI_, bool MULTI = false>
 struct PpTile {
   static constexpr bool NN = NN_;
   static constexpr int EPI = EPI_;
@@ -671,14 +673,15 @@ struct PpTile {
   // NN units are 128 consecutive columns, so a wavefront's second 32 columns are 128 on.
   static constexpr int COL_WN = NN ? 32 : WN, COL_BLK = NN ? 128 : 32;
   static constexpr bool BWD = false, MFMA16 = true;
+  static_assert(!MULTI || (NN && EPI == EPI_ACC), "multi-part contractions");
   static constexpr int UNIT = 128 * BK * 2;
   static constexpr int LDS_BYTES = 8 * UNIT;  // A units [stage parity][half], then B units
   static __device__ __forceinline__ void run(const GemmParams& P, int w);
 };
 
-template <bool NN_, int EPI_>
-__device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, const int w) {
-  using C = PpTile<NN_, EPI_>;
+template <bool NN_, int EPI_, bool MULTI>
+__device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& P, const int w) {
+  using C = PpTile<NN_, EPI_, MULTI>;
   __shared__ __attribute__((aligned(1024))) char L[C::LDS_BYTES];
   lds_char* Ls = (lds_char*)L;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -688,7 +691,7 @@ __device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, cons
 
   const int tiles_n = (P.N + BN - 1) / BN;
   int split = 0, wt = w;
-  if (EPI == EPI_ACC && P.k_splits > 1) {
+  if (MULTI && P.k_splits > 1) {
     const int tiles = ((P.M + BM - 1) / BM) * tiles_n;
     split = w / tiles;
     wt = w - split * tiles;
@@ -699,7 +702,7 @@ __device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, cons
 
   // Contraction steps [kb, kb + nk); step kt of the tile lives in slot kt mod 2.
   int kb = 0, nk = P.K / BK;
-  if (EPI == EPI_ACC && P.k_splits > 1) {
+  if (MULTI && P.k_splits > 1) {
     const int all = nk;
     kb = split * all / P.k_splits;
     nk = (split + 1) * all / P.k_splits - kb;
@@ -739,7 +742,7 @@ __device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, cons
   uint32_t a_k0 = 0;
   int b_k0 = 0;
   auto set_part = [&]() __attribute__((always_inline)) {
-    if constexpr (NN) {
+    if constexpr (MULTI) {
       const uint16_t* pa = P.A_part[0];
       const uint16_t* pb = P.B_part[0];
 #pragma unroll
@@ -751,14 +754,14 @@ __device__ __forceinline__ void PpTile<NN_, EPI_>::run(const GemmParams& P, cons
       rs_b = make_rsrc(pb);
     }
   };
-  if (NN && P.n_parts > 1) {
+  if (MULTI && P.n_parts > 1) {
     k_part = P.k_part;
     cur_part = cur_k / k_part;
     cur_k -= cur_part * k_part;
     set_part();
   }
   auto next_stage = [&]() __attribute__((always_inline)) {
-    if (NN && cur_k >= k_part) {
+    if (MULTI && cur_k >= k_part) {
       cur_k = 0;
       ++cur_part;
       set_part();
@@ -1081,10 +1084,6 @@ long long tiles_of(const GemmParams* ps, int n, int bm, int bn) {
 // tiles than CUs.
 constexpr long long kCus = 256;
 
-hipError_t launch_gemm_swiglu(const GemmParams& p, hipStream_t s) {
-  return launch_gemm_swiglu_group(&p, 1, s);
-}
-
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s) {
   if (tiles_of(ps, n, 256, 128) >= 4 * kCus) {
     if (n == 1) return launch<PpTile<false, EPI_SWIGLU>>(ps[0], s);
@@ -1113,7 +1112,7 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
   if (splits == 1) {
     GemmParams q = p;
     q.k_splits = 1;
-    return launch<PpTile<true, EPI_ACC>>(q, s);
+    return launch<PpTile<true, EPI_ACC, true>>(q, s);
   }
   if (!part) {  // no workspace: the whole contraction per tile, on 128 x 128 tiles
     GemmParams q = p;
@@ -1123,7 +1122,7 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
   GemmParams q = p;
   q.k_splits = splits;
   q.part = part;
-  hipError_t e = launch<PpTile<true, EPI_ACC>>(q, s);
+  hipError_t e = launch<PpTile<true, EPI_ACC, true>>(q, s);
   if (e != hipSuccess) return e;
   const long long threads = (long long)p.M * (p.N / 4);
   void* args[] = {&q};
@@ -1133,30 +1132,27 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
 
 // SwiGLU backward (M = S_loc, N = F/D): 128 x 128 tiles with five 16 KB operand panels
 // per K step (X, dY; W1, W3, W2), two slots = 160 KB.
-hipError_t launch_gemm_swiglu_bwd(const GemmParams& p, hipStream_t s) {
-  if (p.ldt % 8 != 0 || p.ldt < p.M) return hipErrorInvalidValue;
-  return launch<Tile<128, 128, 2, 4, false, EPI_SWIGLU_BWD, 2>>(p, s);
+hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t s) {
+  for (int i = 0; i < n; ++i)
+    if (ps[i].ldt % 8 != 0 || ps[i].ldt < ps[i].M) return hipErrorInvalidValue;
+  return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU_BWD, 2>>(ps, n, s);
 }
 
-// Weight gradients (M = F/D, N = h, K = tokens): 128 x 128 tiles make 352 at the 7B
-// shape where 256 x 256 would make 96.
-hipError_t launch_gemm_nn_acc_small(const GemmParams& p, hipStream_t s) {
-  return launch<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(p, s);
-}
-
-// Several weight-gradient products in one launch (each with M = F/D or H_s d rows).
-hipError_t launch_gemm_nn_acc_small_group(const GemmParams* ps, int n, hipStream_t s) {
+// Weight gradients (M = F/D or H_s d, N = h, K = tokens), several products in one launch.
+// The 256 x 256 alternating tiles run at about 1.6 times the rate of the 128 x 128 ones
+// (7B, S_loc = 8192: 1250 and 780 TFLOP/s), so they are taken unless the rounds they
+// make, each of four times the work, leave them slower: products narrower than a tile (70B:
+// K_s d = 128 rows, half of each tile empty) and launches that do not fill the chip.
+hipError_t launch_gemm_nn_acc_group(const GemmParams* ps, int n, hipStream_t s) {
+  const long long big = (tiles_of(ps, n, 256, 256) + kCus - 1) / kCus;
+  const long long small = (tiles_of(ps, n, 128, 128) + kCus - 1) / kCus;
+  if (4 * 10 * big <= 16 * small) return launch_group<PpTile<true, EPI_ACC>>(ps, n, s);
   return launch_group<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(ps, n, s);
 }
 
 // Projections with few output tiles (the backward's Q and dA products, N = H_s d; GQA
 // shapes; short sequences) would leave CUs idle with 256 x 192 tiles: below one tile per
 // CU they take 128 x 128 tiles.
-hipError_t launch_gemm_qkv(const GemmParams& p, hipStream_t s) {
-  if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  return launch_gemm_qkv_group(&p, 1, s);
-}
-
 hipError_t launch_gemm_qkv_group(const GemmParams* ps, int n, hipStream_t s) {
   if (tiles_of(ps, n, 256, 256) >= 2 * kCus) {
     if (n == 1) return launch<PpTile<false, EPI_QKV>>(ps[0], s);

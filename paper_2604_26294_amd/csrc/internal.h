@@ -41,7 +41,8 @@ struct GemmParams {
 
   // SwiGLU backward (fused products G = A B^T, U = A B2^T and dHs = A2 B3^T, all NT
   // with the same K): with s = SiLU(G), s' its derivative,
-  //   dG = dHs * U * s'  and  dU = dHs * s  -> H, H2 [M, ldh] bf16 (columns N..ldh zero),
+  //   dG = dHs * U * s'  and  dU = dHs * s  -> H, H2 [M, h_cols] bf16, rows ldh apart
+  //   (columns N..h_cols zero),
   //   dG^T, dU^T and Hs^T = (s * U)^T       -> T0, T1, T2 [N, ldt] bf16, row n holding
   //   column n of the product for every m < M (columns M..ldt zero).
   const uint16_t* A2;
@@ -90,25 +91,19 @@ struct GemmParams {
   int kv_col0;
 };
 
-hipError_t launch_gemm_swiglu(const GemmParams& p, hipStream_t s);
-// Up to kGemmGroupMax independent products of launch_gemm_swiglu's form in one launch
-// (each must have M, N > 0; the tiles of product i follow those of the ones before it).
+// Up to kGemmGroupMax independent products of one form in one launch (each must have M, N >
+// 0; the tiles of product i follow those of the ones before it).
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s);
-hipError_t launch_gemm_swiglu_bwd(const GemmParams& p, hipStream_t s);
+hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t s);
 // The accumulate epilogue over [K, N] operands.  Products with fewer 256 x 256 output
 // tiles than CUs split their contraction (gemm_nn_acc_splits ranges) through an fp32
 // workspace `part` of at least splits * M * N floats (unused when splits == 1); without
 // one (part == nullptr) they run unsplit on 128 x 128 tiles.
 hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s);
 int gemm_nn_acc_splits(int M, int N, int K);
-// The accumulate epilogue on 128 x 128 tiles, for products with few output tiles
-// (the weight gradients: F/D x h outputs).
-hipError_t launch_gemm_nn_acc_small(const GemmParams& p, hipStream_t s);
-// Up to kGemmGroupMax independent products of launch_gemm_nn_acc_small's form in one
-// launch (each must have M, N > 0).
-hipError_t launch_gemm_nn_acc_small_group(const GemmParams* ps, int n, hipStream_t s);
-hipError_t launch_gemm_qkv(const GemmParams& p, hipStream_t s);
-// Up to kGemmGroupMax products of launch_gemm_qkv's form in one launch.
+// Up to kGemmGroupMax independent accumulate products (one part, no split contraction) in
+// one launch, for the weight gradients (F/D x h or H_s d x h outputs); each must have M, N > 0.
+hipError_t launch_gemm_nn_acc_group(const GemmParams* ps, int n, hipStream_t s);
 hipError_t launch_gemm_qkv_group(const GemmParams* ps, int n, hipStream_t s);
 
 // Causal flash attention of one rank's queries for the heads of one shard.

@@ -104,15 +104,18 @@ tsp_status check_shape(const tsp_shape* s, Dims* o) {
 // contraction; the sum differs from the step-by-step one only in fp32 rounding order.
 // In a streaming schedule G is the number of shards held at once; with every shard
 // resident (one GPU), the default groups min(D, kGroupMax) steps.
-constexpr int kPair = 2;  // the backward's weight and dX products of two steps at once
+// fp32 partial products of a split accumulate product with contraction length k.
+size_t nn_part_bytes(const Dims& d, int k) {
+  const int splits = tsp::gemm_nn_acc_splits((int)d.M, d.h, k);
+  return splits > 1 ? (size_t)splits * d.M * d.h * 4 : 0;
+}
 // fp32 partial products of a split down (output) projection over groups of n steps of
 // k_step contraction columns each, for the group sizes that occur.
 size_t split_part_bytes(const Dims& d, int k_step) {
   size_t most = 0;
   for (const int n : {d.G, d.D % d.G}) {
     if (n == 0) continue;
-    const int splits = tsp::gemm_nn_acc_splits((int)d.M, d.h, n * k_step);
-    const size_t b = splits > 1 ? (size_t)splits * d.M * d.h * 4 : 0;
+    const size_t b = nn_part_bytes(d, n * k_step);
     if (b > most) most = b;
   }
   return align_up(most);
@@ -196,28 +199,30 @@ AttnLaunchPlan attn_launch_plan(const Dims& d, int n) {
   const AttnLaunchPlan paired = {width_for((tiles + 1) / 2 * d.hs * d.B), true};
   return group_seconds(paired.width, true) < group_seconds(plain.width, false) ? paired : plain;
 }
+// (range, token, head) rows of the key-range partials of the launches of a group of n shards
+// (launches of attn_launch_plan's width, and a remainder); 0 without key ranges.
+size_t attn_part_rows(const Dims& d, int n) {
+  const AttnLaunchPlan lp = attn_launch_plan(d, n);
+  if (lp.pair) return 0;
+  size_t part = 0;
+  for (const int w : {lp.width, n % lp.width}) {
+    if (w == 0) continue;
+    const int ns = attn_group_split(d, w, nullptr);
+    const size_t p = ns > 1 ? (size_t)ns * d.M * w * d.hs : 0;
+    if (p > part) part = p;
+  }
+  return part;
+}
 struct AttnWs {
   size_t q, a, po, pml, proj, total;  // byte offsets and total size
 };
 AttnWs attn_ws(const Dims& d) {
   AttnWs w;
-  // Partials for the widest need among the attention launches that occur: groups of G
-  // (and D mod G for a last, smaller group), each in launches of attn_shards_per_launch
-  // shards (and a remainder).
+  // Partials for the widest need among the groups that occur: G shards, and D mod G for a
+  // last, smaller group.
   size_t part = 0;
-  for (const int n : {d.G, d.D % d.G}) {
-    if (n == 0) continue;
-    const AttnLaunchPlan lp = attn_launch_plan(d, n);
-    if (lp.pair) continue;  // no key ranges
-    const int sub = lp.width;
-    for (const int w : {sub, n % sub}) {
-      if (w == 0) continue;
-      int len = 0;
-      const int ns = attn_group_split(d, w, &len);
-      const size_t p = ns > 1 ? (size_t)ns * d.M * w * d.hs : 0;
-      if (p > part) part = p;
-    }
-  }
+  for (const int n : {d.G, d.D % d.G})
+    if (n != 0) part = std::max(part, attn_part_rows(d, n));
   const size_t qa = align_up((size_t)d.M * d.G * d.hs * d.d * 2);
   w.q = 0;
   w.a = qa;
@@ -232,78 +237,122 @@ AttnWs attn_ws(const Dims& d) {
   return w;
 }
 size_t ws_attn(const Dims& d) { return attn_ws(d).total; }
-// MLP backward workspace: dG, dU [M, F/D rounded up to 64] bf16 (the A operands of the
-// dX products), then dG^T, dU^T, Hs^T [F/D, M rounded up to 64] bf16 (the A operands of
-// the weight-gradient products, zero-padded past M) of two ring steps (one when D = 1):
-// the weight gradients of steps 2i and 2i + 1 run as one grouped launch.
+// MLP backward workspace, for groups of n ring steps (mlp_bwd_group): dG, dU of the group's
+// steps side by side, [M, n x (F/D rounded up to 64)] bf16 (the A operands of the dX
+// products), then dG^T, dU^T, Hs^T [n F/D, M rounded up to 64] bf16 (the A operands of the
+// weight-gradient products, zero-padded past M), then the dX product's partial sums.
 struct MlpBwdWs {
-  size_t dg, du, dgt, dut, hst, tr_set, total;
+  size_t dg, du, dgt, dut, hst, part, total;
   int m_pad;
 };
+// Most ring steps of one dX product (two operand pairs each).
+constexpr int kMlpBwdDxSteps = tsp::kGemmPartsMax / 2;
+// Ring steps per group of the MLP backward: a step alone leaves most of the GPU idle at
+// short sequences (7B, S_loc = 1024: 88 tiles in the gate product), so up to 8 are taken
+// together; long sequences fill it with the steps of one dX product, which keeps the
+// workspace of their wider operands down (7B, S_loc = 8192: 11 rounds of gate tiles).
+int mlp_bwd_group(const Dims& d) {
+  int n = d.M <= 4096 ? kGroupMax : kMlpBwdDxSteps;
+  if (n > d.D) n = d.D;
+  while (n > 1 && d.M * n * d.fs_pad * 2 >= (1LL << 32)) --n;  // 32-bit operand offsets
+  return n;
+}
 MlpBwdWs mlp_bwd_ws(const Dims& d) {
   MlpBwdWs w;
+  const int g = mlp_bwd_group(d);
   w.m_pad = (int)((d.M + 63) / 64 * 64);
-  const size_t rm = align_up((size_t)d.M * d.fs_pad * 2), tr = align_up((size_t)d.fs * w.m_pad * 2);
+  const size_t rm = align_up((size_t)d.M * g * d.fs_pad * 2);
+  const size_t tr = align_up((size_t)g * d.fs * w.m_pad * 2);
+  size_t part = 0;
+  for (int n = 1; n <= g && n <= kMlpBwdDxSteps; ++n)
+    part = std::max(part, nn_part_bytes(d, 2 * n * d.fs_pad));
   w.dg = 0;
   w.du = rm;
   w.dgt = 2 * rm;
   w.dut = 2 * rm + tr;
   w.hst = 2 * rm + 2 * tr;
-  w.tr_set = 3 * tr;  // one step's three transposes; the second step's follow
-  w.total = 2 * rm + (d.D > 1 ? 2 : 1) * 3 * tr;
+  w.part = 2 * rm + 3 * tr;
+  w.total = w.part + align_up(part);
   return w;
 }
-// Attention backward, first stage: Q (recomputed, then scaled in place), A, dA, and dQ of
-// two shard steps [M, H_s d] bf16 (the dX products of shards 2i and 2i + 1 run as one); lse, delta [B, H_s, S_loc] fp32; A^T and dQ^T [H_s d, M rounded up
-// to 64] bf16 (the A operands of the weight-gradient products, zero past M); then the
-// forward recomputation's key-range partials, as for the forward, and the dQ kernel's
-// key-range partials.
+// Attention backward, first stage, in groups of n shards (attn_bwd_group): Q (recomputed),
+// A, dA and dQ of a group's shards side by side, [M, n H_s d] bf16 each; lse, delta [B, n H_s,
+// S_loc] fp32; A^T and dQ^T [n H_s d, M rounded up to 64] bf16 (the A operands of the
+// weight-gradient products, zero past M); then the space that the forward recomputation's
+// key-range partials, the dQ kernel's key-range partials and the dX product's partial sums
+// take one after the other.
 struct AttnBwdWs {
-  size_t q, a, da, dq, dq2, lse, delta, at, dqt, po, pml, dqp, total;
-  int m_pad, n_split, split_len, dq_split, dq_split_len;
+  size_t q, a, da, dq, lse, delta, at, dqt, part, pml, total;
+  int m_pad;
 };
-AttnBwdWs attn_bwd_ws(const Dims& d) {
-  AttnBwdWs w;
+// Shards per group of the attention backward.  A shard alone leaves most of the GPU idle at
+// short sequences (7B, S_loc = 1024: 32 tiles in its Q product, 128 key tiles), so a group
+// holds as many as one grouped launch takes.
+int attn_bwd_group(const Dims& d) { return d.D < kGroupMax ? d.D : kGroupMax; }
+void attn_bwd_segments(const Dims& d, int n, AttnBwdParams* bp) {
   AttnParams ap = {};
   attn_segments(d, &ap);
-  w.n_split = tsp::attn_split_count(ap, &w.split_len);
-  {
-    AttnBwdParams bp = {};
-    bp.batch = d.B;
-    bp.heads = d.hs;
-    bp.n_seg = ap.n_seg;
-    for (int k = 0; k < 2; ++k) {
-      bp.seg_rows[k] = ap.seg_rows[k];
-      bp.seg_pos0[k] = ap.seg_pos0[k];
-    }
-    w.dq_split = tsp::attn_bwd_dq_split(bp, &w.dq_split_len);
+  bp->batch = d.B;
+  bp->s_loc = d.s_loc;
+  bp->heads = n * d.hs;
+  bp->n_seg = ap.n_seg;
+  for (int k = 0; k < 2; ++k) {
+    bp->seg_row0[k] = ap.seg_row0[k];
+    bp->seg_rows[k] = ap.seg_rows[k];
+    bp->seg_pos0[k] = ap.seg_pos0[k];
   }
+}
+AttnBwdWs attn_bwd_ws(const Dims& d) {
+  AttnBwdWs w;
+  const int g = attn_bwd_group(d);
   w.m_pad = (int)((d.M + 63) / 64 * 64);
-  const size_t rows = (size_t)d.M * d.hs;
+  size_t fwd_part = 0, shared = 0;
+  for (const int n : {g, d.D % g}) {  // a full group, and a last one of the remainder
+    if (n == 0) continue;
+    const size_t f = attn_part_rows(d, n);
+    if (f > fwd_part) fwd_part = f;
+    AttnBwdParams bp = {};
+    attn_bwd_segments(d, n, &bp);
+    const int ns = tsp::attn_bwd_dq_split(bp, nullptr);
+    const size_t dq = ns > 1 ? (size_t)ns * d.M * n * d.hs * d.d * 4 : 0;
+    const size_t dx = nn_part_bytes(d, n * d.hs * d.d);
+    shared = std::max({shared, dq, dx});
+  }
+  const size_t rows = (size_t)d.M * g * d.hs;
   const size_t qa = align_up(rows * d.d * 2), f = align_up(rows * 4);
-  const size_t tr = align_up((size_t)d.hs * d.d * w.m_pad * 2);
-  const size_t part = w.n_split > 1 ? (size_t)w.n_split * rows : 0;
+  const size_t tr = align_up((size_t)g * d.hs * d.d * w.m_pad * 2);
   w.q = 0;
   w.a = qa;
   w.da = 2 * qa;
   w.dq = 3 * qa;
-  w.dq2 = 4 * qa;  // dQ of the odd shard of a pair (unused when D = 1)
-  w.lse = (d.D > 1 ? 5 : 4) * qa;
+  w.lse = 4 * qa;
   w.delta = w.lse + f;
   w.at = w.delta + f;
   w.dqt = w.at + tr;
-  w.po = w.dqt + tr;
-  w.pml = w.po + align_up(part * d.d * 4);
-  w.dqp = w.pml + align_up(part * 2 * 4);
-  const size_t dq_part = w.dq_split > 1 ? (size_t)w.dq_split * rows * d.d * 4 : 0;
-  w.total = w.dqp + align_up(dq_part);
+  w.part = w.dqt + tr;
+  w.pml = w.part + align_up(fwd_part * d.d * 4);
+  w.total = std::max(w.pml + align_up(fwd_part * 2 * 4), w.part + align_up(shared));
   return w;
 }
-// Attention backward, second stage: the transposed gradients of one shard's K and V
-// rows, [K_s d, M rounded up to 64] bf16 each.
-size_t ws_attn_kv_bwd(const Dims& d) {
-  const size_t m_pad = (size_t)((d.M + 63) / 64 * 64);
-  return 2 * align_up((size_t)d.ks * d.d * m_pad * 2);
+// Attention backward, second stage: the transposed gradients of every shard's K and V rows,
+// [n_kv d, M rounded up to 64] bf16 each, then the dX product's partial sums.
+constexpr int kKvBwdDxShards = tsp::kGemmPartsMax / 2;  // shards of one dX product
+struct AttnKvBwdWs {
+  size_t kt, vt, part, total;
+  int m_pad;
+};
+AttnKvBwdWs attn_kv_bwd_ws(const Dims& d) {
+  AttnKvBwdWs w;
+  w.m_pad = (int)((d.M + 63) / 64 * 64);
+  const size_t tr = align_up((size_t)d.nkv * d.d * w.m_pad * 2);
+  size_t part = 0;
+  for (int n = 1; n <= d.D && n <= kKvBwdDxShards; ++n)
+    part = std::max(part, nn_part_bytes(d, 2 * n * d.ks * d.d));
+  w.kt = 0;
+  w.vt = tr;
+  w.part = 2 * tr;
+  w.total = w.part + align_up(part);
+  return w;
 }
 size_t ws_layer(const Dims& d) {
   const size_t a = ws_mlp(d), b = ws_attn(d);
@@ -441,95 +490,104 @@ tsp_status run_mlp(const Dims& d, const uint16_t* x, const uint16_t* const* wg,
   return TSP_OK;
 }
 
-// Two-part contraction [A0 A1] [B0; B1] (row strides lda, ldb; B rows >= kb_rows of each
-// part clamped), each part k_part wide.
-void set_two_parts(GemmParams* p, const uint16_t* a0, const uint16_t* b0, const uint16_t* a1,
-                   const uint16_t* b1, int k_part) {
-  p->A = a0;
-  p->B = b0;
-  p->A_part[0] = a0;
-  p->B_part[0] = b0;
-  p->A_part[1] = a1;
-  p->B_part[1] = b1;
-  p->n_parts = 2;
-  p->k_part = k_part;
-  p->K = 2 * k_part;
+// dW[n, h] (+)= T[n, M] X[M, h], T the transpose (rows m_pad apart, zero past M) of the
+// gradient columns that belong to dW's rows.
+GemmParams dw_params(const Dims& d, const uint16_t* t, int m_pad, const uint16_t* x, int n,
+                     float* dw, int accumulate) {
+  GemmParams q = {};
+  q.A = t;
+  q.lda = m_pad;
+  q.B = x;
+  q.ldb = d.h;
+  q.M = n;
+  q.N = d.h;
+  q.K = m_pad;
+  q.Kb_rows = (int)d.M;
+  q.Y = dw;
+  q.ldy = d.h;
+  q.accumulate = accumulate ? 1 : 0;
+  return q;
 }
 
-// Backward of run_mlp (same ring order).  Per shard: one fused GEMM for G, U, dHs and
-// the SwiGLU backward, two accumulating products for dX, three for the weight
-// gradients (each [F/D, h], contracting over the M tokens).
+// Backward of run_mlp (same ring order), in groups of mlp_bwd_group steps.  Per group: one
+// grouped launch for G, U, dHs and the SwiGLU backward of its shards, the accumulating
+// products for dX (over up to kMlpBwdDxSteps steps each), and three grouped launches for the
+// weight gradients (each [F/D, h] per shard, contracting over the M tokens).
 tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
                        const uint16_t* const* wg, const uint16_t* const* wu,
                        const uint16_t* const* wd, float* dx, int accumulate,
                        float* const* dwg, float* const* dwu, float* const* dwd, char* ws,
                        hipStream_t st) {
   const MlpBwdWs w = mlp_bwd_ws(d);
+  const int group = mlp_bwd_group(d);
   uint16_t* dg = reinterpret_cast<uint16_t*>(ws + w.dg);
   uint16_t* du = reinterpret_cast<uint16_t*>(ws + w.du);
-  GemmParams dw[kPair * 3] = {};
-  int n_dw = 0;
-  for (int t = 0; t < d.D; ++t) {
-    const int j = ((d.p - t) % d.D + d.D) % d.D;
-    const size_t set = (size_t)(t % kPair) * w.tr_set;
-    uint16_t* dgt = reinterpret_cast<uint16_t*>(ws + w.dgt + set);
-    uint16_t* dut = reinterpret_cast<uint16_t*>(ws + w.dut + set);
-    uint16_t* hst = reinterpret_cast<uint16_t*>(ws + w.hst + set);
-    GemmParams g = {};
-    g.A = x;
-    g.A2 = dy;
-    g.lda = d.h;
-    g.B = wg[j];
-    g.B2 = wu[j];
-    g.B3 = wd[j];
-    g.ldb = d.h;
-    g.M = (int)d.M;
-    g.N = d.fs;
-    g.K = d.h;
-    g.H = dg;
-    g.H2 = du;
-    g.ldh = d.fs_pad;
-    g.T0 = dgt;
-    g.T1 = dut;
-    g.T2 = hst;
-    g.ldt = w.m_pad;
-    TSP_LAUNCH(TSP_KERNEL_BWD_GATE, st, tsp::launch_gemm_swiglu_bwd(g, st));
+  uint16_t* tr[3] = {reinterpret_cast<uint16_t*>(ws + w.dgt),
+                     reinterpret_cast<uint16_t*>(ws + w.dut),
+                     reinterpret_cast<uint16_t*>(ws + w.hst)};
+  for (int t0 = 0; t0 < d.D; t0 += group) {
+    const int n = d.D - t0 < group ? d.D - t0 : group;
+    const int ld = n * d.fs_pad;
+    int shard[kGroupMax];
+    GemmParams g[tsp::kGemmGroupMax] = {};
+    for (int i = 0; i < n; ++i) {
+      const int j = shard[i] = ((d.p - (t0 + i)) % d.D + d.D) % d.D;
+      g[i].A = x;
+      g[i].A2 = dy;
+      g[i].lda = d.h;
+      g[i].B = wg[j];
+      g[i].B2 = wu[j];
+      g[i].B3 = wd[j];
+      g[i].ldb = d.h;
+      g[i].M = (int)d.M;
+      g[i].N = d.fs;
+      g[i].K = d.h;
+      g[i].H = dg + (size_t)i * d.fs_pad;
+      g[i].H2 = du + (size_t)i * d.fs_pad;
+      g[i].ldh = ld;
+      g[i].h_cols = d.fs_pad;
+      g[i].T0 = tr[0] + (size_t)i * d.fs * w.m_pad;
+      g[i].T1 = tr[1] + (size_t)i * d.fs * w.m_pad;
+      g[i].T2 = tr[2] + (size_t)i * d.fs * w.m_pad;
+      g[i].ldt = w.m_pad;
+    }
+    TSP_LAUNCH(TSP_KERNEL_BWD_GATE, st, tsp::launch_gemm_swiglu_bwd_group(g, n, st));
 
-    // dX (+)= dG W_gate[j] + dU W_up[j] = [dG dU] [W_gate[j]; W_up[j]] in one product
-    // ([M, F/D] x [F/D, h] twice; padded columns of dG, dU are zero).
-    {
+    // dX (+)= sum of dG_j W_gate[j] + dU_j W_up[j]: one product over the operand pairs of
+    // up to kMlpBwdDxSteps steps (padded columns of dG, dU are zero).
+    for (int i0 = 0; i0 < n; i0 += kMlpBwdDxSteps) {
+      const int m = n - i0 < kMlpBwdDxSteps ? n - i0 : kMlpBwdDxSteps;
       GemmParams p = {};
-      set_two_parts(&p, dg, wg[j], du, wu[j], d.fs_pad);
-      p.lda = d.fs_pad;
+      for (int i = 0; i < m; ++i) {
+        const int j = shard[i0 + i];
+        p.A_part[2 * i] = dg + (size_t)(i0 + i) * d.fs_pad;
+        p.B_part[2 * i] = wg[j];
+        p.A_part[2 * i + 1] = du + (size_t)(i0 + i) * d.fs_pad;
+        p.B_part[2 * i + 1] = wu[j];
+      }
+      p.A = p.A_part[0];
+      p.lda = ld;
+      p.B = p.B_part[0];
       p.ldb = d.h;
+      p.n_parts = 2 * m;
+      p.k_part = d.fs_pad;
+      p.K = 2 * m * d.fs_pad;
       p.Kb_rows = d.fs;
       p.M = (int)d.M;
       p.N = d.h;
       p.Y = dx;
       p.ldy = d.h;
-      p.accumulate = (t > 0 || accumulate) ? 1 : 0;
-      TSP_LAUNCH(TSP_KERNEL_BWD_DX, st, tsp::launch_gemm_nn_acc(p, nullptr, st));
+      p.accumulate = (t0 + i0 > 0 || accumulate) ? 1 : 0;
+      TSP_LAUNCH(TSP_KERNEL_BWD_DX, st,
+                 tsp::launch_gemm_nn_acc(p, reinterpret_cast<float*>(ws + w.part), st));
     }
-    // dW (+)= (dG^T | dU^T | Hs^T) (X | X | dY): [F/D, M] x [M, h], padded rows are zero;
-    // the three products of steps 2i and 2i + 1 in one launch (an odd last step alone).
+    // dW (+)= (dG^T | dU^T | Hs^T) (X | X | dY): [F/D, M] x [M, h], padded rows are zero.
+    float* const* const out[3] = {dwg, dwu, dwd};
     for (int k = 0; k < 3; ++k) {
-      GemmParams& q = dw[n_dw++];
-      q = GemmParams{};
-      q.A = k == 0 ? dgt : (k == 1 ? dut : hst);
-      q.lda = w.m_pad;
-      q.B = k < 2 ? x : dy;
-      q.ldb = d.h;
-      q.M = d.fs;
-      q.N = d.h;
-      q.K = w.m_pad;
-      q.Kb_rows = (int)d.M;
-      q.Y = k == 0 ? dwg[j] : (k == 1 ? dwu[j] : dwd[j]);
-      q.ldy = d.h;
-      q.accumulate = accumulate ? 1 : 0;
-    }
-    if (t % kPair == 1 || t == d.D - 1) {
-      TSP_LAUNCH(TSP_KERNEL_BWD_DW, st, tsp::launch_gemm_nn_acc_small_group(dw, n_dw, st));
-      n_dw = 0;
+      for (int i = 0; i < n; ++i)
+        g[i] = dw_params(d, tr[k] + (size_t)i * d.fs * w.m_pad, w.m_pad, k < 2 ? x : dy, d.fs,
+                         out[k][shard[i]], accumulate);
+      TSP_LAUNCH(TSP_KERNEL_BWD_DW, st, tsp::launch_gemm_nn_acc_group(g, n, st));
     }
   }
   return TSP_OK;
@@ -571,6 +629,38 @@ GemmParams qkv_params(const Dims& d, const uint16_t* x, const uint16_t* shard, i
   return g;
 }
 
+// The attention of a group of n shards from r0 on: attn_launch_plan's launches over the
+// columns of those shards in the group's Q and A.  `base` holds the group's operands, row
+// strides, log-sum-exp placement (of shard r0's heads) and partials.
+tsp_status run_attn_launches(const Dims& d, const AttnParams& base, int r0, int n, int kind,
+                             hipStream_t st) {
+  const int qd = d.hs * d.d;
+  const AttnLaunchPlan lp = attn_launch_plan(d, n);
+  for (int i = 0; i < n; i += lp.width) {
+    const int w = n - i < lp.width ? n - i : lp.width;
+    AttnParams ap = base;
+    ap.Q += (size_t)i * qd;
+    ap.O += (size_t)i * qd;
+    attn_segments(d, &ap);
+    ap.heads = w * d.hs;
+    ap.lse_head0 += i * d.hs;
+    ap.group = d.g;
+    ap.seq = d.S;
+    ap.n_kv = d.nkv;
+    ap.kv_head0 = (r0 + i) * d.ks;
+    ap.pair_tiles = lp.pair ? 1 : 0;
+    if (lp.pair) {
+      ap.n_split = 1;
+      ap.split_len = attn_full_len(ap);
+    } else {
+      ap.n_split = attn_group_split(d, w, &ap.split_len);
+    }
+    ap.part_rows = (long long)d.M * ap.heads;
+    TSP_LAUNCH(kind, st, tsp::launch_flash_attn(ap, st));
+  }
+  return TSP_OK;
+}
+
 // Algorithm 1 on a validated problem.  `residual` (bf16 [M, h]) initialises Y at the
 // first output projection instead of zero / the old Y; `u_out` receives bf16(Y) after
 // the last.  The shards run in groups of G consecutive ones (the last may be smaller):
@@ -602,41 +692,19 @@ tsp_status run_attn(const Dims& d, const uint16_t* x, const uint16_t* const* wa,
     }
     TSP_LAUNCH(TSP_KERNEL_QKV, st, tsp::launch_gemm_qkv_group(g, n, st));
 
-    // Attention over the group's heads, lp.width shards per launch (the columns of those
-    // shards within the group's Q and A).
-    const AttnLaunchPlan lp = attn_launch_plan(d, n);
-    const int sub = lp.width;
-    for (int i = 0; i < n; i += sub) {
-      const int w = n - i < sub ? n - i : sub;
-      AttnParams ap = {};
-      ap.Q = q_ws + (size_t)i * qd;
-      ap.Kb = kb;
-      ap.Vb = vb;
-      ap.O = a_ws + (size_t)i * qd;
-      attn_segments(d, &ap);
-      ap.heads = w * d.hs;
-      ap.ld = n * qd;     // Q: the group's workspace rows
-      ap.ld_o = a_ld;     // A: the workspace's, or the caller's wider rows
-      ap.lse = lse_out;
-      ap.lse_head0 = (r0 + i) * d.hs;
-      ap.lse_heads = d.nh;
-      ap.group = d.g;
-      ap.head_dim = d.d;
-      ap.seq = d.S;
-      ap.n_kv = d.nkv;
-      ap.kv_head0 = (r0 + i) * d.ks;
-      ap.pair_tiles = lp.pair ? 1 : 0;
-      if (lp.pair) {
-        ap.n_split = 1;
-        ap.split_len = attn_full_len(ap);
-      } else {
-        ap.n_split = attn_group_split(d, w, &ap.split_len);
-      }
-      ap.part_rows = (long long)d.M * ap.heads;
-      ap.part_o = reinterpret_cast<float*>(ws + aw.po);
-      ap.part_ml = reinterpret_cast<float*>(ws + aw.pml);
-      TSP_LAUNCH(TSP_KERNEL_ATTN, st, tsp::launch_flash_attn(ap, st));
-    }
+    AttnParams ap = {};
+    ap.Q = q_ws;
+    ap.Kb = kb;
+    ap.Vb = vb;
+    ap.O = a_ws;
+    ap.ld = n * qd;  // Q: the group's workspace rows
+    ap.ld_o = a_ld;  // A: the workspace's, or the caller's wider rows
+    ap.lse = lse_out;
+    ap.lse_head0 = r0 * d.hs;
+    ap.lse_heads = d.nh;
+    ap.part_o = reinterpret_cast<float*>(ws + aw.po);
+    ap.part_ml = reinterpret_cast<float*>(ws + aw.pml);
+    TSP_TRY(run_attn_launches(d, ap, r0, n, TSP_KERNEL_ATTN, st));
 
     o.A = a_ws;
     o.lda = a_ld;
@@ -666,10 +734,10 @@ tsp_status run_attn(const Dims& d, const uint16_t* x, const uint16_t* const* wa,
   return TSP_OK;
 }
 
-// C[M, n] = f A[M, h] B[n, h]^T, bf16 out (the Q epilogue of the projection kernel with
-// every column in the Q block).
+// C[M, n] = f A[M, h] B[n, h]^T, bf16 out with rows ld_out apart (the Q epilogue of the
+// projection kernel with every column in the Q block).
 GemmParams nt_params(const Dims& d, const uint16_t* a, const uint16_t* b, int n, uint16_t* out,
-                     float f) {
+                     int ld_out, float f) {
   GemmParams g = {};
   g.q_scale = f;
   g.A = a;
@@ -680,66 +748,64 @@ GemmParams nt_params(const Dims& d, const uint16_t* a, const uint16_t* b, int n,
   g.N = n;
   g.K = d.h;
   g.Q = out;
-  g.ldq = n;
+  g.ldq = ld_out;
   g.nq = n;
   g.rows_per_batch = d.s_loc;
   return g;
 }
 
-// Backward of run_attn, first stage (see tsp_attn_rank_bwd).
+// Backward of run_attn, first stage (see tsp_attn_rank_bwd), in groups of attn_bwd_group
+// shards: every kernel takes a group's n H_s heads (or its n products) in one launch.
 tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
                         const uint16_t* const* wa, const uint16_t* kb, const uint16_t* vb,
                         float* dx, int accumulate, float* const* dw, float* dk, float* dv,
                         char* ws, hipStream_t st, const uint16_t* a_saved = nullptr,
                         const float* lse_saved = nullptr) {
   const int qd = d.hs * d.d, kd = d.ks * d.d;
+  const size_t wo = (size_t)(qd + 2 * kd) * d.h;  // W_O^(r)^T block [H_s d, h] of a shard
   const AttnBwdWs w = attn_bwd_ws(d);
+  const int group = attn_bwd_group(d);
   uint16_t* q_ws = reinterpret_cast<uint16_t*>(ws + w.q);
   uint16_t* a_ws = reinterpret_cast<uint16_t*>(ws + w.a);
   uint16_t* da_ws = reinterpret_cast<uint16_t*>(ws + w.da);
-  uint16_t* dq_buf[kPair] = {reinterpret_cast<uint16_t*>(ws + w.dq),
-                             reinterpret_cast<uint16_t*>(ws + w.dq2)};
+  uint16_t* dq_ws = reinterpret_cast<uint16_t*>(ws + w.dq);
   uint16_t* at_ws = reinterpret_cast<uint16_t*>(ws + w.at);
   uint16_t* dqt_ws = reinterpret_cast<uint16_t*>(ws + w.dqt);
   float* lse = reinterpret_cast<float*>(ws + w.lse);
   float* delta = reinterpret_cast<float*>(ws + w.delta);
-  for (int r = 0; r < d.D; ++r) {
-    const uint16_t* wq = wa[r];
-    const uint16_t* wo_t = wa[r] + (size_t)(qd + 2 * kd) * d.h;  // W_O^(r)^T [H_s d, h]
-    uint16_t* dq_ws = dq_buf[r % kPair];
+  float* part = reinterpret_cast<float*>(ws + w.part);
+  for (int r0 = 0; r0 < d.D; r0 += group) {
+    const int n = d.D - r0 < group ? d.D - r0 : group;
+    const int ld = n * qd;  // token row of the group's Q, A, dA and dQ
+    GemmParams g[tsp::kGemmGroupMax] = {};
     // Q times scale * log2(e), as the attention kernels take it
-    GemmParams g = nt_params(d, x, wq, qd, q_ws, d.scale * kLog2e);
-    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv(g, st));
+    for (int i = 0; i < n; ++i)
+      g[i] = nt_params(d, x, wa[r0 + i], qd, q_ws + (size_t)i * qd, ld, d.scale * kLog2e);
+    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv_group(g, n, st));
+    for (int i = 0; i < n; ++i)  // dA = dY W_O^(r)
+      g[i] = nt_params(d, dy, wa[r0 + i] + wo, qd, da_ws + (size_t)i * qd, ld, 1.f);
+    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv_group(g, n, st));
 
-    AttnParams ap = {};
-    attn_segments(d, &ap);
-    // A and the log-sum-exp: the forward's, kept by tsp_attn_rank_fwd_train (shard r's
+    // A and the log-sum-exp: the forward's, kept by tsp_attn_rank_fwd_train (the group's
     // columns of [M, n_h d] and rows of [B, n_h, S_loc]), or recomputed into the workspace
-    const uint16_t* a_src = a_saved ? a_saved + (size_t)r * qd : a_ws;
-    const int a_ld = a_saved ? d.nh * d.d : qd;
+    const uint16_t* a_src = a_saved ? a_saved + (size_t)r0 * qd : a_ws;
+    const int a_ld = a_saved ? d.nh * d.d : ld;
     if (!a_saved) {
+      AttnParams ap = {};
       ap.Q = q_ws;
       ap.Kb = kb;
       ap.Vb = vb;
       ap.O = a_ws;
-      ap.group = d.g;
-      ap.head_dim = d.d;
-      ap.seq = d.S;
-      ap.n_kv = d.nkv;
-      ap.kv_head0 = r * d.ks;
-      ap.n_split = w.n_split;
-      ap.split_len = w.split_len;
-      ap.part_rows = (long long)d.M * d.hs;
-      ap.part_o = reinterpret_cast<float*>(ws + w.po);
-      ap.part_ml = reinterpret_cast<float*>(ws + w.pml);
+      ap.ld = ap.ld_o = ld;
       ap.lse = lse;
-      TSP_LAUNCH(TSP_KERNEL_ABWD_FWD, st, tsp::launch_flash_attn(ap, st));
+      ap.lse_heads = n * d.hs;
+      ap.part_o = part;
+      ap.part_ml = reinterpret_cast<float*>(ws + w.pml);
+      TSP_TRY(run_attn_launches(d, ap, r0, n, TSP_KERNEL_ABWD_FWD, st));
     }
 
-    g = nt_params(d, dy, wo_t, qd, da_ws, 1.f);  // dA = dY W_O^(r)
-    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv(g, st));
-
     AttnBwdParams bp = {};
+    attn_bwd_segments(d, n, &bp);
     bp.Qs = q_ws;
     bp.O = a_src;
     bp.o_ld = a_ld;
@@ -748,7 +814,7 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     bp.Vb = vb;
     bp.lse = lse_saved ? lse_saved : lse;
     if (lse_saved) {
-      bp.lse_head0 = r * d.hs;
+      bp.lse_head0 = r0 * d.hs;
       bp.lse_heads = d.nh;
     }
     bp.delta = delta;
@@ -756,116 +822,103 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     bp.dK = dk;
     bp.dV = dv;
     bp.accumulate = accumulate ? 1 : 0;
-    bp.batch = d.B;
-    bp.s_loc = d.s_loc;
-    bp.heads = d.hs;
     bp.group = d.g;
     bp.head_dim = d.d;
     bp.seq = d.S;
     bp.n_kv = d.nkv;
-    bp.kv_head0 = r * d.ks;
-    bp.n_seg = ap.n_seg;
-    for (int k = 0; k < 2; ++k) {
-      bp.seg_row0[k] = ap.seg_row0[k];
-      bp.seg_rows[k] = ap.seg_rows[k];
-      bp.seg_pos0[k] = ap.seg_pos0[k];
-    }
+    bp.kv_head0 = r0 * d.ks;
     bp.scale = d.scale;
-    bp.dq_split = w.dq_split;
-    bp.dq_split_len = w.dq_split_len;
-    bp.dq_part = reinterpret_cast<float*>(ws + w.dqp);
+    bp.dq_split = tsp::attn_bwd_dq_split(bp, &bp.dq_split_len);
+    bp.dq_part = part;
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st, tsp::launch_attn_bwd_prep(bp, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_KV, st, tsp::launch_attn_bwd_dkdv(bp, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_Q, st, tsp::launch_attn_bwd_dq(bp, st));
 
-    // dX (+)= dQ W_Q^(r): [M, H_s d] x [H_s d, h], shards 2i and 2i + 1 as one product
-    // ([dQ dQ'] [W_Q; W_Q']), an odd last shard alone.
-    const bool second = r % kPair == 1;
-    if (second || r == d.D - 1) {
-      GemmParams p = {};
-      p.A = dq_buf[0];
-      p.lda = qd;
-      p.B = second ? wa[r - 1] : wq;
-      p.ldb = d.h;
-      p.M = (int)d.M;
-      p.N = d.h;
-      p.K = qd;
-      p.Kb_rows = qd;
-      if (second) set_two_parts(&p, dq_buf[0], wa[r - 1], dq_buf[1], wq, qd);
-      p.Y = dx;
-      p.ldy = d.h;
-      p.accumulate = (r >= kPair || accumulate) ? 1 : 0;
-      TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st, tsp::launch_gemm_nn_acc(p, nullptr, st));
+    // dX (+)= sum of dQ_r W_Q^(r) over the group: one product over its shards.
+    GemmParams p = {};
+    p.A = dq_ws;
+    p.lda = ld;
+    p.B = wa[r0];
+    p.ldb = d.h;
+    p.M = (int)d.M;
+    p.N = d.h;
+    p.K = ld;
+    p.Kb_rows = qd;
+    p.n_parts = n;
+    p.k_part = qd;
+    for (int i = 0; i < n; ++i) {
+      p.A_part[i] = dq_ws + (size_t)i * qd;
+      p.B_part[i] = wa[r0 + i];
     }
+    p.Y = dx;
+    p.ldy = d.h;
+    p.accumulate = (r0 > 0 || accumulate) ? 1 : 0;
+    TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st, tsp::launch_gemm_nn_acc(p, part, st));
 
+    // W_Q blocks (+)= dQ^T X;  W_O^T blocks (+)= A^T dY: [H_s d, M] x [M, h] per shard.
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-               tsp::launch_transpose_bf16(dq_ws, qd, (int)d.M, qd, dqt_ws, w.m_pad, st));
+               tsp::launch_transpose_bf16(dq_ws, ld, (int)d.M, ld, dqt_ws, w.m_pad, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-               tsp::launch_transpose_bf16(a_src, a_ld, (int)d.M, qd, at_ws, w.m_pad, st));
-    // W_Q block (+)= dQ^T X;  W_O^T block (+)= A^T dY: [H_s d, M] x [M, h], one launch.
-    GemmParams q[2] = {};
+               tsp::launch_transpose_bf16(a_src, a_ld, (int)d.M, ld, at_ws, w.m_pad, st));
     for (int k = 0; k < 2; ++k) {
-      q[k].A = k == 0 ? dqt_ws : at_ws;
-      q[k].lda = w.m_pad;
-      q[k].B = k == 0 ? x : dy;
-      q[k].ldb = d.h;
-      q[k].M = qd;
-      q[k].N = d.h;
-      q[k].K = w.m_pad;
-      q[k].Kb_rows = (int)d.M;
-      q[k].Y = dw[r] + (k == 0 ? (size_t)0 : (size_t)(qd + 2 * kd) * d.h);
-      q[k].ldy = d.h;
-      q[k].accumulate = accumulate ? 1 : 0;
+      for (int i = 0; i < n; ++i)
+        g[i] = dw_params(d, (k == 0 ? dqt_ws : at_ws) + (size_t)i * qd * w.m_pad, w.m_pad,
+                         k == 0 ? x : dy, qd, dw[r0 + i] + (k == 0 ? (size_t)0 : wo), accumulate);
+      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(g, n, st));
     }
-    TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_small_group(q, 2, st));
   }
   return TSP_OK;
 }
 
-// Second stage (see tsp_attn_kv_rank_bwd).
+// Second stage (see tsp_attn_kv_rank_bwd): the dX products over kKvBwdDxShards shards each,
+// both gradients transposed whole, and grouped launches for the weight gradients.
 tsp_status run_attn_kv_bwd(const Dims& d, const uint16_t* x, const uint16_t* const* wa,
                            const uint16_t* dkl, const uint16_t* dvl, float* dx, int accumulate,
                            float* const* dw, char* ws, hipStream_t st) {
   const int qd = d.hs * d.d, kd = d.ks * d.d, ld = d.nkv * d.d;
-  const int m_pad = (int)((d.M + 63) / 64 * 64);
-  uint16_t* t_ws = reinterpret_cast<uint16_t*>(ws);
-  const size_t t_elems = align_up((size_t)kd * m_pad * 2) / 2;
-  for (int r = 0; r < d.D; ++r) {
-    const uint16_t* gk = dkl + (size_t)r * kd;  // [M, K_s d], row stride ld
-    const uint16_t* gv = dvl + (size_t)r * kd;
-    {
-      GemmParams p = {};  // dX (+)= dK W_K^(r) + dV W_V^(r), one product over both
-      set_two_parts(&p, gk, wa[r] + (size_t)qd * d.h, gv, wa[r] + (size_t)(qd + kd) * d.h, kd);
-      p.lda = ld;
-      p.ldb = d.h;
-      p.Kb_rows = kd;
-      p.M = (int)d.M;
-      p.N = d.h;
-      p.Y = dx;
-      p.ldy = d.h;
-      p.accumulate = (r > 0 || accumulate) ? 1 : 0;
-      TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st, tsp::launch_gemm_nn_acc(p, nullptr, st));
+  const AttnKvBwdWs w = attn_kv_bwd_ws(d);
+  const uint16_t* const grad[2] = {dkl, dvl};  // [M, n_kv d], shard r's columns at r K_s d
+  uint16_t* const tr[2] = {reinterpret_cast<uint16_t*>(ws + w.kt),
+                           reinterpret_cast<uint16_t*>(ws + w.vt)};
+  // dX (+)= sum of dK_r W_K^(r) + dV_r W_V^(r), one product over the shards' operand pairs.
+  for (int r0 = 0; r0 < d.D; r0 += kKvBwdDxShards) {
+    const int n = d.D - r0 < kKvBwdDxShards ? d.D - r0 : kKvBwdDxShards;
+    GemmParams p = {};
+    for (int i = 0; i < 2 * n; ++i) {
+      const int r = r0 + i / 2, k = i % 2;
+      p.A_part[i] = grad[k] + (size_t)r * kd;
+      p.B_part[i] = wa[r] + (size_t)(qd + k * kd) * d.h;
     }
-    // W_K block (+)= dK^T X;  W_V block (+)= dV^T X: [K_s d, M] x [M, h], one launch.
-    GemmParams q[2] = {};
-    for (int k = 0; k < 2; ++k) {
-      const uint16_t* g = k == 0 ? gk : gv;
-      uint16_t* gt = t_ws + (size_t)k * t_elems;
-      TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-                 tsp::launch_transpose_bf16(g, ld, (int)d.M, kd, gt, m_pad, st));
-      q[k].A = gt;
-      q[k].lda = m_pad;
-      q[k].B = x;
-      q[k].ldb = d.h;
-      q[k].M = kd;
-      q[k].N = d.h;
-      q[k].K = m_pad;
-      q[k].Kb_rows = (int)d.M;
-      q[k].Y = dw[r] + (size_t)(qd + k * kd) * d.h;
-      q[k].ldy = d.h;
-      q[k].accumulate = accumulate ? 1 : 0;
+    p.A = p.A_part[0];
+    p.lda = ld;
+    p.B = p.B_part[0];
+    p.ldb = d.h;
+    p.n_parts = 2 * n;
+    p.k_part = kd;
+    p.K = 2 * n * kd;
+    p.Kb_rows = kd;
+    p.M = (int)d.M;
+    p.N = d.h;
+    p.Y = dx;
+    p.ldy = d.h;
+    p.accumulate = (r0 > 0 || accumulate) ? 1 : 0;
+    TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st,
+               tsp::launch_gemm_nn_acc(p, reinterpret_cast<float*>(ws + w.part), st));
+  }
+  // W_K blocks (+)= dK^T X;  W_V blocks (+)= dV^T X: [K_s d, M] x [M, h] per shard.
+  for (int k = 0; k < 2; ++k)
+    TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
+               tsp::launch_transpose_bf16(grad[k], ld, (int)d.M, ld, tr[k], w.m_pad, st));
+  GemmParams q[tsp::kGemmGroupMax] = {};
+  int n = 0;
+  for (int i = 0; i < 2 * d.D; ++i) {
+    const int r = i / 2, k = i % 2;
+    q[n++] = dw_params(d, tr[k] + (size_t)r * kd * w.m_pad, w.m_pad, x, kd,
+                       dw[r] + (size_t)(qd + k * kd) * d.h, accumulate);
+    if (n == tsp::kGemmGroupMax || i + 1 == 2 * d.D) {
+      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(q, n, st));
+      n = 0;
     }
-    TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_small_group(q, 2, st));
   }
   return TSP_OK;
 }
@@ -948,7 +1001,7 @@ tsp_status tsp_workspace_bytes(const tsp_shape* shape, int op, size_t* bytes) {
     case TSP_OP_LAYER: *bytes = ws_layer(d); return TSP_OK;
     case TSP_OP_MLP_BWD: *bytes = mlp_bwd_ws(d).total; return TSP_OK;
     case TSP_OP_ATTN_BWD: *bytes = attn_bwd_ws(d).total; return TSP_OK;
-    case TSP_OP_ATTN_KV_BWD: *bytes = ws_attn_kv_bwd(d); return TSP_OK;
+    case TSP_OP_ATTN_KV_BWD: *bytes = attn_kv_bwd_ws(d).total; return TSP_OK;
     default: return TSP_ERR_SHAPE;
   }
 }
@@ -1005,9 +1058,12 @@ tsp_status tsp_kv_rank_fwd(const tsp_shape* shape, const uint16_t* x_loc,
   TSP_TRY(check_ptr(k_buf));
   TSP_TRY(check_ptr(v_buf));
   if (d.M == 0) return TSP_OK;
-  for (int r = 0; r < d.D; ++r) {
-    GemmParams g = qkv_params(d, x_loc, w_attn[r], r, nullptr, k_buf, v_buf, false);
-    TSP_LAUNCH(TSP_KERNEL_QKV, stream, tsp::launch_gemm_qkv(g, stream));
+  for (int r0 = 0; r0 < d.D; r0 += tsp::kGemmGroupMax) {
+    const int n = d.D - r0 < tsp::kGemmGroupMax ? d.D - r0 : tsp::kGemmGroupMax;
+    GemmParams g[tsp::kGemmGroupMax] = {};
+    for (int i = 0; i < n; ++i)
+      g[i] = qkv_params(d, x_loc, w_attn[r0 + i], r0 + i, nullptr, k_buf, v_buf, false);
+    TSP_LAUNCH(TSP_KERNEL_QKV, stream, tsp::launch_gemm_qkv_group(g, n, stream));
   }
   return TSP_OK;
 }
@@ -1115,7 +1171,7 @@ tsp_status tsp_attn_kv_rank_bwd(const tsp_shape* shape, const uint16_t* x_loc,
   TSP_TRY(check_ptr(dx_loc));
   TSP_TRY(check_shards(dw_attn, d.D));
   TSP_TRY(check_ptr(ws));
-  if (ws_bytes < ws_attn_kv_bwd(d)) return TSP_ERR_WORKSPACE;
+  if (ws_bytes < attn_kv_bwd_ws(d).total) return TSP_ERR_WORKSPACE;
   if (d.M == 0) return TSP_OK;
   return run_attn_kv_bwd(d, x_loc, w_attn, dk_loc, dv_loc, dx_loc, accumulate, dw_attn,
                          static_cast<char*>(ws), stream);

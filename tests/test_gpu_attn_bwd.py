@@ -18,14 +18,14 @@ from oracle import tsp_oracle as O  # noqa: E402
 from paper_2604_26294_amd import inputs as I  # noqa: E402
 from paper_2604_26294_amd.harness import RankProblem, local_rows, to_device_bf16  # noqa: E402
 from paper_2604_26294_amd.workloads import TINY, Workload  # noqa: E402
-from tests.gpu_common import (MID_GQA64, MID_GQA8, MID_MHA128, ODD3, SINGLE,  # noqa: E402
+from tests.gpu_common import (DEG12, MID_GQA64, MID_GQA8, MID_MHA128, ODD3, SINGLE,  # noqa: E402
                               assert_close, f64)
 
 # Ragged tails: S_loc = 128 / 192 / 640 / 256 / 320 against the 64-query stage and
 # 128-query tile; the zigzag shard's two segments of 96 rows; GQA group 2 and 8.
 CASES = [(TINY, 1), (MID_GQA64, 3), (MID_GQA64, 0), (MID_MHA128, 1), (MID_GQA8, 1),
          (SINGLE, 0), (MID_GQA64.with_layout(1), 2), (MID_MHA128.with_layout(1), 0),
-         (ODD3, 2)]  # odd D: the dX product of the last shard runs alone
+         (ODD3, 2), (DEG12, 7)]  # groups of 3 shards; of 8 and 4
 _cache = {}
 
 
@@ -87,8 +87,9 @@ def test_attention_backward_first_stage(wl, p):
         assert not np.any(dk_all[:, last + 1:, cols]) and not np.any(dv_all[:, last + 1:, cols])
 
 
-@pytest.mark.parametrize("wl,p", [(TINY, 0), (MID_GQA64, 2), (MID_MHA128, 1), (SINGLE, 0)],
-                         ids=["tiny-r0", "gqa64-r2", "mha128-r1", "single"])
+@pytest.mark.parametrize("wl,p", [(TINY, 0), (MID_GQA64, 2), (MID_MHA128, 1), (SINGLE, 0),
+                                  (DEG12, 7)],
+                         ids=["tiny-r0", "gqa64-r2", "mha128-r1", "single", "deg12-r7"])
 def test_attention_backward_second_stage(wl, p):
     print(f"[attn bwd 2] {wl.name} rank {p}", flush=True)
     x_bits, w_bits, _ = _inputs(wl)

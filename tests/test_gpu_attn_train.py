@@ -27,13 +27,13 @@ from paper_2604_26294_amd import tsp as T  # noqa: E402
 from paper_2604_26294_amd.harness import (RankProblem, local_positions, local_rows,  # noqa: E402
                                           to_device_bf16)
 from paper_2604_26294_amd.workloads import TINY  # noqa: E402
-from tests.gpu_common import (MID_GQA64, MID_MHA128, ODD3, SUBL, assert_close,  # noqa: E402
+from tests.gpu_common import (DEG12, MID_GQA64, MID_MHA128, ODD3, SUBL, assert_close,  # noqa: E402
                               f64)
 
 # contiguous and zigzag; GQA; odd D; key-range splits (the log-sum-exp written by the
 # combine kernel) and, in the forward, a shape whose launch pairs query tiles (written by
 # the attention kernel itself)
-CASES = [(TINY, 1), (MID_GQA64, 3), (MID_MHA128.with_layout(1), 0), (ODD3, 2)]
+CASES = [(TINY, 1), (MID_GQA64, 3), (MID_MHA128.with_layout(1), 0), (ODD3, 2), (DEG12, 7)]
 FWD_CASES = CASES + [(SUBL.with_layout(1), 1)]
 _IDS = [f"{w.name}-{w.layout_name}-r{p}" for w, p in CASES]
 _FWD_IDS = [f"{w.name}-{w.layout_name}-r{p}" for w, p in FWD_CASES]
