@@ -15,30 +15,31 @@
 // straight into LDS (buffer loads with an LDS destination, no register staging).  Two main
 // loops: PpTile, 256 x 256 accumulators of 16 x 16 x 32 MFMAs with the two wavefronts of a
 // SIMD alternating between MFMAs and memory (products that fill the chip with such tiles),
-// and gemm_tile, 32 x 32 x 16 MFMAs on smaller tiles with a ring of STAGES slots: while the
-// MFMAs consume step k the loads fill the steps up to k + STAGES - 1.
+// and gemm_tile, smaller tiles with a ring of STAGES slots: while the MFMAs consume step k
+// the loads fill the steps up to k + STAGES - 1.  Both use the 16 x 16 x 32 MFMA, whose
+// accumulator traffic per product is half that of 32 x 32 x 16: on real data these kernels
+// run at the chip's power limit (see PpTile).
 //
 // LDS layouts.  LDS has 64 banks of 4 bytes, so a byte address maps to bank window
 // position (address mod 256).  A [M, K] and "NT" B [N, K] panels are rows of 64 bf16
 // (128 bytes, eight 16-byte chunks); an MFMA operand is one 16-byte read, 16 lanes of
 // which read 16 consecutive rows at one logical chunk, so the physical chunk is the
 // logical one XOR ((row / 2) mod 8) and those 16 reads hit 16 distinct windows.
-// "NN" B panels ([K, N] operands: W2 and W_O^(r)^T) keep their natural [64][BN] layout,
-// chunk XOR 4 (row mod 4) so that the 4 rows x 64 bytes of a half-wave transpose read
-// cover all 64 banks, and are read with the gfx950 LDS transpose read
-// ds_read_b64_tr_b16: in each 16-lane group, source lane s points at row kbase + s/4,
-// columns base + 4 (s % 4), and lane t receives column base + t of rows kbase..kbase+3,
-// i.e. four consecutive contraction indices of one output column -- no transpose pass
-// over HBM and no register shuffles.  Every LDS address is a per-lane base XOR a
-// wave-uniform constant plus an immediate offset.  (PpTile's 16-column blocks read 8 rows x
-// 32 bytes per half-wave, rows r .. r + 3 and r + 8 .. r + 11: its chunk XOR takes bit 3 of
-// the row too.)
+// "NN" B panels ([K, N] operands: W2 and W_O^(r)^T) keep their natural [64][columns] layout
+// and are read with the gfx950 LDS transpose read ds_read_b64_tr_b16: in each 16-lane
+// group, source lane s points at row kbase + s/4, columns base + 4 (s % 4), and lane t
+// receives column base + t of rows kbase..kbase+3, i.e. four consecutive contraction indices
+// of one output column -- no transpose pass over HBM and no register shuffles.  A half-wave
+// reads rows r .. r + 3 and r + 8 .. r + 11 of 16 columns, 8 x 32 bytes, which the chunk XOR
+// of those row bits (nn_swz) spreads over all 64 banks.  Every LDS address is a per-lane base
+// XOR a wave-uniform constant plus an immediate offset.
 //
 // Tails.  Rows or columns past M / N are clamped to the last valid one on load (finite
 // values, results never stored).  K must be a multiple of 64: the gated product Hs is
 // stored with its width padded to a multiple of 64 with zero columns (written by the
 // SwiGLU epilogue), and the matching W2 rows past F/D are clamped, so padded terms
 // contribute exact zeros.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -62,14 +63,26 @@ __device__ __forceinline__ void wait_dma() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Wait for the stage that a step is about to read, with up to AHEAD later stages of LOADS
+// loads each (`issued` of them, if fewer) left in flight.
+template <int AHEAD, int LOADS>
+__device__ __forceinline__ void wait_ahead(int issued) {
+  if constexpr (AHEAD == 0) {
+    wait_dma<0>();
+  } else {
+    if (issued >= AHEAD) wait_dma<AHEAD * LOADS>();
+    else wait_ahead<AHEAD - 1, LOADS>(issued);
+  }
+}
+
 template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
 struct Cfg {
   static constexpr int WAVES = WGM * WGN, THREADS = kWave * WAVES;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
-  static constexpr int TM = WM / 32, TN = WN / 32;
+  static constexpr int TM = WM / 32, TN = WN / 16;  // 32-row, 16-column blocks
   // Output columns of a wavefront: 32-column block j starts at wn COL_WN + j COL_BLK.
   static constexpr int COL_WN = WN, COL_BLK = 32;
-  static constexpr bool BWD = EPI == EPI_SWIGLU_BWD, MFMA16 = false;
+  static constexpr bool BWD = EPI == EPI_SWIGLU_BWD;
   static constexpr int NAP = BWD ? 2 : 1;                                  // A panels
   static constexpr int NBP = EPI == EPI_SWIGLU ? 2 : (BWD ? 3 : 1);        // B panels
   static constexpr int TNB = NBP * TN;
@@ -82,7 +95,7 @@ struct Cfg {
   // [N, K]-operand tiles: only the first half of the wavefronts (one per SIMD) load, each
   // its own share of a stage and that of the other wavefront of its SIMD; [K, N] tiles:
   // every wavefront loads its share.
-  static constexpr bool HALF_LOADERS = !NN;
+  static constexpr bool HALF_LOADERS = !NN && WAVES == 8;
   static constexpr int LOADS = (HALF_LOADERS ? 2 : 1) *
       (NAP * BM / 8 / WAVES + (NN ? BK * (BN * 2) / 1024 / WAVES : NB / 8 / WAVES));
   static_assert(STAGES >= 2 && LDS_BYTES <= 160 * 1024, "LDS ring");
@@ -90,6 +103,7 @@ struct Cfg {
   static constexpr int NN_RB = BN * 2;                         // NN panel row bytes
   static_assert(!(NN && (EPI == EPI_SWIGLU || BWD)), "SwiGLU operands are [N, K]");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
+  static_assert(!NN || BN == 64 || BN == 128, "NN panel swizzle");
   static_assert((BM / 8) % WAVES == 0 && (NB / 8) % WAVES == 0, "NT DMA cover");
   static_assert(!NN || (BK * NN_RB / 1024) % WAVES == 0, "NN DMA cover");
 };
@@ -108,8 +122,13 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 
 // Chunk swizzles of the NT and NN panels (physical chunk = logical chunk XOR swz(row)).
 __device__ __forceinline__ int nt_swz(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int nn_swz(int row) { return 4 * (row & 3); }
-__device__ __forceinline__ int nn_swz16(int row) { return 4 * (row & 3) + 2 * ((row >> 3) & 1); }
+// Panels of 128 columns (256-byte rows) and of 64 (128-byte rows, two per bank window).
+template <int COLS>
+__device__ __forceinline__ int nn_swz(int row) {
+  static_assert(COLS == 64 || COLS == 128, "panel width");
+  return COLS == 128 ? 4 * (row & 3) + 2 * ((row >> 3) & 1)
+                     : 4 * ((row >> 3) & 1) + 2 * ((row >> 1) & 1);
+}
 
 // Operand panels go HBM -> LDS through buffer loads with an LDS destination (lds_dma.h):
 // address = resource base (the matrix) + scalar offset (the stage's K position) + a
@@ -156,7 +175,7 @@ struct NnRows {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int r = r0 + i * RPI * WAVES;
-      const uint32_t gn = (uint32_t)min(n0 + 8 * (pc ^ nn_swz(r)), ncols - 8);
+      const uint32_t gn = (uint32_t)min(n0 + 8 * (pc ^ nn_swz<BN>(r)), ncols - 8);
       off[i] = 2u * ((uint32_t)r * (uint32_t)ld + gn);
     }
   }
@@ -195,7 +214,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
                                               const int m0, const int n0, const int wm,
                                               const int wn, const int split = 0) {
   constexpr int TM = C::TM, TN = C::TN;
-  const int l32 = lane & 31, hh = lane >> 5;
   // Each wavefront stages one 32-row block of its C tile in LDS as fp32, then writes it
   // out in 4-column chunks: consecutive lanes cover consecutive columns, every global
   // access is 16 bytes (fp32) or 8 bytes (bf16), and all loads of a block are in flight
@@ -205,6 +223,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
   constexpr int PER_LANE = 32 * CPR / kWave;
   static_assert(C::WAVES * 32 * EST * 4 <= C::LDS_BYTES, "epilogue staging fits");
   float* E = reinterpret_cast<float*>(L) + wave * 32 * EST;
+  // Element e of accumulator block [row block 2 i + q][column block j] of 32-row block i.
+  auto staged = [&](int q, int j, int e) __attribute__((always_inline)) -> float& {
+    return E[(16 * q + 4 * (lane >> 4) + e) * EST + 16 * j + (lane & 15)];
+  };
   const int ncol0 = n0 + wn * C::COL_WN;
   if constexpr (C::BWD) {
     // SwiGLU backward.  Per 32-row block: dG, dU and Hs replace G, U and dHs in the
@@ -214,24 +236,28 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float g = acc[i][j][e], u = acc[i][j + TN][e], dh = acc[i][j + 2 * TN][e];
-          const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-g));
-          const float sl = g * sg;
-          acc[i][j][e] = dh * u * (sg * (1.f + g * (1.f - sg)));  // dG
-          acc[i][j + TN][e] = dh * sl;                           // dU
-          acc[i][j + 2 * TN][e] = sl * u;                        // Hs
-        }
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float g = acc[2 * i + r][j][e], u = acc[2 * i + r][j + TN][e];
+            const float dh = acc[2 * i + r][j + 2 * TN][e];
+            const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-g));
+            const float sl = g * sg;
+            acc[2 * i + r][j][e] = dh * u * (sg * (1.f + g * (1.f - sg)));  // dG
+            acc[2 * i + r][j + TN][e] = dh * sl;                           // dU
+            acc[2 * i + r][j + 2 * TN][e] = sl * u;                        // Hs
+          }
       const int mrow0 = m0 + wm * C::WM + 32 * i;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int r = 0; r < 2; ++r)
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            E[(8 * (e >> 2) + 4 * hh + (e & 3)) * EST + 32 * j + l32] = acc[i][q * TN + j][e];
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) staged(r, j, e) = acc[2 * i + r][q * TN + j][e];
         wave_lds_sync();
         if (q < 2) {
           uint16_t* H = q == 0 ? P.H : P.H2;
@@ -271,23 +297,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
   };
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    if constexpr (C::MFMA16) {  // 16 x 16 blocks [row block][column block], TNB / 2 panels wide
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int j = 0; j < 2 * TN; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            E[(16 * q + 4 * (lane >> 4) + e) * EST + 16 * j + (lane & 15)] =
-                value(acc[2 * i + q][j][e], EPI == EPI_SWIGLU ? acc[2 * i + q][j + 2 * TN][e] : 0.f);
-    } else {
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          E[(8 * (e >> 2) + 4 * hh + (e & 3)) * EST + 32 * j + l32] =
-              value(acc[i][j][e], EPI == EPI_SWIGLU ? acc[i][j + TN][e] : 0.f);
-    }
+        for (int e = 0; e < 4; ++e)
+          staged(q, j, e) =
+              value(acc[2 * i + q][j][e], EPI == EPI_SWIGLU ? acc[2 * i + q][j + TN][e] : 0.f);
     wave_lds_sync();
     const int mrow0 = m0 + wm * C::WM + 32 * i;
     // Q/K/V scatter: batch entry and token of the block's first row, once per block (a row
@@ -391,14 +408,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
 template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
 __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
   using C = Cfg<BM, BN, WGM, WGN, NN, EPI, STAGES>;
-  constexpr int TM = C::TM, TN = C::TN, TNB = C::TNB;
+  constexpr int TM = 2 * C::TM, TN = C::TN, TNB = C::TNB;  // 16 x 16 blocks
   __shared__ __attribute__((aligned(1024))) char L[C::LDS_BYTES];
   lds_char* Ls = (lds_char*)L;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, hh = lane >> 5;
+  const int l16 = lane & 15, lg = lane >> 4;
 
   const int tiles_n = (P.N + BN - 1) / BN;
   // Work index -> (contraction range, output tile): ranges outermost.
@@ -412,13 +429,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
   tile_coords(wt, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
-  f32x16 acc[TM][TNB];
+  f32x4 acc[TM][TNB];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TNB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
   // The operand pairs of a multi-part contraction, read once into scalar registers (the
   // asm keeps them there: the per-stage choice is then a chain of scalar selects, not an
@@ -506,18 +523,17 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     }
   };
 
-  // Operand addressing (see the header): A / NT-B row R, chunk 2 s + hh ->
-  //   R_base * 128 + (opa ^ 32 s),  opa = l32 * 128 + 16 (hh ^ nt_swz(l32)).
-  const int opa = l32 * 128 + 16 * (hh ^ nt_swz(l32));
-  // NN-B transpose reads for output column block j: rows 16 s + 8 hh + t/4 (+4), columns
-  // wn WN + 32 j + 16 (g mod 2) + 4 (t mod 4)  ->  16 s NN_RB + (nb ^ 2 (wn WN + 32 j)).
+  // Operand addressing (see the header), substep s of 32 contraction indices: A / NT-B row R
+  // + l16, chunk 4 s + lg  ->  R * 128 + (opa ^ 64 s),  opa = l16 * 128 + 16 (lg ^ nt_swz(l16)).
+  const int opa = l16 * 128 + 16 * (lg ^ nt_swz(l16));
+  // NN-B transpose reads for output column block j: rows 32 s + 8 lg + l16 / 4 (+4), columns
+  // wn WN + 16 j + 4 (l16 mod 4)  ->  32 s NN_RB + (nb ^ 2 (wn WN + 16 j)).
   int nb_lo = 0, nb_hi = 0;
   if constexpr (NN) {
-    const int t = lane & 15, g = lane >> 4;
-    const int cl = 2 * (g & 1) + ((t & 3) >> 1), half8 = 8 * (t & 1);
-    const int r_lo = 8 * (g >> 1) + (t >> 2), r_hi = r_lo + 4;
-    nb_lo = r_lo * C::NN_RB + 16 * (cl ^ nn_swz(r_lo)) + half8;
-    nb_hi = r_hi * C::NN_RB + 16 * (cl ^ nn_swz(r_hi)) + half8;
+    const int cl = (l16 & 3) >> 1, half8 = 8 * (l16 & 1);
+    const int r_lo = 8 * lg + (l16 >> 2), r_hi = r_lo + 4;
+    nb_lo = r_lo * C::NN_RB + 16 * (cl ^ nn_swz<BN>(r_lo)) + half8;
+    nb_hi = r_hi * C::NN_RB + 16 * (cl ^ nn_swz<BN>(r_hi)) + half8;
   }
 
   // STAGES-deep ring: stage k lives in slot k mod STAGES.  Step kt waits for stage kt
@@ -535,40 +551,30 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
   for (int st = 0; st < STAGES - 1; ++st)
     if (st < nk) dma_stage(st, (kb + st) * BK);
   for (int kt = 0; kt < nk; ++kt) {
-    const int ahead = min(STAGES - 2, nk - 1 - kt);  // later stages already issued
-    if constexpr (STAGES >= 4) {
-      if (ahead >= 2) wait_dma<C::LOADS * 2>();
-      else if (ahead == 1) wait_dma<C::LOADS>();
-      else wait_dma<0>();
-    } else if constexpr (STAGES == 3) {
-      if (ahead >= 1) wait_dma<C::LOADS>();
-      else wait_dma<0>();
-    } else {
-      wait_dma<0>();
-    }
+    wait_ahead<STAGES - 2, C::LOADS>(nk - 1 - kt);  // (later stages stay in flight)
     __syncthreads();  // stage kt resident; every wave is past step kt-1
     const lds_char* SA = Ls + (kt % STAGES) * C::STAGE;
     const lds_char* SB = SA + C::A_BYTES;
     // Operands of substep s into set s % 2.
     u32x4 a[2][TM], a2[2][TM], b[2][TNB];
     auto read_sub = [&](int s) __attribute__((always_inline)) {
-      const int xo = opa ^ (32 * s), q = s & 1;
+      const int xo = opa ^ (64 * s), q = s & 1;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[q][i] = lds_read16(SA + (wm * C::WM + 32 * i) * 128 + xo);
+      for (int i = 0; i < TM; ++i) a[q][i] = lds_read16(SA + (wm * C::WM + 16 * i) * 128 + xo);
       if constexpr (C::BWD) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-          a2[q][i] = lds_read16(SA + BM * BK * 2 + (wm * C::WM + 32 * i) * 128 + xo);
+          a2[q][i] = lds_read16(SA + BM * BK * 2 + (wm * C::WM + 16 * i) * 128 + xo);
       }
 #pragma unroll
       for (int j = 0; j < TNB; ++j) {
         if constexpr (NN) {
-          const int cx = 2 * (wn * C::WN + 32 * j);
-          const u32x2 lo = lds_read_tr(SB + 16 * s * C::NN_RB + (nb_lo ^ cx));
-          const u32x2 hi = lds_read_tr(SB + 16 * s * C::NN_RB + (nb_hi ^ cx));
+          const int cx = 2 * (wn * C::WN + 16 * j);
+          const u32x2 lo = lds_read_tr(SB + 32 * s * C::NN_RB + (nb_lo ^ cx));
+          const u32x2 hi = lds_read_tr(SB + 32 * s * C::NN_RB + (nb_hi ^ cx));
           b[q][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         } else {
-          const int brow = (j / TN) * BN + wn * C::WN + 32 * (j % TN);  // panel j / TN
+          const int brow = (j / TN) * BN + wn * C::WN + 16 * (j % TN);  // panel j / TN
           b[q][j] = lds_read16(SB + brow * 128 + xo);
         }
       }
@@ -579,14 +585,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     if (kt + STAGES - 1 < nk)
       dma_stage((kt + STAGES - 1) % STAGES, (kb + kt + STAGES - 1) * BK);
 #pragma unroll
-    for (int s = 0; s < BK / 16; ++s) {
-      if (s + 1 < BK / 16) read_sub(s + 1);
+    for (int s = 0; s < BK / 32; ++s) {
+      if (s + 1 < BK / 32) read_sub(s + 1);
       const int q = s & 1;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TNB; ++j)
-          acc[i][j] = mfma32(C::BWD && j >= 2 * TN ? a2[q][i] : a[q][i], b[q][j], acc[i][j]);
+          acc[i][j] = mfma16(C::BWD && j >= 2 * TN ? a2[q][i] : a[q][i], b[q][j], acc[i][j]);
     }
     // Issue order: the operand reads of k-substep s+1 are spread between the MFMAs of
     // substep s (R / M per MFMA, one more for the first R mod M), so LDS latency hides
@@ -597,11 +603,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
       constexpr int RM = R / M;
       __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
 #pragma unroll
-      for (int s = 0; s < BK / 16; ++s)
+      for (int s = 0; s < BK / 32; ++s)
 #pragma unroll
         for (int i = 0; i < M; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if (s + 1 < BK / 16) {
+          if (s + 1 < BK / 32) {
             if (i < R % M) __builtin_amdgcn_sched_group_barrier(0x100, RM + 1, 0);
             else if (RM > 0) __builtin_amdgcn_sched_group_barrier(0x100, RM, 0);
           }
@@ -669,10 +675,10 @@ struct PpTile {
   static constexpr bool SW = EPI == EPI_SWIGLU;
   static constexpr int BM = 256, BN = SW ? 128 : 256, WGM = 2, WGN = 4;
   static constexpr int WAVES = 8, THREADS = kWave * WAVES;
-  static constexpr int WM = 128, WN = SW ? 32 : 64, TM = 4, TN = WN / 32, TNB = 2;
+  static constexpr int WM = 128, WN = SW ? 32 : 64, TM = 4, TN = WN / 16;
   // NN units are 128 consecutive columns, so a wavefront's second 32 columns are 128 on.
   static constexpr int COL_WN = NN ? 32 : WN, COL_BLK = NN ? 128 : 32;
-  static constexpr bool BWD = false, MFMA16 = true;
+  static constexpr bool BWD = false;
   static_assert(!MULTI || (NN && EPI == EPI_ACC), "multi-part contractions");
   static constexpr int UNIT = 128 * BK * 2;
   static constexpr int LDS_BYTES = 8 * UNIT;  // A units [stage parity][half], then B units
@@ -715,7 +721,7 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int r = 8 * (8 * i + wave) + (lane >> 3), pc = (lane & 7) ^ nt_swz(r);
-    const int rn = 4 * (8 * i + wave) + (lane >> 4), pn = (lane & 15) ^ nn_swz16(rn);
+    const int rn = 4 * (8 * i + wave) + (lane >> 4), pn = (lane & 15) ^ nn_swz<128>(rn);
     kr[i] = rn;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -819,7 +825,7 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
         const int r = 8 * g + 4 * h + (l16 >> 2), cl = (l16 & 3) >> 1;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          nb[j][h] = 4 * UNIT + r * 256 + 16 * ((4 * wn + 2 * j + cl) ^ nn_swz16(r)) + 8 * (l16 & 1);
+          nb[j][h] = 4 * UNIT + r * 256 + 16 * ((4 * wn + 2 * j + cl) ^ nn_swz<128>(r)) + 8 * (l16 & 1);
       }
     }
   }
@@ -1072,58 +1078,98 @@ long long tiles_of(const GemmParams* ps, int n, int bm, int bn) {
 
 }  // namespace
 
-// Tile shapes are chosen for the grouped shard products of the 7B-class layer on 256
-// CUs (one workgroup per CU).  Gate+up (M = S_loc, N = F/D = 1376 per shard, 8 shards
-// per launch) takes the alternating tiles of 256 x 128 (256 x 256 accumulators: gate and
-// up) when they make at least 4 rounds (S_loc = 8192: 2816 tiles), else 128 x 128 tiles
-// with a 3-slot ring;
-// Q/K/V (N = 3 d H_s = 1536 per shard) 256 x 256 alternating tiles when they make two
-// rounds or more (S_loc = 8192: 1536 tiles), else 256 x 192 (S_loc = 1024: 256 tiles, one per CU) or,
-// below one tile per CU, 128 x 128; down / O-proj (N = h = 4096)
-// 256 x 256 tiles (512 at S_loc = 8192), their contraction split when that makes fewer
-// tiles than CUs.
+// Tile choice.  The alternating 256 x 256 tiles have the best rate once they fill the chip;
+// smaller ones spread a product over more CUs.  A launch's time goes in rounds of one
+// workgroup per CU, so the alternating tiles are taken when their rounds cost no more than
+// those of the 128 x 128 tiles, with the measured ratio of one round to the other:
+//   gate+up (K = 4096): 86-89 and 55-57 us, 1.55 (S_loc = 2048: 268 us against 329; 1024: 173
+//     and 171; M = 1024 rows of one 7B shard leave the last of 1.4 rounds 60 % empty)
+//   Q/K/V and weight gradients, whose 128 x 128 tiles run two to a CU: 90-104 and 33-42 us,
+//     2.7 (Q/K/V at S_loc = 1024, 192 tiles of 256: 97 us against 127; two thirds of it, 128
+//     tiles: 86 against 72)
 constexpr long long kCus = 256;
 
+long long rounds(long long tiles) { return (tiles + kCus - 1) / kCus; }
+
+// Up to 64 tiles of 128 x 128 the 64 x 64 ones still fit the chip in one round and quarter
+// the work of each CU, with a five-stage ring in place of two stages: a small product is
+// bound by the latency of its chain of loads (S_loc = 128, h = 256: down projection, 12
+// steps on one 256 x 256 tile 24 us, on 64 x 64 tiles 9.7).  From 65 to 256 tiles of 128 x 128 a
+// CU holds one, and gives it a four-stage ring (Q of 8 shards, 1024 x 512 x 4096 each: 69 us
+// with two stages, 50 with four); above, two per CU hide each other's waits.
+constexpr long long kSmallTiles = 64;
+
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s) {
-  if (tiles_of(ps, n, 256, 128) >= 4 * kCus) {
-    if (n == 1) return launch<PpTile<false, EPI_SWIGLU>>(ps[0], s);
+  const long long big = tiles_of(ps, n, 256, 128), t128 = tiles_of(ps, n, 128, 128);
+  if (t128 <= kSmallTiles)
+    return launch_group<Tile<64, 64, 2, 2, false, EPI_SWIGLU, 3>>(ps, n, s);
+  if (155 * rounds(big) <= 100 * rounds(t128))
     return launch_group<PpTile<false, EPI_SWIGLU>>(ps, n, s);
-  }
-  if (n == 1) return launch<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps[0], s);
   return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, s);
 }
 
-// Below one 256 x 256 output tile per CU (short sequences: M = S_loc = 1024 and N = h =
-// 4096 make 64) the contraction is split into ranges, enough (tile, range) items for
-// every CU with at least 16 steps of 64 per range; the partial products go through an
-// fp32 workspace and a reduction kernel that applies the epilogue.
-int gemm_nn_acc_splits(int M, int N, int K) {
-  const long long tiles = (long long)((M + 255) / 256) * ((N + 255) / 256);
-  if (tiles <= 0 || tiles >= kCus || N % 4 != 0) return 1;
-  int splits = (int)((kCus + tiles - 1) / tiles);
-  const int max_splits = K / BK / 16;
-  if (splits > max_splits) splits = max_splits;
-  return splits > 1 ? splits : 1;
+namespace {
+
+// Accumulate products with few output tiles: the tile and the number of contraction ranges
+// (through fp32 partial products and a second kernel) that together take the least time,
+// from the measured time of a 64-deep step on each tile and of moving the partials.
+enum NnTile { kNn256, kNn128, kNn64 };
+struct NnPlan {
+  NnTile tile;
+  int splits;
+};
+NnPlan nn_acc_plan(int M, int N, int K) {
+  const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
+  if (t256 <= 0 || t256 >= kCus || N % 4 != 0) return {kNn256, 1};
+  // Most ranges: enough (tile, range) items of 256 x 256 for every CU with at least 16 steps
+  // per range (the partials' workspace is sized by the choice, so it is bounded by that too).
+  const int steps = K / BK, most = std::max(1, (int)std::min((kCus + t256 - 1) / t256,
+                                                             (long long)(steps / 16)));
+  // us of a step with one workgroup on every CU, and with two where they fit (64 x 64).
+  constexpr struct {
+    NnTile tile;
+    int bm;
+    double step_us;
+  } kTiles[] = {{kNn256, 256, 1.5}, {kNn128, 128, 0.75}, {kNn64, 64, 0.42}};
+  NnPlan best = {kNn256, 1};
+  double best_us = -1.0;
+  for (const auto& t : kTiles) {
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bm - 1) / t.bm);
+    for (int n = 1; n <= most; ++n) {
+      const long long items = tiles * n, per_cu = t.tile == kNn64 ? 2 : 1;
+      // full rounds of per_cu workgroups (two take 1.5 times one's time), then what is left
+      const long long full = items / (kCus * per_cu), rest = items - full * kCus * per_cu;
+      const double passes = full * (per_cu == 2 ? 1.5 : 1.0) +
+                            (rest == 0 ? 0.0 : (rest > kCus ? 1.5 : 1.0));
+      const double us = passes * ((steps + n - 1) / n * t.step_us + 2.0) +
+                        (n > 1 ? 5.0 + 2.0 * n * M * N * 4 / 4.5e6 : 0.0);
+      if (best_us < 0 || us < best_us) {
+        best_us = us;
+        best = {t.tile, n};
+      }
+    }
+  }
+  return best;
 }
+
+}  // namespace
+
+int gemm_nn_acc_splits(int M, int N, int K) { return nn_acc_plan(M, N, K).splits; }
 
 hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  const int splits = gemm_nn_acc_splits(p.M, p.N, p.K);
-  if (splits == 1) {
-    GemmParams q = p;
-    q.k_splits = 1;
-    return launch<PpTile<true, EPI_ACC, true>>(q, s);
-  }
-  if (!part) {  // no workspace: the whole contraction per tile, on 128 x 128 tiles
-    GemmParams q = p;
-    q.k_splits = 1;
-    return launch<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(q, s);
-  }
+  const NnPlan plan = nn_acc_plan(p.M, p.N, p.K);
   GemmParams q = p;
-  q.k_splits = splits;
+  q.k_splits = plan.splits;
   q.part = part;
-  hipError_t e = launch<PpTile<true, EPI_ACC, true>>(q, s);
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if (plan.tile == kNn256)
+    e = launch<PpTile<true, EPI_ACC, true>>(q, s);
+  else if (plan.tile == kNn128)
+    e = launch<Tile<128, 128, 2, 4, true, EPI_ACC, 4>>(q, s);
+  else
+    e = launch<Tile<64, 64, 2, 2, true, EPI_ACC, 5>>(q, s);
+  if (e != hipSuccess || plan.splits == 1) return e;
   const long long threads = (long long)p.M * (p.N / 4);
   void* args[] = {&q};
   return hipLaunchKernel(reinterpret_cast<const void*>(&splitk_reduce_kernel),
@@ -1139,31 +1185,20 @@ hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t
 }
 
 // Weight gradients (M = F/D or H_s d, N = h, K = tokens), several products in one launch.
-// The 256 x 256 alternating tiles run at about 1.6 times the rate of the 128 x 128 ones
-// (7B, S_loc = 8192: 1250 and 780 TFLOP/s), so they are taken unless the rounds they
-// make, each of four times the work, leave them slower: products narrower than a tile (70B:
-// K_s d = 128 rows, half of each tile empty) and launches that do not fill the chip.
 hipError_t launch_gemm_nn_acc_group(const GemmParams* ps, int n, hipStream_t s) {
-  const long long big = (tiles_of(ps, n, 256, 256) + kCus - 1) / kCus;
-  const long long small = (tiles_of(ps, n, 128, 128) + kCus - 1) / kCus;
-  if (4 * 10 * big <= 16 * small) return launch_group<PpTile<true, EPI_ACC>>(ps, n, s);
+  const long long big = tiles_of(ps, n, 256, 256), t128 = tiles_of(ps, n, 128, 128);
+  if (t128 <= kSmallTiles) return launch_group<Tile<64, 64, 2, 2, true, EPI_ACC, 5>>(ps, n, s);
+  if (27 * rounds(big) <= 10 * rounds(t128)) return launch_group<PpTile<true, EPI_ACC>>(ps, n, s);
+  if (t128 <= kCus) return launch_group<Tile<128, 128, 2, 4, true, EPI_ACC, 4>>(ps, n, s);
   return launch_group<Tile<128, 128, 2, 4, true, EPI_ACC, 2>>(ps, n, s);
 }
 
-// Projections with few output tiles (the backward's Q and dA products, N = H_s d; GQA
-// shapes; short sequences) would leave CUs idle with 256 x 192 tiles: below one tile per
-// CU they take 128 x 128 tiles.
 hipError_t launch_gemm_qkv_group(const GemmParams* ps, int n, hipStream_t s) {
-  if (tiles_of(ps, n, 256, 256) >= 2 * kCus) {
-    if (n == 1) return launch<PpTile<false, EPI_QKV>>(ps[0], s);
-    return launch_group<PpTile<false, EPI_QKV>>(ps, n, s);
-  }
-  if (tiles_of(ps, n, 256, 192) < kCus) {
-    if (n == 1) return launch<Tile<128, 128, 2, 4, false, EPI_QKV, 2>>(ps[0], s);
-    return launch_group<Tile<128, 128, 2, 4, false, EPI_QKV, 2>>(ps, n, s);
-  }
-  if (n == 1) return launch<Tile<256, 192, 4, 2, false, EPI_QKV, 2>>(ps[0], s);
-  return launch_group<Tile<256, 192, 4, 2, false, EPI_QKV, 2>>(ps, n, s);
+  const long long big = tiles_of(ps, n, 256, 256), t128 = tiles_of(ps, n, 128, 128);
+  if (t128 <= kSmallTiles) return launch_group<Tile<64, 64, 2, 2, false, EPI_QKV, 5>>(ps, n, s);
+  if (27 * rounds(big) <= 10 * rounds(t128)) return launch_group<PpTile<false, EPI_QKV>>(ps, n, s);
+  if (t128 <= kCus) return launch_group<Tile<128, 128, 2, 4, false, EPI_QKV, 4>>(ps, n, s);
+  return launch_group<Tile<128, 128, 2, 4, false, EPI_QKV, 2>>(ps, n, s);
 }
 
 }  // namespace tsp

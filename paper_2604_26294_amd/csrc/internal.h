@@ -95,10 +95,9 @@ struct GemmParams {
 // 0; the tiles of product i follow those of the ones before it).
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s);
 hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t s);
-// The accumulate epilogue over [K, N] operands.  Products with fewer 256 x 256 output
-// tiles than CUs split their contraction (gemm_nn_acc_splits ranges) through an fp32
-// workspace `part` of at least splits * M * N floats (unused when splits == 1); without
-// one (part == nullptr) they run unsplit on 128 x 128 tiles.
+// The accumulate epilogue over [K, N] operands.  Products with few output tiles may split
+// their contraction (gemm_nn_acc_splits ranges) through an fp32 workspace `part` of at least
+// splits * M * N floats (unused when splits == 1).
 hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s);
 int gemm_nn_acc_splits(int M, int N, int K);
 // Up to kGemmGroupMax independent accumulate products (one part, no split contraction) in

@@ -26,12 +26,16 @@ def _rel(got, ref):
     return ((got.double() - ref).norm() / ref.norm()).item()
 
 
-# 16387 rows make 65 row tiles of 256.  Gate+up in alternating tiles (>= 1024 tiles of 256 x
-# 128) with contractions of 1, 2, 3 and 5 stages; down projections in them (>= 256 tiles of
-# 256 x 256) with 1, 2, 3, 4 (200 columns padded to 256) stages.
+# 16387 rows make 65 row tiles of 256.  Gate+up in alternating tiles with contractions of 1,
+# 2, 3 and 5 stages; down projections in them (>= 256 tiles of 256 x 256) with 1, 2, 3, 4 (200
+# columns padded to 256) stages.  Small products: gate+up and down on 64 x 64 tiles with 1, 2
+# and 5 or more stages; down split into ranges on 64 x 64 (96 rows, 65 steps) and 128 x 128
+# tiles (300 rows); down on 128 x 128 tiles with a four-stage ring (1100 rows).
 @pytest.mark.parametrize("m,h,f", [(16387, 64, 2056), (16387, 128, 2056), (16387, 192, 2056),
                                    (16387, 320, 2056), (16387, 1024, 64), (16387, 1024, 128),
-                                   (16387, 1024, 192), (16387, 1024, 200)])
+                                   (16387, 1024, 192), (16387, 1024, 200), (1, 64, 8),
+                                   (130, 64, 72), (63, 320, 648), (65, 128, 136),
+                                   (96, 1024, 4104), (300, 2048, 4096), (1100, 2048, 512)])
 def test_mlp_tiles(m, h, f):
     print(f"[mlp tiles] {m} x {h} x {f}", flush=True)
     sh = T.make_shape(1, m, h, f, h // 64, h // 64, 64, 1, 0)
@@ -45,9 +49,31 @@ def test_mlp_tiles(m, h, f):
     assert _rel(y, ref) < BOUND
 
 
-@pytest.mark.parametrize("m,heads", [(16387, 16), (8200, 16)])
+# Weight gradients on the alternating tiles (2 x 33 x 16 tiles of 128) with a contraction of 3
+# stages, and dX on few rows.
+@pytest.mark.parametrize("m,h,f", [(130, 2048, 4104)])
+def test_mlp_backward_tiles(m, h, f):
+    print(f"[mlp bwd tiles] {m} x {h} x {f}", flush=True)
+    sh = T.make_shape(1, m, h, f, h // 64, h // 64, 64, 1, 0)
+    x, dy = _normal(1, m, h), _normal(5, m, h)
+    g, u, d = (_normal(k, f, h, std=h ** -0.5) for k in (2, 3, 4))
+    dx = torch.full((m, h), float("nan"), device="cuda")
+    dw = [torch.full((f, h), float("nan"), device="cuda") for _ in range(3)]
+    ws = torch.empty(T.workspace_bytes(sh, T.OP_MLP_BWD), dtype=torch.uint8, device="cuda")
+    T.tsp_mlp_rank_bwd(sh, x, dy, [g], [u], [d], dx, False, [dw[0]], [dw[1]], [dw[2]], ws)
+    xd, dyd, gd, ud, dd = (t.double() for t in (x, dy, g, u, d))
+    gg, uu, dh = xd @ gd.T, xd @ ud.T, dyd @ dd.T
+    sg = torch.sigmoid(gg)
+    dg, du = dh * uu * sg * (1 + gg * (1 - sg)), dh * gg * sg
+    assert _rel(dx, dg @ gd + du @ ud) < BOUND
+    for got, ref in zip(dw, (dg.T @ xd, du.T @ xd, (gg * sg * uu).T @ dyd)):
+        assert _rel(got, ref) < BOUND
+
+
+@pytest.mark.parametrize("m,heads", [(16387, 16), (2100, 16), (1000, 16), (130, 2), (1, 1)])
 def test_kv_projection_tiles(m, heads):
-    """K and V rows of one rank (D = 1): 256 x 256 tiles from two rounds, 256 x 192 below."""
+    """K and V rows of one rank (D = 1): the alternating tiles, 128 x 128 with two and four
+    stages, 64 x 64."""
     print(f"[kv tiles] {m} x {heads} heads", flush=True)
     h = 64 * heads
     sh = T.make_shape(1, m, h, 64, heads, heads, 64, 1, 0)
