@@ -19,20 +19,20 @@
 // P = 2^(Qs K^T - lse) reproduces the forward's probabilities.  Since scale Q =
 // Qs / log2(e) up to that rounding, dK = ln(2) dS^T Qs.
 //
-// MFMA layouts (32 x 32 x 16).  Key-stationary: S = Qs K^T and dP = dO V^T with the
-// queries as rows (A operands read from LDS row by row, K and V fragments as B from
-// registers); the accumulator then holds 16 queries of one key per lane, which is
-// the B-operand layout of dV^T = dO^T P and dK^T = Qs^T dS (contraction over queries
-// in the accumulator's row order), whose A operands dO^T and Qs^T come from the same
-// LDS tiles through transpose reads.  Query-stationary: S^T = K Qs^T and
-// dP^T = V dO^T with keys as rows (Qs and dO fragments in registers), so each lane
-// holds 16 keys of one query, the B-operand layout of dQ^T = K^T dS^T, whose A
-// operand K^T comes from the K tile through transpose reads.
+// MFMA layouts (16 x 16 x 32, whose accumulator traffic per product is half that of 32 x 32 x
+// 16: these kernels run at the chip's power limit).  Key-stationary: S = Qs K^T and dP = dO
+// V^T with the queries as rows (A operands read from LDS row by row, K and V fragments as
+// B); lane l then holds queries 4 (l / 16) + 0..3 of each 16-row block for one key of each
+// 16-key block, which is the B-operand layout of dV^T = dO^T P and dK^T = Qs^T dS (contraction
+// over 32 queries, slots 0-3 from one row block and 4-7 from the next), whose A operands dO^T
+// and Qs^T come from the same LDS tiles through transpose reads.  Query-stationary: S^T = K
+// Qs^T and dP^T = V dO^T with keys as rows (Qs and dO fragments in registers), the same with
+// keys for queries: dQ^T = K^T dS^T, K^T from transpose reads of the K tile.
 //
 // LDS tiles are rows of 16-byte chunks; the physical chunk is the logical chunk XOR
 // f(row), with f chosen so that both read forms are bank-conflict free: 16 rows at one
-// logical chunk (row reads) and 4 rows x 4 chunks (transpose reads of a 32-column
-// block).
+// logical chunk (row reads) and 8 rows x 2 chunks (half a wave's transpose reads of a
+// 16-column block).
 #include <math.h>
 
 #include <type_traits>
@@ -62,20 +62,19 @@ struct BwCfg {
   static constexpr int KCH = D / 8;             // 16-byte chunks per row
   static constexpr int RB = D * 2;              // row bytes
   static constexpr int RPW = 256 / RB;          // rows per 256-byte bank window
-  static constexpr int KS = D / 16;             // contraction steps over d
-  static constexpr int EB = D / 32;             // 32-row blocks of d
+  static constexpr int KS = D / 32;             // contraction steps over d
+  static constexpr int DB = D / 16;             // 16-row blocks of d
   static constexpr int T64 = 64 * RB;           // bytes of a 64-row tile
   static constexpr int RPD = kWave / KCH;       // rows one wave-wide LDS load fills
   static constexpr int DMA64 = 64 / (kBwdWaves * RPD);  // such loads per wave per tile
   static_assert(DMA64 * kBwdWaves * RPD == 64, "tile cover");
-  // m = row / RPW indexes the row's bank window.  d = 128 (one row per window):
-  // f = 4 (m mod 4) + (m / 4 mod 4), distinct over 16 consecutive rows, and distinct
-  // in its upper two bits over 4 consecutive rows.  d = 64 (two rows per window, at
-  // chunk offsets 0 and 8): f = 4 (m mod 2) + (m / 2 mod 4), distinct over 8
-  // consecutive windows, and rows r, r + 2 (same half of a window) differ in bit 2.
+  // m = row / RPW indexes the row's bank window.  d = 128 (one row per window): f = 2 (m mod
+  // 8) + (m / 8 mod 2), distinct over 16 consecutive rows, and in its upper three bits over 8
+  // aligned ones.  d = 64 (two rows per window, at chunk offsets 0 and 8): f = 2 (m mod 4) +
+  // (m / 4 mod 2), distinct over 8 consecutive windows, and in its upper two bits over 4.
   __device__ static int f(int row) {
     const int m = row / RPW;
-    return D == 128 ? (((m & 3) << 2) | ((m >> 2) & 3)) : (((m & 1) << 2) | ((m >> 1) & 3));
+    return D == 128 ? (((m & 7) << 1) | ((m >> 3) & 1)) : (((m & 3) << 1) | ((m >> 2) & 1));
   }
   // Byte offset of (row, column) in a tile (column a multiple of 4 for transpose reads).
   __device__ static int off(int row, int col) {
@@ -103,12 +102,12 @@ __device__ __forceinline__ void load_tile64(const uint16_t* base, uint32_t row_b
   }
 }
 
-// Lane layout of the transpose reads: source lane (t, group g) of a 16-lane group
-// points at row 4 (g / 2) + t / 4 and column 16 (g % 2) + 4 (t % 4) of a 32-column
-// block, so lane l receives column l % 32 of rows 4 (l / 32) + 0..3: the contraction
-// slots 0-3 of the accumulator-ordered B operands; rows + 8 give slots 4-7.
-__device__ __forceinline__ int tr_row(int lane) { return (((lane >> 4) >> 1) << 2) + ((lane & 15) >> 2); }
-__device__ __forceinline__ int tr_col(int lane) { return 16 * ((lane >> 4) & 1) + 4 * (lane & 3); }
+// Lane layout of the transpose reads: source lane t of 16-lane group g points at row 4 g +
+// t / 4 and column 4 (t % 4) of a 16-column block, so lane l receives column l % 16 of rows
+// 4 (l / 16) + 0..3: the contraction slots 0-3 of the accumulator-ordered B operands; rows +
+// 16 give slots 4-7.
+__device__ __forceinline__ int tr_row(int lane) { return 4 * (lane >> 4) + ((lane & 15) >> 2); }
+__device__ __forceinline__ int tr_col(int lane) { return 4 * (lane & 3); }
 
 // ---------------------------------------------------------------------------------
 // delta = rowsum(dO * O) per (query, head).  A group of D / 8 lanes handles one
@@ -182,6 +181,12 @@ __device__ __forceinline__ void bwd_wait_ge(lds_int* p, int target, lds_int* fla
 // barrier per tile), unrolled by slot so that LDS addresses are registers plus
 // immediates; each wave takes a tile in two 32-query blocks: S and dP (row reads), the
 // probabilities and dS (vector ops), then dV^T and dK^T (transpose reads).
+//
+// Bound by instruction issue and, on real data, by power (11.6 ms on zeros where random data
+// takes 13.9).  7B, S = 65536, rank 7, 32 heads in one launch: 14.7 ms with 32 x 32 x 16 MFMAs,
+// 15.0 with 16 x 16 x 32 and a scheduling barrier after each operand group (which the other
+// shape needed to fit its registers), 14.2 without the barriers; S = 8192: 414 -> 292 us (its
+// 64-byte instead of 32-byte segments of dK / dV rows per store count there).
 template <int D>
 __global__ __launch_bounds__(kKvThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
@@ -198,7 +203,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hh = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4;
   const int kv_heads = P.heads / P.group;
 
   // Work item -> (batch, kv head, key tile), key tile fastest: an XCD's contiguous share
@@ -214,7 +219,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   const int kvh = P.kv_head0 + kvl;
   const int k0 = kt * kKvTile;
   const int wk0 = k0 + 32 * wave;  // this wave's first key
-  const int key = wk0 + l32;       // this lane's key (the accumulator column)
+  const int key = wk0 + l16;       // this lane's keys (accumulator columns): key, key + 16
 
   // Keys at or past kv_len (the last query position + 1) are never read: their K
   // fragments are zero and their V rows repeat the last readable key; every query masks
@@ -232,17 +237,20 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
       load_tile64<D, kKvWaves>(vvbase + (size_t)(k0 + min(64 * part, v_last)) * kv_stride,
                                2u * (uint32_t)kv_stride, max(v_last - 64 * part, 0),
                                Ls + VO + part * T64, wave, lane);
-  // K fragments of this lane's key (B operand of S): d slots 16 s + 8 hh.
-  const bool kread = key < kv_len;
-  u32x4 kf[C::KS];
+  // K fragments of this lane's keys (B operand of S): d slots 32 s + 8 g ..
+  u32x4 kf[2][C::KS];
 #pragma unroll
-  for (int s = 0; s < C::KS; ++s)
-    kf[s] = kread ? ld16(kvbase + (size_t)key * kv_stride + 16 * s + 8 * hh) : u32x4{0u, 0u, 0u, 0u};
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s)
+      kf[kb][s] = key + 16 * kb < kv_len
+                      ? ld16(kvbase + (size_t)(key + 16 * kb) * kv_stride + 32 * s + 8 * g)
+                      : u32x4{0u, 0u, 0u, 0u};
   // Consume the K fragments here, before the loop: the compiler then waits for their
   // loads once, instead of at a point inside the loop where the same wait would also
   // cover the newest tile loads.
 #pragma unroll
-  for (int s = 0; s < C::KS; ++s) asm volatile("" ::"v"(kf[s]));
+  for (int s = 0; s < C::KS; ++s) asm volatile("" ::"v"(kf[0][s]), "v"(kf[1][s]));
 
   // Query tiles of 64 rows that can see key k0 or later: per segment, tiles from tf (none
   // of a segment that ends before k0, though its last tile, if partial, may reach past it).
@@ -285,10 +293,14 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   // They are written to LDS negated; rows past the segment are clamped on load and get
   // -lse = -inf, -delta = 0 there (P = 0).
   // (loader wavefronts only: 16 rows each, lanes 0-15 lse, 16-31 delta)
-  const int pr = 16 * wave + (lane & 15), pwhich = (lane >> 4) & 1;
-  // (the array base is chosen from two scalar values, not by indexing the parameter
-  // block per lane, which would load the pointer from memory)
-  const float* const pbase = pwhich ? P.delta : P.lse;
+  // The lane number, opaque to the compiler: what the tile loads derive from it is formed
+  // again for each tile, as the registers to keep it across the loop are not there (spilled,
+  // its reloads would wait for the loads in flight).
+  auto lane_again = [&]() __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    return ln;
+  };
   const int lse_rows = P.lse_heads > 0 ? P.lse_heads : P.heads;
   // lse / delta run two tiles ahead of the rows (pend[S] holds those of the next tile
   // to use slot S), with one unconditional load per wave per tile so that the number of
@@ -301,6 +313,10 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     constexpr int S = decltype(slot)::value;
     const Tile T = tile_at(c_lse);
     if (--lse_left > 0) adv(c_lse);  // past the last tile: reload the last one
+    const int ln = lane_again(), pr = 16 * wave + (ln & 15), pwhich = (ln >> 4) & 1;
+    // (the array base is chosen from two scalar values, not by indexing the parameter
+    // block per lane, which would load the pointer from memory)
+    const float* const pbase = pwhich ? P.delta : P.lse;
     const int last = P.seg_rows[T.seg] - 1 - T.r0;
     const size_t t_row = (size_t)P.seg_row0[T.seg] + T.r0 + min(pr, last);
     // delta: [B, H_s, S_loc]; lse: [B, lse_heads, S_loc] from row lse_head0
@@ -314,101 +330,110 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     const Tile T = tile_at(c_next);
     adv(c_next);
     const size_t e0 = (((size_t)b * P.s_loc + P.seg_row0[T.seg] + T.r0) * P.heads + T.head) * D;
-    const int last = P.seg_rows[T.seg] - 1 - T.r0;
+    const int last = P.seg_rows[T.seg] - 1 - T.r0, ln = lane_again();
 #pragma unroll
     for (int v = 0; v < 2; ++v) {  // the loader's two shares
       load_tile64<D, kKvWaves>(P.Qs + e0, q_row_bytes, last, Ls + S * T64, wave + v * kKvLoaders,
-                               lane);
+                               ln);
       load_tile64<D, kKvWaves>(P.dO + e0, q_row_bytes, last, Ls + (2 + S) * T64,
-                               wave + v * kKvLoaders, lane);
+                               wave + v * kKvLoaders, ln);
     }
   };
 
   // Per-lane LDS offsets (the swizzle of a row depends only on its index mod 16, which
-  // the slot, block and k-step offsets preserve): row reads of k-step ks at
-  // kad ^ (32 ks); transpose reads of column block eb at tra[eb] / trb[eb].
-  const int kad = l32 * C::RB + 16 * (hh ^ C::f(l32));
-  const int trr = tr_row(lane), trc = tr_col(lane);
-  int tra[C::EB], trb[C::EB];
-#pragma unroll
-  for (int eb = 0; eb < C::EB; ++eb) {
-    tra[eb] = C::off(trr, 32 * eb + trc);
-    trb[eb] = C::off(trr + 8, 32 * eb + trc);
-  }
+  // the slot, block and k-step offsets preserve): row reads of k-step ks at kad ^ (64 ks);
+  // transpose reads of column block db at tra ^ (32 db).
+  const int kad = l16 * C::RB + 16 * (g ^ C::f(l16));
+  const int tra = C::off(tr_row(lane), tr_col(lane));
   const lds_char* vrows = Ls + VO + 32 * wave * C::RB;  // this wave's 32 V rows
 
-  f32x16 dkT[C::EB], dvT[C::EB];
+  f32x4 dkT[C::DB][2], dvT[C::DB][2];
 #pragma unroll
-  for (int eb = 0; eb < C::EB; ++eb)
+  for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) dkT[eb][e] = dvT[eb][e] = 0.f;
+    for (int kb = 0; kb < 2; ++kb) dkT[db][kb] = dvT[db][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Block HF of the tile in slot S, at position tpos: element 4 g + r of the score /
-  // dP accumulators is query row 32 HF + 8 g + 4 hh + r, key `key`.
-  auto block = [&](auto slot, auto half, int tpos, int rows_left) __attribute__((always_inline)) {
+  // Block HF of the tile in slot S, at position tpos: element e of accumulator block [rb][kb]
+  // is query row 32 HF + 16 rb + 4 g + e, key `key` + 16 kb.
+  auto block = [&](auto slot, auto half, int tpos) __attribute__((always_inline)) {
     constexpr int S = decltype(slot)::value, HF = decltype(half)::value;
     constexpr int QB = S * T64 + HF * 32 * C::RB;  // this block's Qs rows
     constexpr int OB = QB + 2 * T64;                    // and dO rows
     // The accumulators start at -lse and -delta of their query rows (held negated in
     // LDS), so that they end as S - lse and dP - delta.
-    const float* nlse = Lf + S * 2 * kQStage + 32 * HF + 4 * hh;
-    f32x16 s, dp;
+    const float* nlse = Lf + S * 2 * kQStage + 32 * HF + 4 * g;
+    f32x4 s[2][2], dp[2][2];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 l4 = *reinterpret_cast<const f32x4*>(nlse + 8 * g);
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(nlse + kQStage + 8 * g);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        s[4 * g + r] = l4[r];
-        dp[4 * g + r] = d4[r];
-      }
+    for (int rb = 0; rb < 2; ++rb) {
+      s[rb][0] = s[rb][1] = *reinterpret_cast<const f32x4*>(nlse + 16 * rb);
+      dp[rb][0] = dp[rb][1] = *reinterpret_cast<const f32x4*>(nlse + kQStage + 16 * rb);
     }
+    // (Read addresses are formed here each time: kept across the loop, their registers make
+    // the compiler spill.)
+    int ka = kad;
+    asm volatile("" : "+v"(ka));
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) {
-      const int o = kad ^ (32 * ks);
-      const u32x4 vf = lds_read16(vrows + o);
-      s = mfma32(lds_read16(Ls + QB + o), kf[ks], s);
-      dp = mfma32(lds_read16(Ls + OB + o), vf, dp);
-      // (no operand prefetch across steps: registers are the limit here, and the other
-      // wave of the SIMD covers the LDS latency)
-      __builtin_amdgcn_sched_barrier(0);
+      const int o = ka ^ (64 * ks);
+      u32x4 vf[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) vf[kb] = lds_read16(vrows + 16 * kb * C::RB + o);
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const u32x4 qa = lds_read16(Ls + QB + 16 * rb * C::RB + o);
+        const u32x4 oa = lds_read16(Ls + OB + 16 * rb * C::RB + o);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          s[rb][kb] = mfma16(qa, kf[kb][ks], s[rb][kb]);
+          dp[rb][kb] = mfma16(oa, vf[kb], dp[rb][kb]);
+        }
+      }
     }
     // Causal mask, only in blocks that cross this wave's diagonal: scores of keys after
-    // the query (rel > 8 g + r) become -inf, so P and dS are zero there.
+    // the query become -inf, so P and dS are zero there.
     if (wk0 + 31 > tpos + 32 * HF) {
-      const int rel = key - (tpos + 32 * HF + 4 * hh);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = rel > 8 * (e >> 2) + (e & 3) ? -INFINITY : s[e];
+      for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          const int rel = key + 16 * kb - (tpos + 32 * HF + 16 * rb + 4 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[rb][kb][e] = rel > e ? -INFINITY : s[rb][kb][e];
+        }
     }
-    // P = 2^(S - lse), dS = P (dP - delta), packed to bf16 in the accumulator's row order
-    // (the B operands below).
+    // P = 2^(S - lse), dS = P (dP - delta), packed to bf16 in the accumulators' row order
+    // (the B operands below: slots 0-3 from row block 0, 4-7 from row block 1).
     u32x4 pf[2], df[2];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float pv[4], dv[4];
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        pv[r] = __builtin_amdgcn_exp2f(s[4 * g + r]);
-        dv[r] = pv[r] * dp[4 * g + r];
+      for (int rb = 0; rb < 2; ++rb) {
+        float pv[4], dv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          pv[e] = __builtin_amdgcn_exp2f(s[rb][kb][e]);
+          dv[e] = pv[e] * dp[rb][kb][e];
+        }
+        pf[kb][2 * rb] = pack_bf16x2(pv[0], pv[1]);
+        pf[kb][2 * rb + 1] = pack_bf16x2(pv[2], pv[3]);
+        df[kb][2 * rb] = pack_bf16x2(dv[0], dv[1]);
+        df[kb][2 * rb + 1] = pack_bf16x2(dv[2], dv[3]);
       }
-      pf[g >> 1][2 * (g & 1)] = pack_bf16x2(pv[0], pv[1]);
-      pf[g >> 1][2 * (g & 1) + 1] = pack_bf16x2(pv[2], pv[3]);
-      df[g >> 1][2 * (g & 1)] = pack_bf16x2(dv[0], dv[1]);
-      df[g >> 1][2 * (g & 1) + 1] = pack_bf16x2(dv[2], dv[3]);
+    // dV^T += dO^T P and dK^T += Qs^T dS over the block's 32 query rows.
+    int tr = tra;
+    asm volatile("" : "+v"(tr));
+#pragma unroll
+    for (int db = 0; db < C::DB; ++db) {
+      const lds_char* bq = Ls + QB + (tr ^ (32 * db));
+      const u32x2 olo = lds_read_tr(bq + 2 * T64), ohi = lds_read_tr(bq + 2 * T64 + 16 * C::RB);
+      const u32x2 qlo = lds_read_tr(bq), qhi = lds_read_tr(bq + 16 * C::RB);
+      const u32x4 oa{olo[0], olo[1], ohi[0], ohi[1]}, qa{qlo[0], qlo[1], qhi[0], qhi[1]};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        dvT[db][kb] = mfma16(oa, pf[kb], dvT[db][kb]);
+        dkT[db][kb] = mfma16(qa, df[kb], dkT[db][kb]);
+      }
     }
-    // dV^T += dO^T P and dK^T += Qs^T dS; k-step s2 covers query rows 32 HF + 16 s2 + ..
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int eb = 0; eb < C::EB; ++eb) {
-        const lds_char* bq = Ls + QB + 16 * s2 * C::RB;
-        const u32x2 olo = lds_read_tr(bq + 2 * T64 + tra[eb]), ohi = lds_read_tr(bq + 2 * T64 + trb[eb]);
-        dvT[eb] = mfma32(u32x4{olo[0], olo[1], ohi[0], ohi[1]}, pf[s2], dvT[eb]);
-        const u32x2 qlo = lds_read_tr(bq + tra[eb]), qhi = lds_read_tr(bq + trb[eb]);
-        dkT[eb] = mfma32(u32x4{qlo[0], qlo[1], qhi[0], qhi[1]}, df[s2], dkT[eb]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    (void)rows_left;
   };
 
   // One tile in slot S: the loaders put its lse / delta into LDS once their shares of
@@ -427,6 +452,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     constexpr int S = decltype(slot)::value;
     if (loader) {
       asm volatile("s_waitcnt vmcnt(1)" ::: "memory");  // all but tile t + 1's lse / delta
+      const int pr = 16 * wave + (lane & 15), pwhich = (lane >> 4) & 1;
       if (lane < 32)
         Lf[S * 2 * kQStage + pwhich * kQStage + pr] =
             pr <= pend_last[S] ? -pend[S] : (pwhich ? 0.f : -INFINITY);
@@ -436,7 +462,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     const Tile T = tile_at(c_pos);
     adv(c_pos);
     const int tpos = P.seg_pos0[T.seg] + T.r0;
-    block(slot, IC<0>{}, tpos, 0);
+    block(slot, IC<0>{}, tpos);
     if (loader) {
       if (t + 1 < n_tiles) {
         if (t > 0)
@@ -445,7 +471,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
       }
       pend_load(IC<S>{});  // tile t + 2
     }
-    if (T.r0 + 32 < P.seg_rows[T.seg]) block(slot, IC<1>{}, tpos, 0);
+    if (T.r0 + 32 < P.seg_rows[T.seg]) block(slot, IC<1>{}, tpos);
     bwd_signal(ctr_empty + S);
   };
   if (tid < 5) ctr_full[tid] = 0;
@@ -462,31 +488,28 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   }
   __syncthreads();  // every wavefront is past its last wait
   if (bwd_count(ctr_gave_up) != 0) {
+    constexpr float kNan = __builtin_nanf("");
 #pragma unroll
-    for (int eb = 0; eb < C::EB; ++eb)
+    for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dkT[eb][e] = dvT[eb][e] = __builtin_nanf("");
+      for (int kb = 0; kb < 2; ++kb) dkT[db][kb] = dvT[db][kb] = f32x4{kNan, kNan, kNan, kNan};
   }
 
-  // Accumulator element 4 g + r of block eb: d = 32 eb + 8 g + 4 hh + r, key = `key`.
-  if (key < P.seq) {
-    float* dkrow = P.dK + ((size_t)b * P.seq + key) * kv_stride + (size_t)kvh * D;
-    float* dvrow = P.dV + ((size_t)b * P.seq + key) * kv_stride + (size_t)kvh * D;
+  // Element e of accumulator block [db][kb]: d = 16 db + 4 g + e, key `key` + 16 kb.
 #pragma unroll
-    for (int eb = 0; eb < C::EB; ++eb)
+  for (int kb = 0; kb < 2; ++kb) {
+    if (key + 16 * kb >= P.seq) continue;
+    const size_t at = ((size_t)b * P.seq + key + 16 * kb) * kv_stride + (size_t)kvh * D + 4 * g;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int c = 32 * eb + 8 * g + 4 * hh;
-        f32x4 k4{dkT[eb][4 * g] * kLn2, dkT[eb][4 * g + 1] * kLn2, dkT[eb][4 * g + 2] * kLn2,
-                 dkT[eb][4 * g + 3] * kLn2};
-        f32x4 v4{dvT[eb][4 * g], dvT[eb][4 * g + 1], dvT[eb][4 * g + 2], dvT[eb][4 * g + 3]};
-        if (P.accumulate) {
-          k4 += *reinterpret_cast<const f32x4*>(dkrow + c);
-          v4 += *reinterpret_cast<const f32x4*>(dvrow + c);
-        }
-        *reinterpret_cast<f32x4*>(dkrow + c) = k4;
-        *reinterpret_cast<f32x4*>(dvrow + c) = v4;
+    for (int db = 0; db < C::DB; ++db) {
+      f32x4 k4 = dkT[db][kb] * kLn2, v4 = dvT[db][kb];
+      if (P.accumulate) {
+        k4 += *reinterpret_cast<const f32x4*>(P.dK + at + 16 * db);
+        v4 += *reinterpret_cast<const f32x4*>(P.dV + at + 16 * db);
       }
+      *reinterpret_cast<f32x4*>(P.dK + at + 16 * db) = k4;
+      *reinterpret_cast<f32x4*>(P.dV + at + 16 * db) = v4;
+    }
   }
 }
 
@@ -499,7 +522,8 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
 // tile's keys are split into n_split ranges whose partial dQ (fp32) a second kernel
 // sums; with n_split = 1 the workgroup writes bf16 dQ itself.  The K / V tiles go round
 // a two-slot ring, unrolled by slot so that LDS addresses are registers plus
-// immediates.
+// immediates.  Bound by power on real data (7B, S = 65536, rank 7: 7.0 ms on zeros); 16 x 16 x
+// 32 MFMAs took it from 9.85 to 9.4 ms.
 template <int D>
 __global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bwd_dq_kernel(const AttnBwdParams P) {
@@ -511,7 +535,7 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hh = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4;
 
   // Work item -> (batch, head, key range, query tile), query tile fastest; last segment
   // and last tile (most keys) first.
@@ -529,9 +553,14 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
   const int kvh = P.kv_head0 + head / P.group;
   const int q0 = qt * kDqTile;
 
-  const int qloc = q0 + 32 * wave + l32;  // this lane's query (accumulator column)
-  const bool qvalid = qloc < seg_rows;
-  const int qpos = pos0 + qloc;
+  // This lane's two queries (accumulator columns 16 qb + l mod 16), within the segment.
+  int qloc[2];
+  bool qvalid[2];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    qloc[qb] = q0 + 32 * wave + 16 * qb + l16;
+    qvalid[qb] = qloc[qb] < seg_rows;
+  }
   const bool wave_active = q0 + 32 * wave < seg_rows;
   const int wpos_min = pos0 + q0 + 32 * wave;
   const int wpos_max = pos0 + min(q0 + 32 * wave + 31, seg_rows - 1);
@@ -541,25 +570,34 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
   const int j0 = k_begin / kKStage;
   const int n_steps = k_end > k_begin ? (k_end - k_begin + kKStage - 1) / kKStage : 0;
 
-  // Qs and dO fragments of this lane's query (B operands of S^T and dP^T); the score
+  // Qs and dO fragments of this lane's queries (B operands of S^T and dP^T); the score
   // and dP accumulators start from -lse and -delta.
-  const size_t qrow = (((size_t)b * P.s_loc + row0 + (qvalid ? qloc : 0)) * P.heads + head) * D;
-  u32x4 qf[C::KS], of[C::KS];
+  size_t qrow[2];
+  u32x4 qf[2][C::KS], of[2][C::KS];
+  float neg_lse[2], neg_del[2];
 #pragma unroll
-  for (int s = 0; s < C::KS; ++s) {
-    qf[s] = ld16(P.Qs + qrow + 16 * s + 8 * hh);
-    of[s] = ld16(P.dO + qrow + 16 * s + 8 * hh);
+  for (int qb = 0; qb < 2; ++qb) {
+    const int t = row0 + (qvalid[qb] ? qloc[qb] : 0);
+    qrow[qb] = (((size_t)b * P.s_loc + t) * P.heads + head) * D;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+      qf[qb][s] = ld16(P.Qs + qrow[qb] + 32 * s + 8 * g);
+      of[qb][s] = ld16(P.dO + qrow[qb] + 32 * s + 8 * g);
+    }
+    const size_t li = ((size_t)b * P.heads + head) * P.s_loc + t;
+    const size_t li_lse =
+        ((size_t)b * (P.lse_heads > 0 ? P.lse_heads : P.heads) + P.lse_head0 + head) * P.s_loc + t;
+    neg_lse[qb] = qvalid[qb] ? -P.lse[li_lse] : -INFINITY;  // invalid query: P = 0
+    neg_del[qb] = qvalid[qb] ? -P.delta[li] : 0.f;
   }
-  const size_t li = ((size_t)b * P.heads + head) * P.s_loc + row0 + (qvalid ? qloc : 0);
-  const size_t li_lse = ((size_t)b * (P.lse_heads > 0 ? P.lse_heads : P.heads) + P.lse_head0 +
-                         head) * P.s_loc + row0 + (qvalid ? qloc : 0);
-  const float neg_lse = qvalid ? -P.lse[li_lse] : -INFINITY;  // invalid query: P = 0
-  const float neg_del = qvalid ? -P.delta[li] : 0.f;
   // Consume these loads before the loop: the compiler then waits for them once, not at
   // a point inside the loop where the same wait would also cover the newest key tiles.
 #pragma unroll
-  for (int s = 0; s < C::KS; ++s) asm volatile("" ::"v"(qf[s]), "v"(of[s]));
-  asm volatile("" ::"v"(neg_lse), "v"(neg_del));
+  for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) asm volatile("" ::"v"(qf[qb][s]), "v"(of[qb][s]));
+    asm volatile("" ::"v"(neg_lse[qb]), "v"(neg_del[qb]));
+  }
 
   const size_t kv_stride = (size_t)P.n_kv * D;
   const uint32_t kv_row_bytes = 2u * (uint32_t)kv_stride;
@@ -575,22 +613,16 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
                    wave, lane);
   };
 
-  f32x16 dqT[C::EB];
+  f32x4 dqT[C::DB][2];
 #pragma unroll
-  for (int eb = 0; eb < C::EB; ++eb)
+  for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) dqT[eb][e] = 0.f;
+    for (int qb = 0; qb < 2; ++qb) dqT[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Per-lane LDS offsets: row reads of k-step ks at ka ^ (32 ks); transpose reads of
-  // column block eb at tra[eb] (rows trr) and trb[eb] (rows trr + 8).
-  const int ka = l32 * C::RB + 16 * (hh ^ C::f(l32));
-  const int trr = tr_row(lane), trc = tr_col(lane);
-  int tra[C::EB], trb[C::EB];
-#pragma unroll
-  for (int eb = 0; eb < C::EB; ++eb) {
-    tra[eb] = C::off(trr, 32 * eb + trc);
-    trb[eb] = C::off(trr + 8, 32 * eb + trc);
-  }
+  // Per-lane LDS offsets: row reads of k-step ks at ka ^ (64 ks); transpose reads of
+  // column block db at tra ^ (32 db).
+  const int ka = l16 * C::RB + 16 * (g ^ C::f(l16));
+  const int tra = C::off(tr_row(lane), tr_col(lane));
 
   // One step: the 64 keys of stage j (slot SLOT) in two blocks of 32.
   auto step = [&](auto slot, int j) __attribute__((always_inline)) {
@@ -604,44 +636,63 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
       const int kbase0 = j * kKStage + 32 * kb;
       if (kbase0 > wpos_max) break;  // every key after every query
       constexpr int KO = S * T64;    // this slot's K tile; the V tile follows at 2 T64
-      f32x16 s, dp;
+      f32x4 s[2][2], dp[2][2];  // [16-key block][query block]
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[e] = neg_lse;
-        dp[e] = neg_del;
-      }
+      for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int ks = 0; ks < C::KS; ++ks) {
-        const int o = (ka ^ (32 * ks)) + 32 * kb * C::RB;
-        s = mfma32(lds_read16(Ls + KO + o), qf[ks], s);
-        dp = mfma32(lds_read16(Ls + KO + 2 * T64 + o), of[ks], dp);
-      }
-      // Element 4 g + r: key kbase0 + 8 g + 4 hh + r, this lane's query.
-      float pv[16];
+        for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) pv[e] = __builtin_amdgcn_exp2f(s[e]);
+          for (int e = 0; e < 4; ++e) {
+            s[rb][qb][e] = neg_lse[qb];
+            dp[rb][qb][e] = neg_del[qb];
+          }
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const int o = (ka ^ (64 * ks)) + (32 * kb + 16 * rb) * C::RB;
+          const u32x4 kr = lds_read16(Ls + KO + o), vr = lds_read16(Ls + KO + 2 * T64 + o);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            s[rb][qb] = mfma16(kr, qf[qb][ks], s[rb][qb]);
+            dp[rb][qb] = mfma16(vr, of[qb][ks], dp[rb][qb]);
+          }
+        }
+      // Element e of block [rb][qb]: key kbase0 + 16 rb + 4 g + e, this lane's query qb.
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[rb][qb][e] = __builtin_amdgcn_exp2f(s[rb][qb][e]);
       if (kbase0 + 31 > wpos_min) {  // the block crosses this wave's diagonal
-        const int rel = qpos - kbase0 - 4 * hh;  // key offset 8 g + r must be <= rel
 #pragma unroll
-        for (int e = 0; e < 16; ++e) pv[e] = 8 * (e >> 2) + (e & 3) > rel ? 0.f : pv[e];
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            const int rel = pos0 + qloc[qb] - kbase0 - 16 * rb - 4 * g;  // key e must be <= rel
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[rb][qb][e] = e > rel ? 0.f : s[rb][qb][e];
+          }
       }
       u32x4 df[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          df[h][q] = pack_bf16x2(pv[8 * h + 2 * q] * dp[8 * h + 2 * q],
-                                 pv[8 * h + 2 * q + 1] * dp[8 * h + 2 * q + 1]);
-      // dQ^T += K^T dS^T; k-step s2 covers keys 32 kb + 16 s2 + ..
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-        for (int eb = 0; eb < C::EB; ++eb) {
-          const int ro = (32 * kb + 16 * s2) * C::RB;
-          const u32x2 lo = lds_read_tr(Ls + KO + ro + tra[eb]);
-          const u32x2 hi = lds_read_tr(Ls + KO + ro + trb[eb]);
-          dqT[eb] = mfma32(u32x4{lo[0], lo[1], hi[0], hi[1]}, df[s2], dqT[eb]);
+        for (int rb = 0; rb < 2; ++rb) {
+          const f32x4 ds = s[rb][qb] * dp[rb][qb];
+          df[qb][2 * rb] = pack_bf16x2(ds[0], ds[1]);
+          df[qb][2 * rb + 1] = pack_bf16x2(ds[2], ds[3]);
         }
+      // dQ^T += K^T dS^T over the block's 32 keys.
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) {
+        const lds_char* kt = Ls + KO + 32 * kb * C::RB + (tra ^ (32 * db));
+        const u32x2 lo = lds_read_tr(kt), hi = lds_read_tr(kt + 16 * C::RB);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+          dqT[db][qb] = mfma16(u32x4{lo[0], lo[1], hi[0], hi[1]}, df[qb], dqT[db][qb]);
+      }
     }
   };
 
@@ -651,27 +702,23 @@ void attn_bwd_dq_kernel(const AttnBwdParams P) {
     if (j + 1 < j0 + n_steps) step(IC<1>{}, j + 1);
   }
 
-  if (!qvalid) return;
-  // Element 4 g + r of block eb: d = 32 eb + 8 g + 4 hh + r of this lane's query.
-  if (P.dq_split == 1) {
-    uint16_t* dqrow = P.dQ + qrow;
+  // Element e of block [db][qb]: d = 16 db + 4 g + e of this lane's query qb.
 #pragma unroll
-    for (int eb = 0; eb < C::EB; ++eb)
+  for (int qb = 0; qb < 2; ++qb) {
+    if (!qvalid[qb]) continue;
+    if (P.dq_split == 1) {
+      uint16_t* dqrow = P.dQ + qrow[qb] + 4 * g;
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<u32x2*>(dqrow + 32 * eb + 8 * g + 4 * hh) =
-            u32x2{pack_bf16x2(dqT[eb][4 * g] * P.scale, dqT[eb][4 * g + 1] * P.scale),
-                  pack_bf16x2(dqT[eb][4 * g + 2] * P.scale, dqT[eb][4 * g + 3] * P.scale)};
-  } else {
-    const size_t rows = (size_t)P.batch * P.s_loc * P.heads;
-    float* prow = P.dq_part + ((size_t)split * rows +
-                               ((size_t)b * P.s_loc + row0 + qloc) * P.heads + head) * D;
+      for (int db = 0; db < C::DB; ++db)
+        *reinterpret_cast<u32x2*>(dqrow + 16 * db) =
+            u32x2{pack_bf16x2(dqT[db][qb][0] * P.scale, dqT[db][qb][1] * P.scale),
+                  pack_bf16x2(dqT[db][qb][2] * P.scale, dqT[db][qb][3] * P.scale)};
+    } else {
+      const size_t rows = (size_t)P.batch * P.s_loc * P.heads;
+      float* prow = P.dq_part + ((size_t)split * rows + qrow[qb] / D) * D + 4 * g;
 #pragma unroll
-    for (int eb = 0; eb < C::EB; ++eb)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(prow + 32 * eb + 8 * g + 4 * hh) =
-            f32x4{dqT[eb][4 * g], dqT[eb][4 * g + 1], dqT[eb][4 * g + 2], dqT[eb][4 * g + 3]};
+      for (int db = 0; db < C::DB; ++db) *reinterpret_cast<f32x4*>(prow + 16 * db) = dqT[db][qb];
+    }
   }
 }
 
