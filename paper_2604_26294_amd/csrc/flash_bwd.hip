@@ -35,6 +35,7 @@
 // 16-column block).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -206,16 +207,17 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   const int l16 = lane & 15, g = lane >> 4;
   const int kv_heads = P.heads / P.group;
 
-  // Work item -> (batch, kv head, key tile), key tile fastest: an XCD's contiguous share
-  // of work indices streams the same queries through its L2.  Key tiles alternate from
-  // both ends of the sequence (early keys see the most queries), so that every XCD's
-  // share holds as much light work as heavy.
+  // Work item -> (batch, kv head, query range, key tile), key tile fastest: an XCD's
+  // contiguous share of work indices streams the same queries through its L2.  Key tiles
+  // alternate from both ends of the sequence (early keys see the most queries), so that
+  // every XCD's share holds as much light work as heavy.
   const int n_kt = (int)((P.seq + kKvTile - 1) / kKvTile);
-  const int w = xcd_work_index(blockIdx.x, n_kt * kv_heads * P.batch);
+  const int w = xcd_work_index(blockIdx.x, n_kt * P.kv_split * kv_heads * P.batch);
   const int kj = w % n_kt;
   const int kt = (kj & 1) ? n_kt - 1 - (kj >> 1) : (kj >> 1);
-  const int kvl = (w / n_kt) % kv_heads;
-  const int b = w / n_kt / kv_heads;
+  const int split = (w / n_kt) % P.kv_split;
+  const int kvl = (w / n_kt / P.kv_split) % kv_heads;
+  const int b = w / n_kt / P.kv_split / kv_heads;
   const int kvh = P.kv_head0 + kvl;
   const int k0 = kt * kKvTile;
   const int wk0 = k0 + 32 * wave;  // this wave's first key
@@ -263,7 +265,9 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     nv[sg] = max(0, nt - tf[sg]);
   }
   const int per_head = nv[0] + nv[1];
-  const int n_tiles = per_head * P.group;
+  // This item's range of the kv head's query tiles (all of them without a split).
+  const int all_tiles = per_head * P.group, t_first = split * all_tiles / P.kv_split;
+  const int n_tiles = (split + 1) * all_tiles / P.kv_split - t_first;
   struct Tile {
     int head, seg, r0;
   };
@@ -286,7 +290,8 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
     T.r0 = kQStage * (T.seg == 0 ? tf[0] + c.u : tf[1] + c.u - nv[0]);
     return T;
   };
-  Cursor c_next{0, 0};
+  const Cursor c_first{per_head > 0 ? t_first % per_head : 0, per_head > 0 ? t_first / per_head : 0};
+  Cursor c_next = c_first;
   const uint32_t q_row_bytes = 2u * (uint32_t)(P.heads * D);
   // Tile at the cursor into slot S: Qs and dO rows (LDS-destination loads) and, in the
   // first 16 lanes of each wave, lse / delta of rows 8 w .. 8 w + 7 into registers.
@@ -307,7 +312,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   // loads behind a tile's rows is the same in every wave.
   float pend[2] = {0.f, 0.f};
   int pend_last[2] = {0, 0};
-  Cursor c_lse{0, 0};
+  Cursor c_lse = c_first;
   int lse_left = n_tiles;
   auto pend_load = [&](auto slot) __attribute__((always_inline)) {
     constexpr int S = decltype(slot)::value;
@@ -447,7 +452,7 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
   lds_int* const ctr_gave_up = ctr_full + 4;
   const int polls = P.poll_limit > 0 ? P.poll_limit : kBwdSpinMax;
   const bool loader = wave < kKvLoaders;
-  Cursor c_pos{0, 0};
+  Cursor c_pos = c_first;
   auto tile = [&](auto slot, int t) __attribute__((always_inline)) {
     constexpr int S = decltype(slot)::value;
     if (loader) {
@@ -499,6 +504,17 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     if (key + 16 * kb >= P.seq) continue;
+    if (P.kv_split > 1) {  // fp32 partials of this query range
+      const size_t rows = (size_t)P.batch * P.seq * kv_heads;
+      float* pk = P.kv_part + ((size_t)split * 2 * rows +
+                               ((size_t)b * P.seq + key + 16 * kb) * kv_heads + kvl) * D + 4 * g;
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) {
+        *reinterpret_cast<f32x4*>(pk + 16 * db) = dkT[db][kb] * kLn2;
+        *reinterpret_cast<f32x4*>(pk + rows * D + 16 * db) = dvT[db][kb];
+      }
+      continue;
+    }
     const size_t at = ((size_t)b * P.seq + key + 16 * kb) * kv_stride + (size_t)kvh * D + 4 * g;
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) {
@@ -511,6 +527,29 @@ void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
       *reinterpret_cast<f32x4*>(P.dV + at + 16 * db) = v4;
     }
   }
+}
+
+// Sums the query-range partials of dK and dV in range order into the gradient rows
+// (overwritten, or added to): 4 columns of both a thread.
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_combine_kernel(const AttnBwdParams P) {
+  const int kv_heads = P.heads / P.group, c4 = kv_heads * P.head_dim / 4;
+  const long long n4 = (long long)P.batch * P.seq * c4;
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  const long long row = i / c4;
+  const size_t at = (size_t)row * P.n_kv * P.head_dim + (size_t)P.kv_head0 * P.head_dim +
+                    4 * (size_t)(i - row * c4);
+  f32x4 k = {0.f, 0.f, 0.f, 0.f}, v = k;
+  for (int c = 0; c < P.kv_split; ++c) {
+    k += *reinterpret_cast<const f32x4*>(P.kv_part + ((size_t)(2 * c) * n4 + i) * 4);
+    v += *reinterpret_cast<const f32x4*>(P.kv_part + ((size_t)(2 * c + 1) * n4 + i) * 4);
+  }
+  if (P.accumulate) {
+    k += *reinterpret_cast<const f32x4*>(P.dK + at);
+    v += *reinterpret_cast<const f32x4*>(P.dV + at);
+  }
+  *reinterpret_cast<f32x4*>(P.dK + at) = k;
+  *reinterpret_cast<f32x4*>(P.dV + at) = v;
 }
 
 // ---------------------------------------------------------------------------------
@@ -827,8 +866,28 @@ hipError_t launch_attn_bwd_dkdv(const AttnBwdParams& p_in, hipStream_t s) {
   const int n_kt = (int)((p.seq + kKvTile - 1) / kKvTile);
   const void* fn = p.head_dim == 128 ? reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128>)
                                      : reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64>);
-  return hipLaunchKernel(fn, dim3(n_kt * (p.heads / p.group) * p.batch), dim3(kKvThreads), args,
-                         0, s);
+  if (p.kv_split < 1 || (p.kv_split > 1 && !p.kv_part)) return hipErrorInvalidValue;
+  const hipError_t e2 =
+      hipLaunchKernel(fn, dim3(n_kt * p.kv_split * (p.heads / p.group) * p.batch),
+                      dim3(kKvThreads), args, 0, s);
+  if (e2 != hipSuccess || p.kv_split == 1) return e2;
+  const long long n4 = (long long)p.batch * p.seq * (p.heads / p.group) * p.head_dim / 4;
+  return hipLaunchKernel(reinterpret_cast<const void*>(&attn_bwd_dkdv_combine_kernel),
+                         dim3((unsigned)((n4 + 255) / 256)), dim3(256), args, 0, s);
+}
+
+// With fewer key tiles than CUs (short sequences, few kv heads) each one's query tiles are
+// cut into ranges, as many as fit the chip in one round, of at least four tiles (16 query and
+// 4 kv heads, S = 4096, 1024 rows: 64 workgroups 196 us, 256 and the sum of their partials 83;
+// 70B, S_loc = 256: 109 -> 62; 8 heads, S = 1280, 640 rows: 44.6 -> 38.3).
+int attn_bwd_kv_split(const AttnBwdParams& p) {
+  const long long items = (p.seq + kKvTile - 1) / kKvTile * (p.heads / p.group) * p.batch;
+  long long tiles = 0;
+  for (int k = 0; k < p.n_seg; ++k) tiles += (p.seg_rows[k] + kQStage - 1) / kQStage;
+  tiles *= p.group;
+  if (items <= 0) return 1;
+  const long long n = std::min({(long long)kAttnTargetWorkgroups / items, tiles / 4, 8LL});
+  return n > 1 ? (int)n : 1;
 }
 
 hipError_t launch_attn_bwd_dq(const AttnBwdParams& p, hipStream_t s) {

@@ -225,6 +225,11 @@ struct AttnBwdParams {
   int dq_split;
   int dq_split_len;
   float* dq_part;
+  // dK / dV query-range split (attn_bwd_kv_split): with kv_split > 1 each range of a key
+  // tile's query tiles writes fp32 partials kv_part [kv_split][2][B S][H_s / g][d] (dK, then
+  // dV), summed into dK and dV by a second kernel.
+  int kv_split;
+  float* kv_part;
   // Row strides and head placement of inputs that come from a wider buffer (a saved
   // forward): O's token rows o_ld elements apart (0: H_s d); lse rows of this launch's
   // heads at lse_head0 .. of [B, lse_heads, S_loc] (lse_heads = 0: H_s rows from 0).
@@ -239,6 +244,10 @@ struct AttnBwdParams {
 // Number of key ranges for the dQ kernel (and their length, a multiple of the key
 // stage, in *split_len); depends on the shape only.
 int attn_bwd_dq_split(const AttnBwdParams& p, int* split_len);
+
+// Number of query ranges for the dK / dV kernel (uses seq, heads, group, batch and the
+// segments of p).
+int attn_bwd_kv_split(const AttnBwdParams& p);
 
 // The three kernels of the backward, in this order: delta; dK / dV; dQ.
 hipError_t launch_attn_bwd_prep(const AttnBwdParams& p, hipStream_t s);

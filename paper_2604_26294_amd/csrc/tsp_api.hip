@@ -279,8 +279,8 @@ MlpBwdWs mlp_bwd_ws(const Dims& d) {
 // A, dA and dQ of a group's shards side by side, [M, n H_s d] bf16 each; lse, delta [B, n H_s,
 // S_loc] fp32; A^T and dQ^T [n H_s d, M rounded up to 64] bf16 (the A operands of the
 // weight-gradient products, zero past M); then the space that the forward recomputation's
-// key-range partials, the dQ kernel's key-range partials and the dX product's partial sums
-// take one after the other.
+// key-range partials, the dK / dV kernel's query-range and the dQ kernel's key-range partials
+// and the dX product's partial sums take one after the other.
 struct AttnBwdWs {
   size_t q, a, da, dq, lse, delta, at, dqt, part, pml, total;
   int m_pad;
@@ -295,6 +295,8 @@ void attn_bwd_segments(const Dims& d, int n, AttnBwdParams* bp) {
   bp->batch = d.B;
   bp->s_loc = d.s_loc;
   bp->heads = n * d.hs;
+  bp->group = d.g;
+  bp->seq = d.S;
   bp->n_seg = ap.n_seg;
   for (int k = 0; k < 2; ++k) {
     bp->seg_row0[k] = ap.seg_row0[k];
@@ -316,7 +318,9 @@ AttnBwdWs attn_bwd_ws(const Dims& d) {
     const int ns = tsp::attn_bwd_dq_split(bp, nullptr);
     const size_t dq = ns > 1 ? (size_t)ns * d.M * n * d.hs * d.d * 4 : 0;
     const size_t dx = nn_part_bytes(d, n * d.hs * d.d);
-    shared = std::max({shared, dq, dx});
+    const int kvs = tsp::attn_bwd_kv_split(bp);
+    const size_t kv = kvs > 1 ? (size_t)kvs * 2 * d.B * d.S * n * d.ks * d.d * 4 : 0;
+    shared = std::max({shared, dq, dx, kv});
   }
   const size_t rows = (size_t)d.M * g * d.hs;
   const size_t qa = align_up(rows * d.d * 2), f = align_up(rows * 4);
@@ -822,14 +826,14 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     bp.dK = dk;
     bp.dV = dv;
     bp.accumulate = accumulate ? 1 : 0;
-    bp.group = d.g;
     bp.head_dim = d.d;
-    bp.seq = d.S;
     bp.n_kv = d.nkv;
     bp.kv_head0 = r0 * d.ks;
     bp.scale = d.scale;
     bp.dq_split = tsp::attn_bwd_dq_split(bp, &bp.dq_split_len);
     bp.dq_part = part;
+    bp.kv_split = tsp::attn_bwd_kv_split(bp);
+    bp.kv_part = part;
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st, tsp::launch_attn_bwd_prep(bp, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_KV, st, tsp::launch_attn_bwd_dkdv(bp, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_Q, st, tsp::launch_attn_bwd_dq(bp, st));

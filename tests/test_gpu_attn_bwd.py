@@ -120,10 +120,12 @@ def test_attention_backward_second_stage(wl, p):
 # queries 170 .. 254), at the end of the buffer (rank 3), and within a key tile (zigzag).
 ODD_SEQ = Workload("odd-seq-340", 1, 340, 256, 512, 4, 4, 64, 4, 0, w_std=0.06)
 ODD_ZZ = Workload("odd-seq-580", 2, 580, 256, 512, 2, 2, 128, 2, 0, w_std=0.06, layout=1)
+# the same with each key tile's 24 query tiles (two heads, two segments) cut into 6 ranges
+ODD_SPLIT = Workload("odd-seq-1332", 1, 1332, 256, 512, 4, 2, 64, 2, 0, w_std=0.06, layout=1)
 
 
-@pytest.mark.parametrize("wl,p", [(ODD_SEQ, 2), (ODD_SEQ, 3), (ODD_ZZ, 1)],
-                         ids=["contiguous-r2", "contiguous-r3", "zigzag-r1"])
+@pytest.mark.parametrize("wl,p", [(ODD_SEQ, 2), (ODD_SEQ, 3), (ODD_ZZ, 1), (ODD_SPLIT, 1)],
+                         ids=["contiguous-r2", "contiguous-r3", "zigzag-r1", "split-r1"])
 def test_first_stage_reads_no_key_past_the_last_visible_one(wl, p):
     """K/V rows past the last visible key hold NaN here; the contributions to their
     gradients are exactly zero all the same, and the others meet the oracle."""
@@ -164,10 +166,11 @@ def test_two_stages_accumulate_into_one_dx():
     assert torch.allclose(both, first + second_only, rtol=1e-5, atol=1e-6)
 
 
-def test_first_stage_accumulates():
+@pytest.mark.parametrize("wl,p", [(MID_GQA64, 2), (MID_GQA8, 1)], ids=["whole", "split"])
+def test_first_stage_accumulates(wl, p):
     """A second first-stage call with accumulate != 0 adds the same dX, weight-gradient
-    blocks and K/V-gradient contributions again (up to the fp32 summation order)."""
-    wl, p = MID_GQA64, 2
+    blocks and K/V-gradient contributions again (up to the fp32 summation order), with the
+    K/V gradients written by the kernel itself or summed from query ranges."""
     x_bits, w_bits, dy_bits = _inputs(wl)
     prob = RankProblem(wl, x_bits, w_bits, p)
     prob.prefill_kv(include_self=True)
