@@ -82,12 +82,10 @@ struct Cfg {
   static constexpr int TM = WM / 32, TN = WN / 16;  // 32-row, 16-column blocks
   // Output columns of a wavefront: 32-column block j starts at wn COL_WN + j COL_BLK.
   static constexpr int COL_WN = WN, COL_BLK = 32;
-  static constexpr bool BWD = EPI == EPI_SWIGLU_BWD;
-  static constexpr int NAP = BWD ? 2 : 1;                                  // A panels
-  static constexpr int NBP = EPI == EPI_SWIGLU ? 2 : (BWD ? 3 : 1);        // B panels
+  static constexpr int NBP = EPI == EPI_SWIGLU ? 2 : 1;       // B panels
   static constexpr int TNB = NBP * TN;
   static constexpr int NB = NBP * BN;                         // B rows of an NT panel
-  static constexpr int A_BYTES = NAP * BM * BK * 2;
+  static constexpr int A_BYTES = BM * BK * 2;
   static constexpr int B_BYTES = NB * BK * 2;                  // NT [NB][64] or NN [64][BN]
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int LDS_BYTES = STAGES * STAGE;
@@ -97,11 +95,11 @@ struct Cfg {
   // every wavefront loads its share.
   static constexpr bool HALF_LOADERS = !NN && WAVES == 8;
   static constexpr int LOADS = (HALF_LOADERS ? 2 : 1) *
-      (NAP * BM / 8 / WAVES + (NN ? BK * (BN * 2) / 1024 / WAVES : NB / 8 / WAVES));
+      (BM / 8 / WAVES + (NN ? BK * (BN * 2) / 1024 / WAVES : NB / 8 / WAVES));
   static_assert(STAGES >= 2 && LDS_BYTES <= 160 * 1024, "LDS ring");
   static_assert(LOADS * (STAGES - 2) < 64, "vmcnt range");
   static constexpr int NN_RB = BN * 2;                         // NN panel row bytes
-  static_assert(!(NN && (EPI == EPI_SWIGLU || BWD)), "SwiGLU operands are [N, K]");
+  static_assert(!(NN && EPI == EPI_SWIGLU), "SwiGLU operands are [N, K]");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
   static_assert(!NN || BN == 64 || BN == 128, "NN panel swizzle");
   static_assert((BM / 8) % WAVES == 0 && (NB / 8) % WAVES == 0, "NT DMA cover");
@@ -206,7 +204,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Epilogue of one C tile (configuration C: WAVES, WM, WN, TM, TN, TNB, LDS_BYTES, BWD)
+// Epilogue of one C tile (configuration C: WAVES, WM, WN, TM, TN, COL_WN, COL_BLK, LDS_BYTES)
 // from the accumulators of each wavefront, staged through the workgroup's LDS (free:
 // every operand read has completed).
 template <class C, int EPI, class Acc>
@@ -228,11 +226,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
     return E[(16 * q + 4 * (lane >> 4) + e) * EST + 16 * j + (lane & 15)];
   };
   const int ncol0 = n0 + wn * C::COL_WN;
-  if constexpr (C::BWD) {
+  if constexpr (EPI == EPI_SWIGLU_BWD) {
     // SwiGLU backward.  Per 32-row block: dG, dU and Hs replace G, U and dHs in the
-    // accumulators, then each goes through LDS once: dG and dU to their row-major
-    // outputs (4-column chunks, as the forward's Hs), and all three transposed (each
-    // lane writes 8 consecutive rows of one column as one 16-byte vector).
+    // accumulators, then each is staged once in LDS as bf16, transposed (a lane holds four
+    // consecutive rows of a column: one 8-byte write), [column][32 rows].  The transposed
+    // outputs are 16-byte reads of that, the row-major ones (dG, dU) transpose reads of 4
+    // columns of a row.  (Staged in fp32 and read back column by column this epilogue took
+    // 17 % of the launch, 180 of 1045 us at 7B, S_loc = 8192, 4 shards.)
+    constexpr int TST = 32 * 2 + 16;  // staging stride of a column, in bytes
+    lds_char* T = (lds_char*)L + wave * (C::WN * TST);
+    const int l16 = lane & 15, lg = lane >> 4;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -250,41 +253,48 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
             acc[2 * i + r][j + 2 * TN][e] = sl * u;                        // Hs
           }
       const int mrow0 = m0 + wm * C::WM + 32 * i;
+      if (mrow0 + 32 > P.M) {  // rows M..ldt of the transposes: zero padding
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int j = 0; j < 3 * TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (mrow0 + 16 * r + 4 * lg + e >= P.M) acc[2 * i + r][j][e] = 0.f;
+      }
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) staged(r, j, e) = acc[2 * i + r][q * TN + j][e];
+          for (int j = 0; j < TN; ++j) {
+            const f32x4& v = acc[2 * i + r][q * TN + j];
+            *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(
+                T + (16 * j + l16) * TST + 2 * (16 * r + 4 * lg)) =
+                u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+          }
         wave_lds_sync();
         if (q < 2) {
+          // Lane group lg takes columns 16 c + 4 lg .. +3 of rows 16 r + l16.
           uint16_t* H = q == 0 ? P.H : P.H2;
 #pragma unroll
-          for (int r = 0; r < PER_LANE; ++r) {
-            const int idx = r * kWave + lane, row = idx / CPR, c4 = idx % CPR;
-            const int mm = mrow0 + row, nn = ncol0 + 4 * c4;
-            if (mm >= P.M || nn >= P.h_cols) continue;  // columns N..h_cols: zero padding
-            const f32x4 v = *reinterpret_cast<const f32x4*>(E + row * EST + 4 * c4);
-            *reinterpret_cast<u32x2*>(H + (size_t)mm * P.ldh + nn) =
-                nn < P.N ? u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}
-                         : u32x2{0u, 0u};
-          }
-        }
-        uint16_t* T = q == 0 ? P.T0 : (q == 1 ? P.T1 : P.T2);
-        for (int k = lane; k < 4 * C::WN; k += kWave) {
-          const int c = k % C::WN, r0 = 8 * (k / C::WN);
-          const int nn = ncol0 + c, mm = mrow0 + r0;
-          if (nn >= P.N || mm >= P.ldt) continue;  // rows M..ldt: zero padding
-          uint32_t w[4];
+          for (int r = 0; r < 2; ++r)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v0 = mm + 2 * e < P.M ? E[(r0 + 2 * e) * EST + c] : 0.f;
-            const float v1 = mm + 2 * e + 1 < P.M ? E[(r0 + 2 * e + 1) * EST + c] : 0.f;
-            w[e] = pack_bf16x2(v0, v1);
-          }
-          *reinterpret_cast<u32x4*>(T + (size_t)nn * P.ldt + mm) = u32x4{w[0], w[1], w[2], w[3]};
+            for (int c = 0; c < TN; ++c) {
+              const u32x2 v = lds_read_tr(T + (16 * c + 4 * lg + (l16 >> 2)) * TST +
+                                          2 * (16 * r + 4 * (l16 & 3)));
+              const int mm = mrow0 + 16 * r + l16, nn = ncol0 + 16 * c + 4 * lg;
+              if (mm < P.M && nn < P.h_cols)  // columns N..h_cols: zero padding
+                *reinterpret_cast<u32x2*>(H + (size_t)mm * P.ldh + nn) = nn < P.N ? v : u32x2{0u, 0u};
+            }
+        }
+        uint16_t* Tg = q == 0 ? P.T0 : (q == 1 ? P.T1 : P.T2);
+#pragma unroll
+        for (int k = 0; k < C::WN / 16; ++k) {
+          const int c = 16 * k + (lane >> 2), r0 = 8 * (lane & 3);
+          const u32x4 v = lds_read16(T + c * TST + 2 * r0);
+          const int nn = ncol0 + c, mm = mrow0 + r0;
+          if (nn < P.N && mm < P.ldt) st16(Tg + (size_t)nn * P.ldt + mm, v);
         }
         wave_lds_sync();
       }
@@ -454,8 +464,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     if (multi) k_part = P.k_part;
     asm volatile("" : "+s"(k_part));
   }
-  // Per-lane DMA offsets of this tile (A and A2 share rows and stride, as do the NT B
-  // panels), and the operands' buffer resources.
+  // Per-lane DMA offsets of this tile (the NT B panels share rows and stride), and the
+  // operands' buffer resources.
   // With HALF_LOADERS only the first half of the wavefronts (one per SIMD: wavefronts are
   // placed on the SIMDs round-robin) issue loads, each its own share and that of
   // wavefront wave + W/2 (the other wavefront of its SIMD): a CU's load path takes a
@@ -478,10 +488,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     if constexpr (C::HALF_LOADERS) rows_b_hi.init(P.ldb, n0, P.N, wave2, lane);
   }
   const rsrc_t rs_a = make_rsrc(P.A);
-  const rsrc_t rs_a2 = make_rsrc(C::BWD ? P.A2 : P.A);
   const rsrc_t rs_b = make_rsrc(P.B);
-  const rsrc_t rs_b2 = make_rsrc(EPI == EPI_SWIGLU || C::BWD ? P.B2 : P.B);
-  const rsrc_t rs_b3 = make_rsrc(C::BWD ? P.B3 : P.B);
+  const rsrc_t rs_b2 = make_rsrc(EPI == EPI_SWIGLU ? P.B2 : P.B);
   auto dma_stage = [&](int stage, int k0) __attribute__((always_inline)) {
     if (!loader) return;
     lds_char* S = Ls + stage * C::STAGE;
@@ -505,21 +513,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     }
     rows_a.issue(S, rs_a, (uint32_t)k0, wave);
     if constexpr (C::HALF_LOADERS) rows_a_hi.issue(S, rs_a, (uint32_t)k0, wave2);
-    if constexpr (C::BWD) {
-      rows_a.issue(S + BM * BK * 2, rs_a2, (uint32_t)k0, wave);
-      if constexpr (C::HALF_LOADERS) rows_a_hi.issue(S + BM * BK * 2, rs_a2, (uint32_t)k0, wave2);
-    }
     rows_b.issue(S + C::A_BYTES, rs_b, (uint32_t)k0, wave);
     if constexpr (C::HALF_LOADERS) rows_b_hi.issue(S + C::A_BYTES, rs_b, (uint32_t)k0, wave2);
-    if constexpr (EPI == EPI_SWIGLU || C::BWD) {
+    if constexpr (EPI == EPI_SWIGLU) {
       rows_b.issue(S + C::A_BYTES + BN * BK * 2, rs_b2, (uint32_t)k0, wave);
       if constexpr (C::HALF_LOADERS)
         rows_b_hi.issue(S + C::A_BYTES + BN * BK * 2, rs_b2, (uint32_t)k0, wave2);
-    }
-    if constexpr (C::BWD) {
-      rows_b.issue(S + C::A_BYTES + 2 * BN * BK * 2, rs_b3, (uint32_t)k0, wave);
-      if constexpr (C::HALF_LOADERS)
-        rows_b_hi.issue(S + C::A_BYTES + 2 * BN * BK * 2, rs_b3, (uint32_t)k0, wave2);
     }
   };
 
@@ -556,16 +555,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
     const lds_char* SA = Ls + (kt % STAGES) * C::STAGE;
     const lds_char* SB = SA + C::A_BYTES;
     // Operands of substep s into set s % 2.
-    u32x4 a[2][TM], a2[2][TM], b[2][TNB];
+    u32x4 a[2][TM], b[2][TNB];
     auto read_sub = [&](int s) __attribute__((always_inline)) {
       const int xo = opa ^ (64 * s), q = s & 1;
 #pragma unroll
       for (int i = 0; i < TM; ++i) a[q][i] = lds_read16(SA + (wm * C::WM + 16 * i) * 128 + xo);
-      if constexpr (C::BWD) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          a2[q][i] = lds_read16(SA + BM * BK * 2 + (wm * C::WM + 16 * i) * 128 + xo);
-      }
 #pragma unroll
       for (int j = 0; j < TNB; ++j) {
         if constexpr (NN) {
@@ -592,13 +586,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TNB; ++j)
-          acc[i][j] = mfma16(C::BWD && j >= 2 * TN ? a2[q][i] : a[q][i], b[q][j], acc[i][j]);
+          acc[i][j] = mfma16(a[q][i], b[q][j], acc[i][j]);
     }
     // Issue order: the operand reads of k-substep s+1 are spread between the MFMAs of
     // substep s (R / M per MFMA, one more for the first R mod M), so LDS latency hides
     // behind matrix work.
     {
-      constexpr int R = C::NAP * TM + (NN ? 2 : 1) * TNB;  // LDS reads per substep
+      constexpr int R = TM + (NN ? 2 : 1) * TNB;  // LDS reads per substep
       constexpr int M = TM * TNB;                          // MFMAs per substep
       constexpr int RM = R / M;
       __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
@@ -630,6 +624,13 @@ struct Tile {
 };
 
 // ------------------------------------------------------------------ alternating tiles
+// The barrier that ends a slot of both tiles below: nothing moves across it.
+__device__ __forceinline__ void swap_slot() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // 256 x 256 accumulators (SwiGLU: 256 x 128 gate and as many up) on 8 wavefronts, each
 // 128 x 64, in which the two wavefronts of a SIMD take turns: while one issues the MFMAs
 // of a quarter of its K step (64 x 32 of its output, 256 matrix cycles), the other reads
@@ -678,7 +679,6 @@ struct PpTile {
   static constexpr int WM = 128, WN = SW ? 32 : 64, TM = 4, TN = WN / 16;
   // NN units are 128 consecutive columns, so a wavefront's second 32 columns are 128 on.
   static constexpr int COL_WN = NN ? 32 : WN, COL_BLK = NN ? 128 : 32;
-  static constexpr bool BWD = false;
   static_assert(!MULTI || (NN && EPI == EPI_ACC), "multi-part contractions");
   static constexpr int UNIT = 128 * BK * 2;
   static constexpr int LDS_BYTES = 8 * UNIT;  // A units [stage parity][half], then B units
@@ -861,11 +861,6 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-  auto swap_slot = [&]() __attribute__((always_inline)) {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-  };
   // Ends a MEM slot, issues the quarter's MFMAs and ends their slot.  The wait for the LDS
   // reads comes before the MFMAs in every quarter, also where they are for the next step:
   // the units' refills rely on it.
@@ -956,6 +951,177 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
   __syncthreads();  // operand units are free for the epilogue
 
   gemm_epilogue<C, EPI>(P, acc, L, wave, lane, m0, n0, wm, wn, split);
+}
+
+// SwiGLU backward on the alternating schedule: 128 x 128 tiles of G = X W1^T, U = X W3^T and
+// dHs = dY W2^T on 8 wavefronts, each 64 x 32 of all three.  A 64-deep stage is five units
+// (X, dY, W1, W3, W2: 128 rows each), two stages of each fill the LDS; a step has one slot per
+// product, X staying in registers for two of them:
+//            operands    MEM reads   MEM loads (unit of stage)
+//   Q0       dY x W2     dY, W2      W1, X of k + 1
+//   Q1       X x W1      X, W1       W3    of k + 1
+//   Q2       X x W3      W3          dY, W2 of k + 2
+// with the slot order, the refill rule and the wait of PpTile (five units are issued after
+// the one that the next quarter reads: vmcnt(10), a lead of four quarters).  It is bound by
+// the CU's load path (80 KB per 1536 matrix cycles: 5 units per 3 blocks of 128 x 128, where
+// PpTile loads 4 per 4): with the waits loosened it runs as long, without the loads 30 %
+// less.  7B, S_loc = 8192, 4 shards a launch: 1060 us against 1207 for a two-slot ring with a
+// barrier per step, which asked for a whole stage at once.
+struct PpBwdTile {
+  static constexpr bool NN = false;
+  static constexpr int EPI = EPI_SWIGLU_BWD;
+  static constexpr int BM = 128, BN = 128, WGM = 2, WGN = 4, WAVES = 8, THREADS = kWave * WAVES;
+  static constexpr int WM = 64, WN = 32, TM = 2, TN = WN / 16;
+  static constexpr int COL_WN = WN, COL_BLK = 32;
+  static constexpr int UNIT = 128 * BK * 2;
+  static constexpr int LDS_BYTES = 10 * UNIT;  // [X, dY, W1, W3, W2][stage parity]
+  static __device__ __forceinline__ void run(const GemmParams& P, int w);
+};
+
+__device__ __forceinline__ void PpBwdTile::run(const GemmParams& P, const int w) {
+  using C = PpBwdTile;
+  __shared__ __attribute__((aligned(1024))) char L[LDS_BYTES];
+  lds_char* Ls = (lds_char*)L;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int tiles_n = (P.N + BN - 1) / BN;
+  int tm, tn;
+  tile_coords(w, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
+  const int m0 = tm * BM, n0 = tn * BN, nk = P.K / BK;
+
+  enum { X = 0, Y = 1, W1 = 2, W3 = 3, W2 = 4 };
+  // Load i (of two) of a unit: LDS rows 8 (8 i + wave) + lane / 8.
+  uint32_t off_a[2], off_b[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = 8 * (8 * i + wave) + (lane >> 3), pc = (lane & 7) ^ nt_swz(r);
+    off_a[i] = 2u * ((uint32_t)min(m0 + r, P.M - 1) * (uint32_t)P.lda + 8u * (uint32_t)pc);
+    off_b[i] = 2u * ((uint32_t)min(n0 + r, P.N - 1) * (uint32_t)P.ldb + 8u * (uint32_t)pc);
+  }
+  const rsrc_t rs[5] = {make_rsrc(P.A), make_rsrc(P.A2), make_rsrc(P.B), make_rsrc(P.B2),
+                        make_rsrc(P.B3)};
+  // Unit u of stage k into slot S.
+  auto load = [&](auto unit, auto slot, int k) __attribute__((always_inline)) {
+    constexpr int U = decltype(unit)::value, S = decltype(slot)::value;
+    lds_char* dst = Ls + (2 * U + S) * UNIT + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      dma16(rs[U], U == X || U == Y ? off_a[i] : off_b[i], 2u * (uint32_t)(k * BK),
+            dst + i * 8192);
+  };
+  // Operand reads as in PpTile; W2's units are out of reach of the 16-bit immediate offset.
+  int ra[2], rb[2], rb2[2];
+  {
+    const int l16 = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int op = l16 * 128 + 16 * ((4 * t + g) ^ nt_swz(l16));
+      ra[t] = wm * 64 * 128 + op;
+      rb[t] = 2 * W1 * UNIT + wn * 32 * 128 + op;
+      rb2[t] = 2 * W2 * UNIT + wn * 32 * 128 + op;
+    }
+  }
+  u32x4 ax[4][2], ay[4][2], b1[2][2], b3[2][2], b2[2][2];
+  auto read_a = [&](auto unit, auto slot, u32x4 (&a)[4][2]) __attribute__((always_inline)) {
+    constexpr int U = decltype(unit)::value, S = decltype(slot)::value;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a[i][t] = lds_read16(Ls + ra[t] + ((2 * U + S) * UNIT + i * 16 * 128));
+  };
+  auto read_b = [&](auto unit, auto slot, u32x4 (&b)[2][2]) __attribute__((always_inline)) {
+    constexpr int U = decltype(unit)::value, S = decltype(slot)::value;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        b[j][t] = U == W2 ? lds_read16(Ls + rb2[t] + (S * UNIT + j * 16 * 128))
+                          : lds_read16(Ls + rb[t] + ((2 * (U - W1) + S) * UNIT + j * 16 * 128));
+  };
+  f32x4 acc[4][6];  // [16-row block][G, U, dHs x 16-column block]
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 6; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // Ends a MEM slot, issues product `panel`'s MFMAs and ends their slot.
+  auto quarter = [&](auto panel, u32x4 (&a)[4][2], u32x4 (&b)[2][2]) __attribute__((always_inline)) {
+    constexpr int PN = decltype(panel)::value;
+    swap_slot();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][2 * PN + j] = mfma16(a[i][t], b[j][t], acc[i][2 * PN + j]);
+    __builtin_amdgcn_s_setprio(0);
+    swap_slot();
+  };
+  // Step k in slot S = k mod 2, `left` steps left, this one included.
+  auto step = [&](auto slot, const int k, const int left) __attribute__((always_inline)) {
+    constexpr int S = decltype(slot)::value;
+    constexpr Ic<S> s{};
+    constexpr Ic<1 - S> o{};
+    read_a(Ic<Y>{}, s, ay);
+    read_b(Ic<W2>{}, s, b2);
+    if (left >= 2) {
+      load(Ic<W1>{}, o, k + 1);
+      load(Ic<X>{}, o, k + 1);
+      wait_dma<10>();
+    } else {
+      wait_dma<2>();
+    }
+    quarter(Ic<2>{}, ay, b2);
+    read_a(Ic<X>{}, s, ax);
+    read_b(Ic<W1>{}, s, b1);
+    if (left >= 2) {
+      load(Ic<W3>{}, o, k + 1);
+      wait_dma<10>();
+    } else {
+      wait_dma<0>();
+    }
+    quarter(Ic<0>{}, ax, b1);
+    read_b(Ic<W3>{}, s, b3);
+    if (left >= 3) {
+      load(Ic<Y>{}, s, k + 2);
+      load(Ic<W2>{}, s, k + 2);
+      wait_dma<10>();
+    } else if (left == 2) {
+      wait_dma<6>();
+    }
+    quarter(Ic<1>{}, ax, b3);
+  };
+
+  constexpr Ic<0> s0{};
+  constexpr Ic<1> s1{};
+  load(Ic<Y>{}, s0, 0);
+  load(Ic<W2>{}, s0, 0);
+  load(Ic<W1>{}, s0, 0);
+  load(Ic<X>{}, s0, 0);
+  load(Ic<W3>{}, s0, 0);
+  if (nk > 1) {
+    load(Ic<Y>{}, s1, 1);
+    load(Ic<W2>{}, s1, 1);
+    wait_dma<10>();
+  } else {
+    wait_dma<6>();
+  }
+  swap_slot();                  // dY and W2 of step 0 resident
+  if (wave >= 4) swap_slot();  // wavefronts 4-7 run one slot behind
+  for (int k = 0; k < nk; k += 2) {
+    step(s0, k, nk - k);
+    if (k + 1 < nk) step(s1, k + 1, nk - k - 1);
+  }
+  if (wave < 4) swap_slot();
+  __syncthreads();  // operand units are free for the epilogue
+
+  gemm_epilogue<C, EPI>(P, acc, L, wave, lane, m0, n0, wm, wn);
 }
 
 template <class K>
@@ -1176,12 +1342,18 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
                          dim3((unsigned)((threads + 255) / 256)), dim3(256), args, 0, s);
 }
 
-// SwiGLU backward (M = S_loc, N = F/D): 128 x 128 tiles with five 16 KB operand panels
-// per K step (X, dY; W1, W3, W2), two slots = 160 KB.
+// SwiGLU backward (M = S_loc, N = F/D).  Long launches are cut in two: over many rounds the
+// workgroups of an XCD drift apart and share fewer operand panels in its L2 (7B, S_loc = 8192:
+// 8 products, 22 rounds, 2290 us; two launches of 4, 11 rounds each, 2075), while short ones
+// need all products to fill the chip (S_loc = 1024: 704 tiles, 332 us).
+int gemm_swiglu_bwd_per_launch(const GemmParams* ps, int n) {
+  return n > 4 && rounds(tiles_of(ps, n, 128, 128)) > 12 ? (n + 1) / 2 : n;
+}
+
 hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i)
     if (ps[i].ldt % 8 != 0 || ps[i].ldt < ps[i].M) return hipErrorInvalidValue;
-  return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU_BWD, 2>>(ps, n, s);
+  return launch_group<PpBwdTile>(ps, n, s);
 }
 
 // Weight gradients (M = F/D or H_s d, N = h, K = tokens), several products in one launch.

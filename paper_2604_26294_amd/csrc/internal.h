@@ -95,6 +95,8 @@ struct GemmParams {
 // 0; the tiles of product i follow those of the ones before it).
 hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s);
 hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t s);
+// How many of n such products to put in one launch.
+int gemm_swiglu_bwd_per_launch(const GemmParams* ps, int n);
 // The accumulate epilogue over [K, N] operands.  Products with few output tiles may split
 // their contraction (gemm_nn_acc_splits ranges) through an fp32 workspace `part` of at least
 // splits * M * N floats (unused when splits == 1).

@@ -248,12 +248,12 @@ struct MlpBwdWs {
 // Most ring steps of one dX product (two operand pairs each).
 constexpr int kMlpBwdDxSteps = tsp::kGemmPartsMax / 2;
 // Ring steps per group of the MLP backward: a step alone leaves most of the GPU idle at
-// short sequences (7B, S_loc = 1024: 88 tiles in the gate product), so up to 8 are taken
-// together; long sequences fill it with the steps of one dX product, which keeps the
-// workspace of their wider operands down (7B, S_loc = 8192: 11 rounds of gate tiles).
+// short sequences (7B, S_loc = 1024: 88 tiles in the gate product), and its weight gradients
+// the last round of the chip half empty at any length (7B, 96 tiles each: 4 steps in launches
+// of 4 products make 12 rounds for the layer, 8 steps in launches of 8 products 9: 2110 ->
+// 1795 us at S_loc = 8192), so a group takes as many as a launch holds products.
 int mlp_bwd_group(const Dims& d) {
-  int n = d.M <= 4096 ? kGroupMax : kMlpBwdDxSteps;
-  if (n > d.D) n = d.D;
+  int n = d.D < kGroupMax ? d.D : kGroupMax;
   while (n > 1 && d.M * n * d.fs_pad * 2 >= (1LL << 32)) --n;  // 32-bit operand offsets
   return n;
 }
@@ -513,10 +513,10 @@ GemmParams dw_params(const Dims& d, const uint16_t* t, int m_pad, const uint16_t
   return q;
 }
 
-// Backward of run_mlp (same ring order), in groups of mlp_bwd_group steps.  Per group: one
-// grouped launch for G, U, dHs and the SwiGLU backward of its shards, the accumulating
-// products for dX (over up to kMlpBwdDxSteps steps each), and three grouped launches for the
-// weight gradients (each [F/D, h] per shard, contracting over the M tokens).
+// Backward of run_mlp (same ring order), in groups of mlp_bwd_group steps.  Per group: one or
+// two grouped launches for G, U, dHs and the SwiGLU backward of its shards, the accumulating
+// products for dX (over up to kMlpBwdDxSteps steps each), and grouped launches for the 3 n
+// weight gradients (each [F/D, h], contracting over the M tokens).
 tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
                        const uint16_t* const* wg, const uint16_t* const* wu,
                        const uint16_t* const* wd, float* dx, int accumulate,
@@ -555,7 +555,10 @@ tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
       g[i].T2 = tr[2] + (size_t)i * d.fs * w.m_pad;
       g[i].ldt = w.m_pad;
     }
-    TSP_LAUNCH(TSP_KERNEL_BWD_GATE, st, tsp::launch_gemm_swiglu_bwd_group(g, n, st));
+    const int per_launch = tsp::gemm_swiglu_bwd_per_launch(g, n);
+    for (int i = 0; i < n; i += per_launch)
+      TSP_LAUNCH(TSP_KERNEL_BWD_GATE, st,
+                 tsp::launch_gemm_swiglu_bwd_group(g + i, std::min(n - i, per_launch), st));
 
     // dX (+)= sum of dG_j W_gate[j] + dU_j W_up[j]: one product over the operand pairs of
     // up to kMlpBwdDxSteps steps (padded columns of dG, dU are zero).
@@ -587,11 +590,14 @@ tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     }
     // dW (+)= (dG^T | dU^T | Hs^T) (X | X | dY): [F/D, M] x [M, h], padded rows are zero.
     float* const* const out[3] = {dwg, dwu, dwd};
-    for (int k = 0; k < 3; ++k) {
-      for (int i = 0; i < n; ++i)
-        g[i] = dw_params(d, tr[k] + (size_t)i * d.fs * w.m_pad, w.m_pad, k < 2 ? x : dy, d.fs,
+    for (int q = 0, m = 0; q < 3 * n; ++q) {
+      const int k = q / n, i = q % n;
+      g[m++] = dw_params(d, tr[k] + (size_t)i * d.fs * w.m_pad, w.m_pad, k < 2 ? x : dy, d.fs,
                          out[k][shard[i]], accumulate);
-      TSP_LAUNCH(TSP_KERNEL_BWD_DW, st, tsp::launch_gemm_nn_acc_group(g, n, st));
+      if (m == tsp::kGemmGroupMax || q + 1 == 3 * n) {
+        TSP_LAUNCH(TSP_KERNEL_BWD_DW, st, tsp::launch_gemm_nn_acc_group(g, m, st));
+        m = 0;
+      }
     }
   }
   return TSP_OK;
