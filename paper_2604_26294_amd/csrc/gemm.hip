@@ -414,30 +414,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& P, Acc& acc, cha
   }
 }
 
-// One output tile (work index w) of the product P.
+// The output tile at (m0, n0) of the product P (its contraction range `split`), in the
+// workgroup's LDS L.
 template <int BM, int BN, int WGM, int WGN, bool NN, int EPI, int STAGES>
-__device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
+__device__ __forceinline__ void gemm_tile(const GemmParams& P, const int m0, const int n0,
+                                          const int split, char* L) {
   using C = Cfg<BM, BN, WGM, WGN, NN, EPI, STAGES>;
   constexpr int TM = 2 * C::TM, TN = C::TN, TNB = C::TNB;  // 16 x 16 blocks
-  __shared__ __attribute__((aligned(1024))) char L[C::LDS_BYTES];
   lds_char* Ls = (lds_char*)L;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int l16 = lane & 15, lg = lane >> 4;
-
-  const int tiles_n = (P.N + BN - 1) / BN;
-  // Work index -> (contraction range, output tile): ranges outermost.
-  int split = 0, wt = w;
-  if (EPI == EPI_ACC && P.k_splits > 1) {
-    const int tiles = ((P.M + BM - 1) / BM) * tiles_n;
-    split = w / tiles;
-    wt = w - split * tiles;
-  }
-  int tm, tn;
-  tile_coords(wt, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
 
   f32x4 acc[TM][TNB];
 #pragma unroll
@@ -613,13 +602,32 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& P, const int w) {
   gemm_epilogue<C, EPI>(P, acc, L, wave, lane, m0, n0, wm, wn, split);
 }
 
+// Work index w of a product P on tiles of K -> output tile and contraction range (ranges
+// outermost).
+template <class K>
+__device__ __forceinline__ void work_tile(const GemmParams& P, const int w, int* m0, int* n0,
+                                          int* split) {
+  const int tiles_m = (P.M + K::BM - 1) / K::BM, tiles_n = (P.N + K::BN - 1) / K::BN;
+  int wt = w, tm, tn;
+  *split = 0;
+  if (K::EPI == EPI_ACC && P.k_splits > 1) {
+    *split = w / (tiles_m * tiles_n);
+    wt = w - *split * tiles_m * tiles_n;
+  }
+  tile_coords(wt, tiles_m, tiles_n, &tm, &tn);
+  *m0 = tm * K::BM;
+  *n0 = tn * K::BN;
+}
+
 // The tiles of gemm_tile as a kernel configuration.
 template <int BM_, int BN_, int WGM, int WGN, bool NN_, int EPI_, int STAGES>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, EPI = EPI_, THREADS = kWave * WGM * WGN;
   static constexpr bool NN = NN_;
-  static __device__ __forceinline__ void run(const GemmParams& P, int w) {
-    gemm_tile<BM, BN, WGM, WGN, NN, EPI, STAGES>(P, w);
+  static constexpr int LDS_BYTES = Cfg<BM_, BN_, WGM, WGN, NN_, EPI_, STAGES>::LDS_BYTES;
+  static __device__ __forceinline__ void run(const GemmParams& P, int m0, int n0, int split,
+                                             char* L) {
+    gemm_tile<BM, BN, WGM, WGN, NN, EPI, STAGES>(P, m0, n0, split, L);
   }
 };
 
@@ -682,29 +690,20 @@ struct PpTile {
   static_assert(!MULTI || (NN && EPI == EPI_ACC), "multi-part contractions");
   static constexpr int UNIT = 128 * BK * 2;
   static constexpr int LDS_BYTES = 8 * UNIT;  // A units [stage parity][half], then B units
-  static __device__ __forceinline__ void run(const GemmParams& P, int w);
+  static __device__ __forceinline__ void run(const GemmParams& P, int m0, int n0, int split,
+                                             char* L);
 };
 
 template <bool NN_, int EPI_, bool MULTI>
-__device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& P, const int w) {
+__device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& P, const int m0,
+                                                              const int n0, const int split,
+                                                              char* L) {
   using C = PpTile<NN_, EPI_, MULTI>;
-  __shared__ __attribute__((aligned(1024))) char L[C::LDS_BYTES];
   lds_char* Ls = (lds_char*)L;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int l32 = lane & 31, hh = lane >> 5;
-
-  const int tiles_n = (P.N + BN - 1) / BN;
-  int split = 0, wt = w;
-  if (MULTI && P.k_splits > 1) {
-    const int tiles = ((P.M + BM - 1) / BM) * tiles_n;
-    split = w / tiles;
-    wt = w - split * tiles;
-  }
-  int tm, tn;
-  tile_coords(wt, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
 
   // Contraction steps [kb, kb + nk); step kt of the tile lives in slot kt mod 2.
   int kb = 0, nk = P.K / BK;
@@ -975,20 +974,18 @@ struct PpBwdTile {
   static constexpr int COL_WN = WN, COL_BLK = 32;
   static constexpr int UNIT = 128 * BK * 2;
   static constexpr int LDS_BYTES = 10 * UNIT;  // [X, dY, W1, W3, W2][stage parity]
-  static __device__ __forceinline__ void run(const GemmParams& P, int w);
+  static __device__ __forceinline__ void run(const GemmParams& P, int m0, int n0, int split,
+                                             char* L);
 };
 
-__device__ __forceinline__ void PpBwdTile::run(const GemmParams& P, const int w) {
+__device__ __forceinline__ void PpBwdTile::run(const GemmParams& P, const int m0, const int n0, int,
+                                               char* L) {
   using C = PpBwdTile;
-  __shared__ __attribute__((aligned(1024))) char L[LDS_BYTES];
   lds_char* Ls = (lds_char*)L;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int tiles_n = (P.N + BN - 1) / BN;
-  int tm, tn;
-  tile_coords(w, (P.M + BM - 1) / BM, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN, nk = P.K / BK;
+  const int nk = P.K / BK;
 
   enum { X = 0, Y = 1, W1 = 2, W3 = 3, W2 = 4 };
   // Load i (of two) of a unit: LDS rows 8 (8 i + wave) + lane / 8.
@@ -1128,7 +1125,10 @@ template <class K>
 __global__ __launch_bounds__(K::THREADS) void gemm_kernel(const GemmParams P) {
   const int tiles = ((P.M + K::BM - 1) / K::BM) * ((P.N + K::BN - 1) / K::BN);
   const int items = K::EPI == EPI_ACC && P.k_splits > 1 ? tiles * P.k_splits : tiles;
-  K::run(P, xcd_work_index(blockIdx.x, items));
+  __shared__ __attribute__((aligned(1024))) char L[K::LDS_BYTES];
+  int m0, n0, split;
+  work_tile<K>(P, xcd_work_index(blockIdx.x, items), &m0, &n0, &split);
+  K::run(P, m0, n0, split, L);
 }
 
 // Y = base + sum of the k_splits partial products in range order (base and U as in the
@@ -1164,21 +1164,60 @@ struct GemmGroup {
   int n;
 };
 static_assert(sizeof(GemmGroup) <= 4096, "kernel argument size limit");
+// Tiles of K in each product of G; returns their total.
 template <class K>
-__global__ __launch_bounds__(K::THREADS) void gemm_group_kernel(const GemmGroup G) {
-  int tiles[kGemmGroupMax], total = 0;
+__device__ __forceinline__ int group_tiles(const GemmGroup& G, int (&tiles)[kGemmGroupMax]) {
+  int total = 0;
 #pragma unroll
   for (int i = 0; i < kGemmGroupMax; ++i) {
     tiles[i] = i < G.n ? ((G.p[i].M + K::BM - 1) / K::BM) * ((G.p[i].N + K::BN - 1) / K::BN) : 0;
     total += tiles[i];
   }
+  return total;
+}
+
+template <class K>
+__global__ __launch_bounds__(K::THREADS) void gemm_group_kernel(const GemmGroup G) {
+  __shared__ __attribute__((aligned(1024))) char L[K::LDS_BYTES];
+  int tiles[kGemmGroupMax];
+  const int total = group_tiles<K>(G, tiles);
   int w = xcd_work_index(blockIdx.x, total), i = 0;
   while (i + 1 < G.n && w >= tiles[i]) w -= tiles[i++];  // uniform per workgroup
   // A copy of the product's parameters: read through G.p[i] (an index into the kernel
   // arguments), the compiler reloads every field after each global store of the epilogue
   // (it cannot rule out aliasing), hundreds of serialized scalar loads per tile.
   const GemmParams P = G.p[i];
-  K::run(P, w);
+  int m0, n0, split;
+  work_tile<K>(P, w, &m0, &n0, &split);
+  K::run(P, m0, n0, split, L);
+}
+
+// The same with the tiles from n_big on cut in two row halves of Small tiles, which follow the
+// others in dispatch order: the last, partly filled round of the chip then costs a round of
+// the smaller tiles.
+template <class Big, class Small>
+__global__ __launch_bounds__(Big::THREADS) void gemm_mixed_group_kernel(const GemmGroup G,
+                                                                        const int n_big) {
+  static_assert(Big::THREADS == Small::THREADS && Big::BM == 2 * Small::BM &&
+                    Big::BN == Small::BN, "halves");
+  constexpr int kLds = Big::LDS_BYTES > Small::LDS_BYTES ? Big::LDS_BYTES : Small::LDS_BYTES;
+  __shared__ __attribute__((aligned(1024))) char L[kLds];
+  int tiles[kGemmGroupMax];
+  const int total = group_tiles<Big>(G, tiles);
+  const int b = blockIdx.x;
+  const bool big = b < n_big;
+  const int q = big ? 0 : xcd_work_index(b - n_big, 2 * (total - n_big));
+  int w = big ? xcd_work_index(b, n_big) : n_big + (q >> 1), i = 0;
+  while (i + 1 < G.n && w >= tiles[i]) w -= tiles[i++];
+  const GemmParams P = G.p[i];
+  int m0, n0, split;
+  work_tile<Big>(P, w, &m0, &n0, &split);
+  if (big) {
+    Big::run(P, m0, n0, split, L);
+    return;
+  }
+  m0 += (q & 1) * Small::BM;
+  if (m0 < P.M) Small::run(P, m0, n0, split, L);
 }
 
 template <class K>
@@ -1219,6 +1258,26 @@ hipError_t launch_group(const GemmParams* ps, int n, hipStream_t s) {
   void* args[] = {&g};
   return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_group_kernel<K>),
                          dim3((unsigned)total), dim3(K::THREADS), args, 0, s);
+}
+
+// n_big tiles of Big, the rest halved (gemm_mixed_group_kernel); n products with M, N > 0.
+template <class Big, class Small>
+hipError_t launch_mixed_group(const GemmParams* ps, int n, long long total, long long n_big,
+                              hipStream_t s) {
+  if (n < 1 || n > kGemmGroupMax) return hipErrorInvalidValue;
+  GemmGroup g = {};
+  for (int i = 0; i < n; ++i) {
+    if (ps[i].M <= 0 || ps[i].N <= 0) return hipErrorInvalidValue;
+    const hipError_t e = check_params<Big>(ps[i]);
+    if (e != hipSuccess) return e;
+    g.p[i] = ps[i];
+  }
+  g.n = n;
+  int nb = (int)n_big;
+  void* args[] = {&g, &nb};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_mixed_group_kernel<Big, Small>),
+                         dim3((unsigned)(n_big + 2 * (total - n_big))), dim3(Big::THREADS), args,
+                         0, s);
 }
 
 template <class K>
@@ -1269,6 +1328,13 @@ hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s) 
   const long long big = tiles_of(ps, n, 256, 128), t128 = tiles_of(ps, n, 128, 128);
   if (t128 <= kSmallTiles)
     return launch_group<Tile<64, 64, 2, 2, false, EPI_SWIGLU, 3>>(ps, n, s);
+  // Whole rounds of the alternating tiles with the last, partial one on halved tiles, when
+  // that makes one round (7B, S_loc = 1024: 352 tiles, 176 -> 157 us; 700: 264 tiles, 179 -> 156).
+  const long long full = big / kCus, rest = big - full * kCus;
+  if (full > 0 && rest > 0 && 2 * rest <= kCus &&
+      155 * full + 100 < std::min(155 * rounds(big), 100 * rounds(t128)))
+    return launch_mixed_group<PpTile<false, EPI_SWIGLU>,
+                              Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, big, full * kCus, s);
   if (155 * rounds(big) <= 100 * rounds(t128))
     return launch_group<PpTile<false, EPI_SWIGLU>>(ps, n, s);
   return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, s);

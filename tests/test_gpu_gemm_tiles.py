@@ -30,12 +30,14 @@ def _rel(got, ref):
 # 2, 3 and 5 stages; down projections in them (>= 256 tiles of 256 x 256) with 1, 2, 3, 4 (200
 # columns padded to 256) stages.  Small products: gate+up and down on 64 x 64 tiles with 1, 2
 # and 5 or more stages; down split into ranges on 64 x 64 (96 rows, 65 steps) and 128 x 128
-# tiles (300 rows); down on 128 x 128 tiles with a four-stage ring (1100 rows).
+# tiles (300 rows); down on 128 x 128 tiles with a four-stage ring (1100 rows).  Gate+up with
+# a last round of halved tiles (289 tiles), whose last half row tile has 2 rows or none.
 @pytest.mark.parametrize("m,h,f", [(16387, 64, 2056), (16387, 128, 2056), (16387, 192, 2056),
                                    (16387, 320, 2056), (16387, 1024, 64), (16387, 1024, 128),
                                    (16387, 1024, 192), (16387, 1024, 200), (1, 64, 8),
                                    (130, 64, 72), (63, 320, 648), (65, 128, 136),
-                                   (96, 1024, 4104), (300, 2048, 4096), (1100, 2048, 512)])
+                                   (96, 1024, 4104), (300, 2048, 4096), (1100, 2048, 512),
+                                   (4226, 128, 2056), (4200, 320, 2056)])
 def test_mlp_tiles(m, h, f):
     print(f"[mlp tiles] {m} x {h} x {f}", flush=True)
     sh = T.make_shape(1, m, h, f, h // 64, h // 64, 64, 1, 0)
