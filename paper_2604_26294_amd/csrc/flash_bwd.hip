@@ -776,10 +776,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_combine_kernel(const AttnBwdP
 
 // ---------------------------------------------------------------------------------
 // out[n][m] = in[m][n] for m < rows, n < cols; out[n][m] = 0 for rows <= m < ld_out.
-// 64 x 64 tiles through LDS; 16-byte loads and stores.
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* in, int ld_in,
-                                                             int rows, int cols, uint16_t* out,
-                                                             int ld_out) {
+// 64 x 64 tiles through LDS; 16-byte loads and stores.  Grid layer z takes matrix z of two.
+__global__ __launch_bounds__(256) void transpose2_bf16_kernel(const uint16_t* in0, int ld0,
+                                                              uint16_t* out0, const uint16_t* in1,
+                                                              int ld1, uint16_t* out1, int rows,
+                                                              int cols, int ld_out) {
+  const uint16_t* in = blockIdx.z == 0 ? in0 : in1;
+  uint16_t* out = blockIdx.z == 0 ? out0 : out1;
+  const int ld_in = blockIdx.z == 0 ? ld0 : ld1;
   __shared__ uint16_t T[64][64 + 2];
   const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
   const int tid = threadIdx.x;
@@ -933,13 +937,15 @@ int attn_bwd_dq_split(const AttnBwdParams& p, int* split_len) {
   return n;
 }
 
-hipError_t launch_transpose_bf16(const uint16_t* in, int ld_in, int rows, int cols,
-                                 uint16_t* out, int ld_out, hipStream_t s) {
+hipError_t launch_transpose2_bf16(const uint16_t* in0, int ld0, uint16_t* out0,
+                                  const uint16_t* in1, int ld1, uint16_t* out1, int rows,
+                                  int cols, int ld_out, hipStream_t s) {
   if (rows < 0 || cols <= 0 || ld_out < rows || ld_out % 8 != 0) return hipErrorInvalidValue;
   if (ld_out == 0) return hipSuccess;
-  const dim3 grid((ld_out + 63) / 64, (cols + 63) / 64);
-  void* args[] = {const_cast<uint16_t**>(&in), &ld_in, &rows, &cols, &out, &ld_out};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&transpose_bf16_kernel), grid, dim3(256),
+  const dim3 grid((ld_out + 63) / 64, (cols + 63) / 64, 2);
+  void* args[] = {const_cast<uint16_t**>(&in0), &ld0, &out0, const_cast<uint16_t**>(&in1), &ld1,
+                  &out1, &rows, &cols, &ld_out};
+  return hipLaunchKernel(reinterpret_cast<const void*>(&transpose2_bf16_kernel), grid, dim3(256),
                          args, 0, s);
 }
 

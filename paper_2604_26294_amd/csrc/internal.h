@@ -256,9 +256,10 @@ hipError_t launch_attn_bwd_prep(const AttnBwdParams& p, hipStream_t s);
 hipError_t launch_attn_bwd_dkdv(const AttnBwdParams& p, hipStream_t s);
 hipError_t launch_attn_bwd_dq(const AttnBwdParams& p, hipStream_t s);
 
-// out[n][m] = in[m][n] (bf16) for m < rows, n < cols, and 0 for rows <= m < ld_out
-// (ld_out a multiple of 8; in rows 16-byte aligned).
-hipError_t launch_transpose_bf16(const uint16_t* in, int ld_in, int rows, int cols,
-                                 uint16_t* out, int ld_out, hipStream_t s);
+// out[n][m] = in[m][n] (bf16) for m < rows, n < cols, and 0 for rows <= m < ld_out (ld_out a
+// multiple of 8; rows of in 16-byte aligned), of two matrices of one size in one launch.
+hipError_t launch_transpose2_bf16(const uint16_t* in0, int ld0, uint16_t* out0,
+                                  const uint16_t* in1, int ld1, uint16_t* out1, int rows,
+                                  int cols, int ld_out, hipStream_t s);
 
 }  // namespace tsp

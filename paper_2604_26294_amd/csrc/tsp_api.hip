@@ -787,14 +787,16 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
   for (int r0 = 0; r0 < d.D; r0 += group) {
     const int n = d.D - r0 < group ? d.D - r0 : group;
     const int ld = n * qd;  // token row of the group's Q, A, dA and dQ
-    GemmParams g[tsp::kGemmGroupMax] = {};
-    // Q times scale * log2(e), as the attention kernels take it
-    for (int i = 0; i < n; ++i)
+    // The group's products of two kinds, n each: one launch when it holds them all.
+    GemmParams g[2 * tsp::kGemmGroupMax] = {};
+    const int per_launch = 2 * n <= tsp::kGemmGroupMax ? 2 * n : n;
+    for (int i = 0; i < n; ++i) {
+      // Q times scale * log2(e), as the attention kernels take it, and dA = dY W_O^(r)
       g[i] = nt_params(d, x, wa[r0 + i], qd, q_ws + (size_t)i * qd, ld, d.scale * kLog2e);
-    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv_group(g, n, st));
-    for (int i = 0; i < n; ++i)  // dA = dY W_O^(r)
-      g[i] = nt_params(d, dy, wa[r0 + i] + wo, qd, da_ws + (size_t)i * qd, ld, 1.f);
-    TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv_group(g, n, st));
+      g[n + i] = nt_params(d, dy, wa[r0 + i] + wo, qd, da_ws + (size_t)i * qd, ld, 1.f);
+    }
+    for (int i = 0; i < 2 * n; i += per_launch)
+      TSP_LAUNCH(TSP_KERNEL_ABWD_PROJ, st, tsp::launch_gemm_qkv_group(g + i, per_launch, st));
 
     // A and the log-sum-exp: the forward's, kept by tsp_attn_rank_fwd_train (the group's
     // columns of [M, n_h d] and rows of [B, n_h, S_loc]), or recomputed into the workspace
@@ -867,15 +869,15 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
 
     // W_Q blocks (+)= dQ^T X;  W_O^T blocks (+)= A^T dY: [H_s d, M] x [M, h] per shard.
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-               tsp::launch_transpose_bf16(dq_ws, ld, (int)d.M, ld, dqt_ws, w.m_pad, st));
-    TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-               tsp::launch_transpose_bf16(a_src, a_ld, (int)d.M, ld, at_ws, w.m_pad, st));
-    for (int k = 0; k < 2; ++k) {
-      for (int i = 0; i < n; ++i)
-        g[i] = dw_params(d, (k == 0 ? dqt_ws : at_ws) + (size_t)i * qd * w.m_pad, w.m_pad,
-                         k == 0 ? x : dy, qd, dw[r0 + i] + (k == 0 ? (size_t)0 : wo), accumulate);
-      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(g, n, st));
+               tsp::launch_transpose2_bf16(dq_ws, ld, dqt_ws, a_src, a_ld, at_ws, (int)d.M, ld,
+                                           w.m_pad, st));
+    for (int i = 0; i < n; ++i) {
+      const size_t at = (size_t)i * qd * w.m_pad;
+      g[i] = dw_params(d, dqt_ws + at, w.m_pad, x, qd, dw[r0 + i], accumulate);
+      g[n + i] = dw_params(d, at_ws + at, w.m_pad, dy, qd, dw[r0 + i] + wo, accumulate);
     }
+    for (int i = 0; i < 2 * n; i += per_launch)
+      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(g + i, per_launch, st));
   }
   return TSP_OK;
 }
@@ -916,9 +918,9 @@ tsp_status run_attn_kv_bwd(const Dims& d, const uint16_t* x, const uint16_t* con
                tsp::launch_gemm_nn_acc(p, reinterpret_cast<float*>(ws + w.part), st));
   }
   // W_K blocks (+)= dK^T X;  W_V blocks (+)= dV^T X: [K_s d, M] x [M, h] per shard.
-  for (int k = 0; k < 2; ++k)
-    TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-               tsp::launch_transpose_bf16(grad[k], ld, (int)d.M, ld, tr[k], w.m_pad, st));
+  TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
+             tsp::launch_transpose2_bf16(grad[0], ld, tr[0], grad[1], ld, tr[1], (int)d.M, ld,
+                                         w.m_pad, st));
   GemmParams q[tsp::kGemmGroupMax] = {};
   int n = 0;
   for (int i = 0; i < 2 * d.D; ++i) {
