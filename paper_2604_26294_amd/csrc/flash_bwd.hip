@@ -69,13 +69,16 @@ struct BwCfg {
   static constexpr int RPD = kWave / KCH;       // rows one wave-wide LDS load fills
   static constexpr int DMA64 = 64 / (kBwdWaves * RPD);  // such loads per wave per tile
   static_assert(DMA64 * kBwdWaves * RPD == 64, "tile cover");
-  // m = row / RPW indexes the row's bank window.  d = 128 (one row per window): f = 2 (m mod
-  // 8) + (m / 8 mod 2), distinct over 16 consecutive rows, and in its upper three bits over 8
-  // aligned ones.  d = 64 (two rows per window, at chunk offsets 0 and 8): f = 2 (m mod 4) +
-  // (m / 4 mod 2), distinct over 8 consecutive windows, and in its upper two bits over 4.
+  // m = row / RPW indexes the row's bank window, bits m3 m2 m1 m0.  d = 128 (one row per
+  // window): f = bits m0, m1, m2 ^ m3, m3; d = 64 (two rows per window, at chunk offsets 0 and
+  // 8): f = bits m0, m1 ^ m2, m2.  Transpose reads need f distinct above its lowest bit over 8
+  // aligned rows; row reads need it distinct over 16 rows and, as a 16-byte read takes its
+  // lanes in the sets 0-3, 12-15 of one 16-lane group with 4-11 of the next (whose logical
+  // chunk differs in bit 0), rows r and r ^ 12 to differ in exactly that bit.
   __device__ static int f(int row) {
     const int m = row / RPW;
-    return D == 128 ? (((m & 7) << 1) | ((m >> 3) & 1)) : (((m & 3) << 1) | ((m >> 2) & 1));
+    return D == 128 ? (((m & 1) << 3) | ((m & 2) << 1) | (((m >> 1) ^ (m >> 2)) & 2) | ((m >> 3) & 1))
+                    : (((m & 1) << 2) | ((m ^ (m >> 1)) & 2) | ((m >> 2) & 1));
   }
   // Byte offset of (row, column) in a tile (column a multiple of 4 for transpose reads).
   __device__ static int off(int row, int col) {
