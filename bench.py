@@ -72,8 +72,7 @@ def log(msg):
 def kernel_flops(wl):
     """Algorithmic FLOPs of each kernel class (TSP_KERNEL_* order) over one call of the
     entry point that launches it (all D shard steps), whatever the number of launches:
-    the forward's products of one group of steps share a launch, and so do the two dX
-    products of one MLP backward step."""
+    the products of one group of steps share a launch."""
     from paper_2604_26294_amd.flops import step_attn_core_flops
     D = wl.degree
     m = wl.batch * wl.s_loc

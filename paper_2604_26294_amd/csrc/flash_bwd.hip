@@ -189,8 +189,10 @@ __device__ __forceinline__ void bwd_wait_ge(lds_int* p, int target, lds_int* fla
 // Bound by instruction issue and, on real data, by power (11.6 ms on zeros where random data
 // takes 13.9).  7B, S = 65536, rank 7, 32 heads in one launch: 14.7 ms with 32 x 32 x 16 MFMAs,
 // 15.0 with 16 x 16 x 32 and a scheduling barrier after each operand group (which the other
-// shape needed to fit its registers), 14.2 without the barriers; S = 8192: 414 -> 292 us (its
-// 64-byte instead of 32-byte segments of dK / dV rows per store count there).
+// shape needed to fit its registers), 14.2 without the barriers, and 13.5 -> 12.95 (one card in
+// turn) with the swizzle f above, whose row reads have no bank conflicts (1.2e10 -> 3e7 conflict
+// cycles over 8 launches); S = 8192: 414 -> 292 -> 283 us (the 64-byte instead of 32-byte
+// segments of dK / dV rows per store count there).
 template <int D>
 __global__ __launch_bounds__(kKvThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bwd_dkdv_kernel(const AttnBwdParams P) {
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_combine_kernel(const AttnBw
 // sums; with n_split = 1 the workgroup writes bf16 dQ itself.  The K / V tiles go round
 // a two-slot ring, unrolled by slot so that LDS addresses are registers plus
 // immediates.  Bound by power on real data (7B, S = 65536, rank 7: 7.0 ms on zeros); 16 x 16 x
-// 32 MFMAs took it from 9.85 to 9.4 ms.
+// 32 MFMAs took it from 9.85 to 9.4 ms, the conflict-free swizzle f from 9.32 to 9.19.
 template <int D>
 __global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bwd_dq_kernel(const AttnBwdParams P) {
