@@ -169,7 +169,8 @@ int attn_full_len(const AttnParams& ap) {
 // several rounds drifts out of step, as the query tiles' key counts differ, and re-reads
 // K/V).  Pairing (tile i with tile n_qt - 1 - i: equal work per workgroup) halves the
 // work items; whichever plan the dispatch simulation of the attention launches
-// (tsp::attn_launch_seconds) prices lower for the whole group is taken.
+// (tsp::attn_launch_seconds) prices lower for the whole group is taken, paired tiles also over
+// more shards than fill the GPU once.
 struct AttnLaunchPlan {
   int width;
   bool pair;
@@ -197,7 +198,24 @@ AttnLaunchPlan attn_launch_plan(const Dims& d, int n) {
   const AttnLaunchPlan plain = {width_for(tiles * d.hs * d.B), false};
   if (tiles < 2) return plain;
   const AttnLaunchPlan paired = {width_for((tiles + 1) / 2 * d.hs * d.B), true};
-  return group_seconds(paired.width, true) < group_seconds(plain.width, false) ? paired : plain;
+  const double sec_paired = group_seconds(paired.width, true);
+  const double sec_plain = group_seconds(plain.width, false);
+  AttnLaunchPlan best = sec_paired < sec_plain ? paired : plain;
+  double sec = std::min(sec_paired, sec_plain);
+  // Paired items are all of one length, so launches over more shards keep their rounds in step
+  // and waste less of the last one (13B, 4 shards of 320 items: 2 rounds each, 5 together; the
+  // key ranges they replace: attention of rank 3 4.22 -> 3.84 ms, zigzag rank 0 2.92 -> 2.24,
+  // rank 3 2.64 -> 2.24; unpaired over 4 shards 3.87, 2.35, 2.30).  Where the rounds come out
+  // whole already a wider launch gains nothing (7B, S = 65536: 3.40 and 3.38 ms), so the
+  // fewest shards stay unless the simulation saves more than 1 %.
+  for (int w = paired.width + 1; w <= n; ++w) {
+    const double t = group_seconds(w, true);
+    if (t < 0.99 * sec) {
+      sec = t;
+      best = {w, true};
+    }
+  }
+  return best;
 }
 // (range, token, head) rows of the key-range partials of the launches of a group of n shards
 // (launches of attn_launch_plan's width, and a remainder); 0 without key ranges.

@@ -34,6 +34,9 @@ MLP_LONG = Workload("mlp-long-d6", 1, 24960, 384, 432, 6, 6, 64, 6, 2, w_std=0.0
 # launch plan pairs query tiles (5 tiles: pairs (0, 4), (1, 3) and tile 2 alone; in the
 # zigzag layout 6 tiles, pairs across the two segments); GQA g = 2.
 SUBL = Workload("sub-launch-b10", 10, 5120, 512, 1024, 8, 4, 64, 4, 2, w_std=0.05)
+# 2 heads x 44 entries, 3 (contiguous) or 4 (zigzag) query tiles each, per shard: paired launches
+# of two shards leave their last round mostly idle, one of all four does not
+WIDE = Workload("wide-launch-b44", 44, 2560, 512, 1024, 8, 4, 64, 4, 2, w_std=0.05)
 # the gate+up product of a group of 8 shards in 256 x 128 tiles (at least 4 rounds on 256
 # CUs: 16 x 8 x 8 = 1024 tiles) with a ragged F/D = 1000
 MLP_BIG = Workload("mlp-big-fd1000", 1, 32768, 512, 8000, 8, 8, 64, 8, 7, w_std=0.04)

@@ -11,9 +11,10 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+from paper_2604_26294_amd import tsp as T  # noqa: E402
 from paper_2604_26294_amd.harness import RankProblem  # noqa: E402
-from tests.gpu_common import (DEG16, MID_GQA64, MID_MHA128, ODD3, SUBL, assert_close,  # noqa: E402
-                              gen, oracle_blocks)
+from tests.gpu_common import (DEG16, MID_GQA64, MID_MHA128, ODD3, SUBL, WIDE,  # noqa: E402
+                              assert_close, gen, oracle_blocks)
 
 # (workload, rank, group_steps values); 0 is the library default, min(D, 8)
 CASES = [(MID_GQA64, 3, (1, 2, 3)), (MID_GQA64.with_layout(1), 1, (1, 3)),
@@ -62,7 +63,7 @@ def test_attention_with_paired_query_tiles(wl, p, block):
     """A group's attention with two query tiles per workgroup (the i-th most and the i-th
     fewest keys), as the launch plan takes it for shapes with many work items per shard;
     launches over part of a group's shards (heads' columns inside group-wide Q and A rows)
-    are covered at full size (7B S=65536, 70B: 4 of 8 shards per launch; 13B: 1 of 4)."""
+    are covered at full size (7B S=65536, 70B: 4 of 8 shards per launch)."""
     print(f"[grouping] {wl.name} {wl.layout_name} rank {p} {block}", flush=True)
     x_bits, w_bits = _inputs(wl)
     prob = RankProblem(wl, x_bits, w_bits, p)
@@ -71,3 +72,28 @@ def test_attention_with_paired_query_tiles(wl, p, block):
     torch.cuda.synchronize()
     ref = oracle_blocks(wl, x_bits, w_bits, p, blocks=(block,))[block]
     assert_close(y.double().cpu().numpy(), ref, f"{wl.name} r{p} {block}")
+
+
+@pytest.mark.parametrize("wl,p", [(WIDE, 2), (WIDE.with_layout(1), 1)],
+                         ids=["contiguous-r2", "zigzag-r1"])
+def test_paired_launch_over_more_shards_than_fill_the_gpu(wl, p):
+    """One paired launch over all four shards where two already fill every CU, because its
+    rounds waste less of the last one; against the oracle, and every shard for itself."""
+    print(f"[grouping] {wl.name} {wl.layout_name} rank {p}", flush=True)
+    x_bits, w_bits = _inputs(wl)
+    outs = []
+    for steps in (0, 1):
+        prob = RankProblem(wl, x_bits, w_bits, p, group_steps=steps)
+        prob.prefill_kv()
+        T.tsp_profile_enable(True)
+        try:
+            y = prob.attn_fwd()
+            torch.cuda.synchronize()
+            launches = T.tsp_profile_read(T.KERNELS.index("attn"))[1]
+        finally:
+            T.tsp_profile_enable(False)
+        assert launches == (4 if steps else 1)
+        outs.append(y.double().cpu().numpy())
+    assert_close(outs[0], oracle_blocks(wl, x_bits, w_bits, p, blocks=("attn",))["attn"],
+                 f"{wl.name} r{p}")
+    assert np.max(np.abs(outs[0] - outs[1])) <= 1e-2 * np.max(np.abs(outs[1]))
