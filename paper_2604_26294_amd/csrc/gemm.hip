@@ -672,7 +672,8 @@ __device__ __forceinline__ void swap_slot() {
 // per SIMD): X MEM(Q0) | X MFMA(Q0), Y MEM(Q0) | X MEM(Q1), Y MFMA(Q0) | ...  A unit read
 // in X's slot t and Y's slot t + 1 is in registers by the barrier that ends slot t + 2 (both
 // wait for their LDS reads before their MFMAs), and its refill is issued in slot t + 4 at
-// the earliest.  A unit read in slot t (X) was waited for by every wavefront in its MEM
+// the earliest.  B0 of the first step, read before slot 0 by both and refilled in slot 2, has a
+// wait of its own in Y.  A unit read in slot t (X) was waited for by every wavefront in its MEM
 // slot before, i.e. ahead of the barrier that ends slot t - 1: five units are issued after
 // it by then, two loads each per wavefront, hence vmcnt(10).
 // MULTI: the contraction may have several parts or be split into ranges ([K, N] operands,
@@ -941,7 +942,12 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
   }
   swap_slot();  // B0 and A0 of step 0 resident
   read_b(s0, s0);
-  if (wave >= 4) swap_slot();  // Y runs one slot behind X
+  if (wave >= 4) {
+    // Y runs one slot behind X, so its first MFMA slot's wait for LDS reads lies behind two
+    // barriers, and X refills B0 right after the second.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    swap_slot();
+  }
   for (int left = nk; left > 0; left -= 2) {
     step(s0, left);
     if (left > 1) step(s1, left - 1);
