@@ -782,94 +782,178 @@ long long dispatch_makespan(long long total, Cost cost) {
   return worst;
 }
 
-// The launch plan of a shape: key ranges (and their length) without pairing, and the
-// estimated seconds of that plan and of paired tiles without ranges.
-struct AttnPlan {
-  int n_split, split_len;
-  double sec_split, sec_pair;
+constexpr long long kPieceCost = kStepKeys;      // setup and output write: ~one step
+constexpr long long kEmptyCost = kStepKeys / 8;  // a workgroup with no keys to visit
+
+// Keys of each query tile of one head, in the kernel's order (last segment first, last tile
+// first).
+struct QueryTiles {
+  static constexpr int kMax = 1024;  // (longer shards are not planned: one range, unpaired)
+  int keys[kMax];
+  int n = 0, max_keys = 1;
+  explicit QueryTiles(const AttnParams& p) {
+    for (int k = p.n_seg - 1; k >= 0; --k) {
+      const int nt = (p.seg_rows[k] + kQTile - 1) / kQTile;
+      for (int t = nt - 1; t >= 0; --t) {
+        const int seen = p.seg_pos0[k] + min((t + 1) * kQTile, p.seg_rows[k]);
+        if (n < kMax) keys[n] = seen;
+        ++n;
+        max_keys = max(max_keys, seen);
+      }
+    }
+  }
+  // Length of n ranges over every key.
+  int range_len(int ranges) const {
+    const int len = (max_keys + ranges - 1) / ranges;
+    return (len + kStepKeys - 1) / kStepKeys * kStepKeys;
+  }
 };
 
-AttnPlan attn_plan_uncached(const AttnParams& p) {
-  constexpr long long kPieceCost = kStepKeys;      // setup and output write: ~one step
-  constexpr long long kEmptyCost = kStepKeys / 8;  // a workgroup with no keys to visit
-  // Keys of each query tile, in the kernel's order (last segment first, last tile first).
-  constexpr int kMaxTiles = 1024;
-  int tile_keys[kMaxTiles];
-  int n_qt = 0, max_keys = 1;
-  for (int k = p.n_seg - 1; k >= 0; --k) {
-    const int nt = (p.seg_rows[k] + kQTile - 1) / kQTile;
-    for (int t = nt - 1; t >= 0; --t) {
-      const int keys = p.seg_pos0[k] + min((t + 1) * kQTile, p.seg_rows[k]);
-      if (n_qt < kMaxTiles) tile_keys[n_qt] = keys;
-      ++n_qt;
-      max_keys = max(max_keys, keys);
-    }
-  }
-  auto len_of = [&](int n) {
-    const int len = (max_keys + n - 1) / n;
-    return (len + kStepKeys - 1) / kStepKeys * kStepKeys;
-  };
-  const long long bh = (long long)p.batch * p.heads;
-  AttnPlan plan = {1, len_of(1), 0.0, 0.0};
-  if (bh <= 0 || n_qt > kMaxTiles) return plan;
-  // Time per key of a workgroup: 4 kQTile d FLOPs (its Q K^T and P V rows) at the
-  // fraction of one CU's bf16 MFMA peak (2516.6 / 256 TFLOP/s) this kernel reaches (0.50
-  // measured at 7B, S = 65536: ~27 ns per key at d = 128).  Key-range partials move at
-  // about half the HBM peak (8 TB/s).  Only the ratio of the two matters; the fraction is
-  // refitted to the measured one whenever the kernel's speed changes.
-  constexpr double kCuPeak = 2516.6e12 / 256, kPeakFraction = 0.50, kPartialBw = 4e12;
-  const double t_key = 4.0 * kQTile * p.head_dim / (kPeakFraction * kCuPeak);
-  const double rows = (double)bh * p.s_loc;
-  // Key ranges: candidate counts 1..8, at least 4 key tiles per range; estimated time =
-  // simulated makespan x t_key + the partials' traffic (written, read back, merged); the
-  // smallest wins, ties going to fewer ranges.
-  double best = -1.0;
-  for (int n = 1; n <= 8; ++n) {
-    const int len = len_of(n);
-    if (n > 1 && len < 4 * kStepKeys) break;
-    if ((max_keys + len - 1) / len != n) continue;  // same ranges as a smaller n
-    const double traffic =
-        n > 1 ? (2.0 * n * rows * (p.head_dim + 2) * 4 + rows * p.head_dim * 2) / kPartialBw : 0.0;
-    const long long span = dispatch_makespan(bh * n_qt * n, [&](long long w) {
-      const int t = (int)(w % n_qt), split = (int)((w / n_qt) % n);
-      const long long keys =
-          min(max((long long)tile_keys[t] - (long long)split * len, 0LL), (long long)len);
-      return keys > 0 ? keys + kPieceCost : kEmptyCost;
-    });
-    const double sec = span * t_key + traffic;
-    if (best < 0 || sec < best) {
-      best = sec;
-      plan.n_split = n;
-      plan.split_len = len;
-    }
-  }
-  plan.sec_split = best;
-  // Paired tiles: item i takes tiles i and n_qt - 1 - i (one tile if they coincide).
-  const int n_items = (n_qt + 1) / 2;
-  const long long span = dispatch_makespan(bh * n_items, [&](long long w) {
-    const int i = (int)(w % n_items), j = n_qt - 1 - i;
-    return tile_keys[i] + kPieceCost + (j != i ? tile_keys[j] + kPieceCost : 0LL);
-  });
-  plan.sec_pair = span * t_key;
-  return plan;
+// Time per key of a workgroup: 4 kQTile d FLOPs (its Q K^T and P V rows) at the
+// fraction of one CU's bf16 MFMA peak (2516.6 / 256 TFLOP/s) this kernel reaches (0.50
+// measured at 7B, S = 65536: ~27 ns per key at d = 128).  Key-range partials move at
+// about half the HBM peak (8 TB/s).  Only the ratio of the two matters; the fraction is
+// refitted to the measured one whenever the kernel's speed changes.
+constexpr double kCuPeak = 2516.6e12 / 256, kPeakFraction = 0.50, kPartialBw = 4e12;
+double key_seconds(const AttnParams& p) {
+  return 4.0 * kQTile * p.head_dim / (kPeakFraction * kCuPeak);
+}
+// No dispatch of items of this total cost ends earlier.
+double least_seconds(const AttnParams& p, double total) {
+  return total / kAttnTargetWorkgroups * key_seconds(p);
 }
 
-// Shapes already planned (the plan depends on these fields only); callers ask for the
-// same shape several times per entry point call.
+// Key ranges of one launch over `heads` heads: candidate counts 1..8, at least 4 key tiles
+// per range; estimated time = simulated makespan x time per key + the partials' traffic
+// (written, read back, merged); the smallest wins, ties going to fewer ranges.  (A candidate
+// whose work, spread evenly, takes as long as the best so far is not simulated.)
+struct KeyRanges {
+  int n, len;
+  double sec;
+};
+KeyRanges best_key_ranges(const AttnParams& p, const QueryTiles& q, int heads) {
+  const long long bh = (long long)p.batch * heads;
+  KeyRanges best = {1, q.range_len(1), -1.0};
+  if (bh <= 0 || q.n > QueryTiles::kMax) return {best.n, best.len, 0.0};
+  const double rows = (double)bh * p.s_loc;
+  for (int n = 1; n <= 8; ++n) {
+    const int len = q.range_len(n);
+    if (n > 1 && len < 4 * kStepKeys) break;
+    if ((q.max_keys + len - 1) / len != n) continue;  // same ranges as a smaller n
+    const double traffic =
+        n > 1 ? (2.0 * n * rows * (p.head_dim + 2) * 4 + rows * p.head_dim * 2) / kPartialBw : 0.0;
+    auto item_cost = [&](int t, int split) {
+      const long long keys =
+          min(max((long long)q.keys[t] - (long long)split * len, 0LL), (long long)len);
+      return keys > 0 ? keys + kPieceCost : kEmptyCost;
+    };
+    if (best.sec >= 0) {
+      double total = 0.0;
+      for (int t = 0; t < q.n; ++t)
+        for (int c = 0; c < n; ++c) total += item_cost(t, c);
+      if (least_seconds(p, total * bh) + traffic >= best.sec) continue;
+    }
+    const long long span = dispatch_makespan(bh * q.n * n, [&](long long w) {
+      return item_cost((int)(w % q.n), (int)((w / q.n) % n));
+    });
+    const double sec = span * key_seconds(p) + traffic;
+    if (best.sec < 0 || sec < best.sec) best = {n, len, sec};
+  }
+  return best;
+}
+
+// Paired tiles: item i takes tiles i and n - 1 - i (one tile if they coincide).
+long long pair_cost(const QueryTiles& q, int i) {
+  const int j = q.n - 1 - i;
+  return q.keys[i] + kPieceCost + (j != i ? q.keys[j] + kPieceCost : 0LL);
+}
+
+// Estimated seconds of the n shards' attention in paired launches over `width` shards each.
+double paired_seconds(const AttnParams& p, const QueryTiles& q, int n, int width) {
+  const int items = (q.n + 1) / 2;
+  auto launch = [&](int shards) {
+    const long long bh = (long long)p.batch * p.heads * shards;
+    return dispatch_makespan(bh * items, [&](long long w) { return pair_cost(q, (int)(w % items)); }) *
+           key_seconds(p);
+  };
+  const int whole = n / width, rest = n % width;
+  return whole * launch(width) + (rest ? launch(rest) : 0.0);
+}
+
+// A launch takes the fewest shards whose work items fill the GPU once: the workgroups on an XCD
+// then start together and stream the same keys of the same head through its L2 (a launch of
+// several rounds drifts out of step, as the query tiles' key counts differ, and re-reads
+// K/V).  Pairing (tile i with tile n_qt - 1 - i: equal work per workgroup) halves the
+// work items; whichever plan the dispatch simulation prices lower for the whole group is taken,
+// paired tiles also over more shards than fill the GPU once.
+AttnLaunchPlan plan_launches(const AttnParams& p, int n) {
+  const QueryTiles q(p);
+  auto width_for = [&](long long items_per_shard) {
+    if (items_per_shard <= 0) return n;
+    const long long need = (kAttnTargetWorkgroups + items_per_shard - 1) / items_per_shard;
+    return (int)(need < n ? need : n);
+  };
+  const long long bh = (long long)p.batch * p.heads;
+  AttnLaunchPlan plain = {width_for(q.n * bh), false, {1, 1}, {q.range_len(1), q.range_len(1)}};
+  double sec_plain = 0.0;
+  for (int k = 0; k < 2; ++k) {
+    const int w = k == 0 ? plain.width : n % plain.width;
+    if (w == 0) continue;
+    const KeyRanges r = best_key_ranges(p, q, w * p.heads);
+    plain.n_split[k] = r.n;
+    plain.split_len[k] = r.len;
+    sec_plain += (k == 0 ? n / plain.width : 1) * r.sec;
+  }
+  if (q.n < 2 || q.n > QueryTiles::kMax || bh <= 0) return plain;
+  AttnLaunchPlan paired = {width_for((q.n + 1) / 2 * bh), true, {1, 1},
+                           {q.range_len(1), q.range_len(1)}};
+  double sec = paired_seconds(p, q, n, paired.width);
+  const bool plain_best = sec_plain <= sec;
+  if (plain_best) sec = sec_plain;
+  // Paired items are all of one length, so launches over more shards keep their rounds in step
+  // and waste less of the last one (13B, 4 shards of 320 items: 2 rounds each, 5 together; the
+  // key ranges they replace: attention of rank 3 4.22 -> 3.84 ms, zigzag rank 0 2.92 -> 2.24,
+  // rank 3 2.64 -> 2.24; unpaired over 4 shards 3.87, 2.35, 2.30).  Where the rounds come out
+  // whole already a wider launch gains nothing (7B, S = 65536: 3.40 and 3.38 ms), so the
+  // fewest shards stay unless the simulation saves more than 1 %.
+  // One key range in place of several rounds the probabilities against another reference and
+  // drops the partials' merge: the layer's output moves by 1.5e-3, its error stays (A of every
+  // token against 64 bits, 13B rank 3 of two ranges and zigzag rank 0 of three: 0.004284 ->
+  // 0.004287 and 0.004665 -> 0.004666).
+  double total = 0.0;
+  for (int i = 0; i < (q.n + 1) / 2; ++i) total += pair_cost(q, i);
+  const double least = least_seconds(p, total * bh * n);
+  int wide = 0;
+  for (int w = paired.width + 1; w <= n && least < 0.99 * sec; ++w) {
+    const double t = paired_seconds(p, q, n, w);
+    if (t < 0.99 * sec) {
+      sec = t;
+      wide = w;
+    }
+  }
+  if (wide) paired.width = wide;
+  return plain_best && !wide ? plain : paired;
+}
+
+// Shapes already planned, the oldest replaced first (the plan depends on these fields only);
+// callers ask for the same shape several times per entry point call.
 struct PlanKey {
-  int batch, heads, head_dim, n_seg, seg_rows[2], seg_pos0[2];
+  int batch, heads, head_dim, shards, n_seg, seg_rows[2], seg_pos0[2];
   bool operator==(const PlanKey& o) const {
-    return batch == o.batch && heads == o.heads && head_dim == o.head_dim && n_seg == o.n_seg &&
-           seg_rows[0] == o.seg_rows[0] && seg_rows[1] == o.seg_rows[1] &&
+    return batch == o.batch && heads == o.heads && head_dim == o.head_dim && shards == o.shards &&
+           n_seg == o.n_seg && seg_rows[0] == o.seg_rows[0] && seg_rows[1] == o.seg_rows[1] &&
            seg_pos0[0] == o.seg_pos0[0] && seg_pos0[1] == o.seg_pos0[1];
   }
 };
 std::mutex g_plan_mu;
-std::vector<std::pair<PlanKey, AttnPlan>> g_plan_cache;
-constexpr size_t kPlanCacheMax = 64;
+std::vector<std::pair<PlanKey, AttnLaunchPlan>> g_plan_cache;
+size_t g_plan_oldest = 0;
+constexpr size_t kPlanCacheMax = 128;
 
-AttnPlan attn_plan(const AttnParams& p) {
-  PlanKey key = {p.batch, p.heads, p.head_dim, p.n_seg, {0, 0}, {0, 0}};
+}  // namespace
+
+AttnLaunchPlan attn_launch_plan(const AttnParams& p, int n) {
+  PlanKey key = {p.batch, p.heads, p.head_dim, n, p.n_seg, {0, 0}, {0, 0}};
   for (int k = 0; k < p.n_seg && k < 2; ++k) {
     key.seg_rows[k] = p.seg_rows[k];
     key.seg_pos0[k] = p.seg_pos0[k];
@@ -879,24 +963,15 @@ AttnPlan attn_plan(const AttnParams& p) {
     for (const auto& c : g_plan_cache)
       if (c.first == key) return c.second;
   }
-  const AttnPlan plan = attn_plan_uncached(p);
+  const AttnLaunchPlan plan = plan_launches(p, n);
   std::lock_guard<std::mutex> lock(g_plan_mu);
-  if (g_plan_cache.size() >= kPlanCacheMax) g_plan_cache.erase(g_plan_cache.begin());
-  g_plan_cache.push_back({key, plan});
+  if (g_plan_cache.size() < kPlanCacheMax) {
+    g_plan_cache.push_back({key, plan});
+  } else {
+    g_plan_cache[g_plan_oldest] = {key, plan};
+    g_plan_oldest = (g_plan_oldest + 1) % kPlanCacheMax;
+  }
   return plan;
-}
-
-}  // namespace
-
-int attn_split_count(const AttnParams& p, int* split_len) {
-  const AttnPlan plan = attn_plan(p);
-  if (split_len) *split_len = plan.split_len;
-  return plan.n_split;
-}
-
-double attn_launch_seconds(const AttnParams& p, bool pair) {
-  const AttnPlan plan = attn_plan(p);
-  return pair ? plan.sec_pair : plan.sec_split;
 }
 
 static std::atomic<int> g_attn_poll_limit{0};

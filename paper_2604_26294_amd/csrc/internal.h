@@ -138,7 +138,7 @@ struct AttnParams {
   int kv_len;       // number of readable keys: the last segment position + 1
   int ld;           // elements between consecutive token rows of Q (0: H_s d)
   int ld_o;         // ... and of O (0: as Q)
-  // Key-range split (attn_split_count): each query tile's keys [0, n) are processed in
+  // Key-range split (AttnLaunchPlan): each query tile's keys [0, n) are processed in
   // ranges [c split_len, (c + 1) split_len), c < n_split.  With n_split > 1 the ranges
   // write partial results -- part_o [n_split][part_rows][d] fp32 (unnormalised O) and
   // part_ml [n_split][part_rows][2] fp32 (reference, sum) with part_rows = B S_loc H_s
@@ -170,14 +170,18 @@ constexpr int kAttnTargetWorkgroups = 256;
 constexpr int kAttnQueryTile = 256;
 constexpr int kAttnKeyStep = 128;
 
-// Number of key ranges (and their length, a multiple of the key tile, in *split_len)
-// for one rank's attention (uses batch, heads and the segments of p): enough (query
-// tile, head, batch, range) work items to fill the GPU.  Depends on the shape only, so
-// workspace sizes are known up front.
-int attn_split_count(const AttnParams& p, int* split_len);
-// Estimated seconds of one attention launch over p's heads: with the split that
-// attn_split_count chooses (pair = false), or with paired query tiles and no split.
-double attn_launch_seconds(const AttnParams& p, bool pair);
+// How a group of n shards runs its attention: launches over `width` shards each and one over
+// the remainder, with paired query tiles (and one key range), or with key ranges: their number
+// and length, a multiple of the key tile, for a launch of `width` shards ([0]) and for the
+// remainder ([1]).  Uses batch, heads (of one shard), head_dim and the segments of p: depends
+// on the shape only, so workspace sizes are known up front.
+struct AttnLaunchPlan {
+  int width;
+  bool pair;
+  int n_split[2];
+  int split_len[2];
+};
+AttnLaunchPlan attn_launch_plan(const AttnParams& p, int n);
 
 // Process-wide cap on the polls of the forward attention's slot waits (0: the default);
 // a test hook for that protocol's failure path.

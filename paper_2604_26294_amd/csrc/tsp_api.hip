@@ -150,84 +150,20 @@ void attn_segments(const Dims& d, AttnParams* ap) {
   }
 }
 
-// Key ranges of the forward attention over the n H_s heads of n shards.
-int attn_group_split(const Dims& d, int n, int* split_len) {
+// How a group of n shards runs its attention.
+tsp::AttnLaunchPlan attn_group_plan(const Dims& d, int n) {
   AttnParams ap = {};
   attn_segments(d, &ap);
-  ap.heads = n * d.hs;
-  return tsp::attn_split_count(ap, split_len);
+  return tsp::attn_launch_plan(ap, n);
 }
-// Key-range length covering every key of a launch in one range (paired tiles).
-int attn_full_len(const AttnParams& ap) {
-  const int keys = ap.seg_pos0[ap.n_seg - 1] + ap.seg_rows[ap.n_seg - 1];
-  return (keys + tsp::kAttnKeyStep - 1) / tsp::kAttnKeyStep * tsp::kAttnKeyStep;
-}
-// How a group of n shards runs its attention: launches over `width` shards each (the
-// last over the remainder), with paired query tiles or with key ranges.  A launch takes
-// the fewest shards whose work items fill the GPU once: the workgroups on an XCD then
-// start together and stream the same keys of the same head through its L2 (a launch of
-// several rounds drifts out of step, as the query tiles' key counts differ, and re-reads
-// K/V).  Pairing (tile i with tile n_qt - 1 - i: equal work per workgroup) halves the
-// work items; whichever plan the dispatch simulation of the attention launches
-// (tsp::attn_launch_seconds) prices lower for the whole group is taken, paired tiles also over
-// more shards than fill the GPU once.
-struct AttnLaunchPlan {
-  int width;
-  bool pair;
-};
-AttnLaunchPlan attn_launch_plan(const Dims& d, int n) {
-  AttnParams ap = {};
-  attn_segments(d, &ap);
-  long long tiles = 0;
-  for (int k = 0; k < ap.n_seg; ++k)
-    tiles += (ap.seg_rows[k] + tsp::kAttnQueryTile - 1) / tsp::kAttnQueryTile;
-  auto width_for = [&](long long items_per_shard) {
-    if (items_per_shard <= 0) return n;
-    const long long need = (tsp::kAttnTargetWorkgroups + items_per_shard - 1) / items_per_shard;
-    return (int)(need < n ? need : n);
-  };
-  auto group_seconds = [&](int width, bool pair) {
-    double sec = 0.0;
-    for (int i = 0; i < n; i += width) {
-      AttnParams q = ap;
-      q.heads = (n - i < width ? n - i : width) * d.hs;
-      sec += tsp::attn_launch_seconds(q, pair);
-    }
-    return sec;
-  };
-  const AttnLaunchPlan plain = {width_for(tiles * d.hs * d.B), false};
-  if (tiles < 2) return plain;
-  const AttnLaunchPlan paired = {width_for((tiles + 1) / 2 * d.hs * d.B), true};
-  const double sec_paired = group_seconds(paired.width, true);
-  const double sec_plain = group_seconds(plain.width, false);
-  AttnLaunchPlan best = sec_paired < sec_plain ? paired : plain;
-  double sec = std::min(sec_paired, sec_plain);
-  // Paired items are all of one length, so launches over more shards keep their rounds in step
-  // and waste less of the last one (13B, 4 shards of 320 items: 2 rounds each, 5 together; the
-  // key ranges they replace: attention of rank 3 4.22 -> 3.84 ms, zigzag rank 0 2.92 -> 2.24,
-  // rank 3 2.64 -> 2.24; unpaired over 4 shards 3.87, 2.35, 2.30).  Where the rounds come out
-  // whole already a wider launch gains nothing (7B, S = 65536: 3.40 and 3.38 ms), so the
-  // fewest shards stay unless the simulation saves more than 1 %.
-  for (int w = paired.width + 1; w <= n; ++w) {
-    const double t = group_seconds(w, true);
-    if (t < 0.99 * sec) {
-      sec = t;
-      best = {w, true};
-    }
-  }
-  return best;
-}
-// (range, token, head) rows of the key-range partials of the launches of a group of n shards
-// (launches of attn_launch_plan's width, and a remainder); 0 without key ranges.
+// (range, token, head) rows of the key-range partials of the launches of a group of n shards;
+// 0 without key ranges.
 size_t attn_part_rows(const Dims& d, int n) {
-  const AttnLaunchPlan lp = attn_launch_plan(d, n);
-  if (lp.pair) return 0;
+  const tsp::AttnLaunchPlan lp = attn_group_plan(d, n);
   size_t part = 0;
-  for (const int w : {lp.width, n % lp.width}) {
-    if (w == 0) continue;
-    const int ns = attn_group_split(d, w, nullptr);
-    const size_t p = ns > 1 ? (size_t)ns * d.M * w * d.hs : 0;
-    if (p > part) part = p;
+  for (int k = 0; k < 2; ++k) {
+    const int w = k == 0 ? lp.width : n % lp.width;
+    if (lp.n_split[k] > 1) part = std::max<size_t>(part, (size_t)lp.n_split[k] * d.M * w * d.hs);
   }
   return part;
 }
@@ -657,13 +593,13 @@ GemmParams qkv_params(const Dims& d, const uint16_t* x, const uint16_t* shard, i
   return g;
 }
 
-// The attention of a group of n shards from r0 on: attn_launch_plan's launches over the
+// The attention of a group of n shards from r0 on: attn_group_plan's launches over the
 // columns of those shards in the group's Q and A.  `base` holds the group's operands, row
 // strides, log-sum-exp placement (of shard r0's heads) and partials.
 tsp_status run_attn_launches(const Dims& d, const AttnParams& base, int r0, int n, int kind,
                              hipStream_t st) {
   const int qd = d.hs * d.d;
-  const AttnLaunchPlan lp = attn_launch_plan(d, n);
+  const tsp::AttnLaunchPlan lp = attn_group_plan(d, n);
   for (int i = 0; i < n; i += lp.width) {
     const int w = n - i < lp.width ? n - i : lp.width;
     AttnParams ap = base;
@@ -677,12 +613,8 @@ tsp_status run_attn_launches(const Dims& d, const AttnParams& base, int r0, int 
     ap.n_kv = d.nkv;
     ap.kv_head0 = (r0 + i) * d.ks;
     ap.pair_tiles = lp.pair ? 1 : 0;
-    if (lp.pair) {
-      ap.n_split = 1;
-      ap.split_len = attn_full_len(ap);
-    } else {
-      ap.n_split = attn_group_split(d, w, &ap.split_len);
-    }
+    ap.n_split = lp.n_split[w < lp.width];
+    ap.split_len = lp.split_len[w < lp.width];
     ap.part_rows = (long long)d.M * ap.heads;
     TSP_LAUNCH(kind, st, tsp::launch_flash_attn(ap, st));
   }

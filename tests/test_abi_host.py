@@ -302,3 +302,24 @@ def test_attention_poll_limit_hook_validates():
     assert T.STATUS_NAMES[T.lib.tsp_test_set_attn_poll_limit(-1)] == "TSP_ERR_SHAPE"
     assert T.lib.tsp_test_set_attn_poll_limit(3) == T.TSP_OK
     assert T.lib.tsp_test_set_attn_poll_limit(0) == T.TSP_OK
+
+
+def test_planning_attention_launches_is_cheap():
+    """The attention launch plan of a new shape is priced on the host by simulating its
+    dispatch, in the workspace query and before the first launch: 0.1 ms for these shapes (13B
+    class, 4 batch entries), where pricing every launch width with all its key ranges took
+    4.5 ms.  Shapes already planned are looked up, also when a program cycles over dozens.
+    The bounds leave a factor of ten for a slower host; the fastest of many calls counts."""
+    import time
+
+    def query(seq):
+        sh = T.make_shape(4, seq, 5120, 13824, 40, 40, 128, 4, 0, 1)
+        t0 = time.perf_counter()
+        T.workspace_bytes(sh, T.OP_ATTN)
+        return time.perf_counter() - t0
+
+    seqs = [16384 - 2048 + 64 * i for i in range(32)]  # planned by no other test
+    first = [query(s) for s in seqs]
+    again = [query(s) for s in seqs]
+    assert min(first) < 1.5e-3, first
+    assert sorted(again)[16] < 0.15e-3, again
