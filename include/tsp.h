@@ -72,7 +72,8 @@ typedef enum tsp_status {
   TSP_ERR_SHAPE = 2,       /* dimensions are non-positive or inconsistent (see below) */
   TSP_ERR_RANK = 3,        /* rank outside [0, degree) */
   TSP_ERR_ALIGN = 4,       /* a device pointer is not 16-byte aligned */
-  TSP_ERR_WORKSPACE = 5,   /* ws_bytes is smaller than tsp_workspace_bytes() */
+  TSP_ERR_WORKSPACE = 5,   /* ws_bytes is smaller than tsp_workspace_bytes() (a shape with
+                              group_steps > 0: than that with TSP_WS_MIN) */
   TSP_ERR_UNSUPPORTED = 6, /* valid shape the kernels do not implement */
   TSP_ERR_HIP = 7          /* a kernel launch failed */
 } tsp_status;
@@ -111,8 +112,10 @@ typedef struct tsp_shape {
  * G n_h/D heads at once.  The result is the step-by-step sum up to fp32 rounding order.
  * In a streaming schedule G is the number of weight shards held at once; with every
  * shard resident (one GPU) the default takes all D steps together (D <= the maximum).
- * The backward calls and tsp_kv_rank_fwd group their shards too, as the sizes ask for (up
- * to TSP_GROUP_STEPS_MAX), and ignore it. */
+ * tsp_kv_rank_fwd ignores it.  The backward calls group their shards as the sizes ask for (up
+ * to TSP_GROUP_STEPS_MAX, tsp_attn_kv_rank_bwd up to D), which keeps the operands of a whole
+ * group in the workspace.  With group_steps = n > 0 they also run in a smaller one, down to
+ * what groups of min(n, D) shards need (TSP_WS_MIN), in the largest groups that it holds. */
 #define TSP_GROUP_STEPS_MAX 8
 
 /* Gated ring MLP of rank p (Algorithm 2):
@@ -309,6 +312,10 @@ enum {
   TSP_OP_ATTN_BWD = 4,
   TSP_OP_ATTN_KV_BWD = 5
 };
+
+/* Or'ed to an op of tsp_workspace_bytes: the smallest workspace the entry point takes.  Less
+ * than without it for the backward ops of a shape with group_steps > 0; the same otherwise. */
+#define TSP_WS_MIN 0x100
 
 /* Workspace bytes the entry point `op` needs for `shape` (validated as above). */
 tsp_status tsp_workspace_bytes(const tsp_shape* shape, int op, size_t* bytes);

@@ -1356,13 +1356,15 @@ struct NnPlan {
   NnTile tile;
   int splits;
 };
-NnPlan nn_acc_plan(int M, int N, int K) {
+NnPlan nn_acc_plan(int M, int N, int K, bool may_split = true) {
   const long long t256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
   if (t256 <= 0 || t256 >= kCus || N % 4 != 0) return {kNn256, 1};
   // Most ranges: enough (tile, range) items of 256 x 256 for every CU with at least 16 steps
   // per range (the partials' workspace is sized by the choice, so it is bounded by that too).
-  const int steps = K / BK, most = std::max(1, (int)std::min((kCus + t256 - 1) / t256,
-                                                             (long long)(steps / 16)));
+  const int steps = K / BK;
+  const int most = may_split ? std::max(1, (int)std::min((kCus + t256 - 1) / t256,
+                                                         (long long)(steps / 16)))
+                             : 1;
   // us of a step with one workgroup on every CU, and with two where they fit (64 x 64).
   constexpr struct {
     NnTile tile;
@@ -1396,7 +1398,7 @@ int gemm_nn_acc_splits(int M, int N, int K) { return nn_acc_plan(M, N, K).splits
 
 hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  const NnPlan plan = nn_acc_plan(p.M, p.N, p.K);
+  const NnPlan plan = nn_acc_plan(p.M, p.N, p.K, part != nullptr);
   GemmParams q = p;
   q.k_splits = plan.splits;
   q.part = part;

@@ -99,7 +99,7 @@ hipError_t launch_gemm_swiglu_bwd_group(const GemmParams* ps, int n, hipStream_t
 int gemm_swiglu_bwd_per_launch(const GemmParams* ps, int n);
 // The accumulate epilogue over [K, N] operands.  Products with few output tiles may split
 // their contraction (gemm_nn_acc_splits ranges) through an fp32 workspace `part` of at least
-// splits * M * N floats (unused when splits == 1).
+// splits * M * N floats (unused when splits == 1; null: not split).
 hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s);
 int gemm_nn_acc_splits(int M, int N, int K);
 // Up to kGemmGroupMax independent accumulate products (one part, no split contraction) in

@@ -32,6 +32,7 @@ struct Dims {
   bool zz;     // zigzag layout: local rows = [chunk p; chunk 2D-1-p] of S/(2D) tokens each
   int s_c;     // S_loc / 2 (zigzag chunk length)
   int G;       // forward shard steps per grouped launch (1 .. min(D, kGroupMax))
+  int least;   // shards of the smallest group a backward call may take (0: full groups only)
 };
 
 // Most shard steps of one grouped launch (the number of operand pairs one product's
@@ -79,6 +80,7 @@ tsp_status check_shape(const tsp_shape* s, Dims* o) {
   o->s_c = o->s_loc / 2;
   o->G = s->group_steps > 0 ? s->group_steps : kGroupMax;
   if (o->G > o->D) o->G = o->D;
+  o->least = s->group_steps > 0 ? o->G : 0;
   // The GEMM operand loads address each operand with 32-bit byte offsets: the widest
   // per-token rows (x and Y [M, h]; the group's gated products [M, G (F/D rounded up to
   // 64)]; the backward's [M, F/D] and transposed [F/D, M] operands) must stay below 4 GiB.
@@ -191,6 +193,11 @@ AttnWs attn_ws(const Dims& d) {
   return w;
 }
 size_t ws_attn(const Dims& d) { return attn_ws(d).total; }
+// A backward group that holds one shard and splits no contraction or query range (no partial
+// sums): the smallest workspace.
+constexpr int kLeanGroup = 0;
+int group_shards(int group) { return group == kLeanGroup ? 1 : group; }
+
 // MLP backward workspace, for groups of n ring steps (mlp_bwd_group): dG, dU of the group's
 // steps side by side, [M, n x (F/D rounded up to 64)] bf16 (the A operands of the dX
 // products), then dG^T, dU^T, Hs^T [n F/D, M rounded up to 64] bf16 (the A operands of the
@@ -211,14 +218,14 @@ int mlp_bwd_group(const Dims& d) {
   while (n > 1 && d.M * n * d.fs_pad * 2 >= (1LL << 32)) --n;  // 32-bit operand offsets
   return n;
 }
-MlpBwdWs mlp_bwd_ws(const Dims& d) {
+MlpBwdWs mlp_bwd_ws(const Dims& d, int group) {
   MlpBwdWs w;
-  const int g = mlp_bwd_group(d);
+  const int g = group_shards(group);
   w.m_pad = (int)((d.M + 63) / 64 * 64);
   const size_t rm = align_up((size_t)d.M * g * d.fs_pad * 2);
   const size_t tr = align_up((size_t)g * d.fs * w.m_pad * 2);
   size_t part = 0;
-  for (int n = 1; n <= g && n <= kMlpBwdDxSteps; ++n)
+  for (int n = 1; group != kLeanGroup && n <= g && n <= kMlpBwdDxSteps; ++n)
     part = std::max(part, nn_part_bytes(d, 2 * n * d.fs_pad));
   w.dg = 0;
   w.du = rm;
@@ -258,9 +265,9 @@ void attn_bwd_segments(const Dims& d, int n, AttnBwdParams* bp) {
     bp->seg_pos0[k] = ap.seg_pos0[k];
   }
 }
-AttnBwdWs attn_bwd_ws(const Dims& d) {
+AttnBwdWs attn_bwd_ws(const Dims& d, int group) {
   AttnBwdWs w;
-  const int g = attn_bwd_group(d);
+  const int g = group_shards(group);
   w.m_pad = (int)((d.M + 63) / 64 * 64);
   size_t fwd_part = 0, shared = 0;
   for (const int n : {g, d.D % g}) {  // a full group, and a last one of the remainder
@@ -271,8 +278,8 @@ AttnBwdWs attn_bwd_ws(const Dims& d) {
     attn_bwd_segments(d, n, &bp);
     const int ns = tsp::attn_bwd_dq_split(bp, nullptr);
     const size_t dq = ns > 1 ? (size_t)ns * d.M * n * d.hs * d.d * 4 : 0;
-    const size_t dx = nn_part_bytes(d, n * d.hs * d.d);
-    const int kvs = tsp::attn_bwd_kv_split(bp);
+    const size_t dx = group != kLeanGroup ? nn_part_bytes(d, n * d.hs * d.d) : 0;
+    const int kvs = group != kLeanGroup ? tsp::attn_bwd_kv_split(bp) : 1;
     const size_t kv = kvs > 1 ? (size_t)kvs * 2 * d.B * d.S * n * d.ks * d.d * 4 : 0;
     shared = std::max({shared, dq, dx, kv});
   }
@@ -292,25 +299,52 @@ AttnBwdWs attn_bwd_ws(const Dims& d) {
   w.total = std::max(w.pml + align_up(fwd_part * 2 * 4), w.part + align_up(shared));
   return w;
 }
-// Attention backward, second stage: the transposed gradients of every shard's K and V rows,
-// [n_kv d, M rounded up to 64] bf16 each, then the dX product's partial sums.
+// Attention backward, second stage, in groups of g shards (all D by default): the transposed
+// gradients of a group's K and V rows, [g K_s d, M rounded up to 64] bf16 each, then the dX
+// product's partial sums.
 constexpr int kKvBwdDxShards = tsp::kGemmPartsMax / 2;  // shards of one dX product
 struct AttnKvBwdWs {
   size_t kt, vt, part, total;
   int m_pad;
 };
-AttnKvBwdWs attn_kv_bwd_ws(const Dims& d) {
+AttnKvBwdWs attn_kv_bwd_ws(const Dims& d, int group) {
   AttnKvBwdWs w;
+  const int g = group_shards(group);
   w.m_pad = (int)((d.M + 63) / 64 * 64);
-  const size_t tr = align_up((size_t)d.nkv * d.d * w.m_pad * 2);
+  const size_t tr = align_up((size_t)g * d.ks * d.d * w.m_pad * 2);
   size_t part = 0;
-  for (int n = 1; n <= d.D && n <= kKvBwdDxShards; ++n)
+  for (int n = 1; group != kLeanGroup && n <= g && n <= kKvBwdDxShards; ++n)
     part = std::max(part, nn_part_bytes(d, 2 * n * d.ks * d.d));
   w.kt = 0;
   w.vt = tr;
   w.part = 2 * tr;
   w.total = w.part + align_up(part);
   return w;
+}
+// Backward workspaces by group, and the most shards a group takes (the workspace query's
+// default).  Groups fill the chip, but hold their shards' operands; a caller short of memory
+// sets group_steps = n > 0, with which a call runs in any workspace that holds groups of n (n =
+// 1: kLeanGroup), in the largest groups that fit.
+size_t mlp_bwd_bytes(const Dims& d, int group) { return mlp_bwd_ws(d, group).total; }
+size_t attn_bwd_bytes(const Dims& d, int group) { return attn_bwd_ws(d, group).total; }
+size_t attn_kv_bwd_bytes(const Dims& d, int group) { return attn_kv_bwd_ws(d, group).total; }
+int attn_kv_bwd_group(const Dims& d) { return d.D; }
+using BwdBytes = size_t (*)(const Dims&, int);
+// The smallest group that a call may take, of at most `most` shards.
+int least_group(const Dims& d, int most) {
+  if (d.least == 1) return kLeanGroup;
+  return d.least > 0 && d.least < most ? d.least : most;
+}
+size_t bwd_query(const Dims& d, int most, BwdBytes bytes, bool smallest) {
+  size_t need = bytes(d, most);
+  for (int g = least_group(d, most); smallest && g < most; ++g) need = std::min(need, bytes(d, g));
+  return need;
+}
+// The group of a call with ws_bytes of workspace; negative if that is too small.
+int fitting_group(const Dims& d, int most, BwdBytes bytes, size_t ws_bytes) {
+  int g = most;
+  while (g >= least_group(d, most) && bytes(d, g) > ws_bytes) --g;
+  return g >= least_group(d, most) ? g : -1;
 }
 size_t ws_layer(const Dims& d) {
   const size_t a = ws_mlp(d), b = ws_attn(d);
@@ -467,7 +501,7 @@ GemmParams dw_params(const Dims& d, const uint16_t* t, int m_pad, const uint16_t
   return q;
 }
 
-// Backward of run_mlp (same ring order), in groups of mlp_bwd_group steps.  Per group: one or
+// Backward of run_mlp (same ring order), in groups of ws_group steps.  Per group: one or
 // two grouped launches for G, U, dHs and the SwiGLU backward of its shards, the accumulating
 // products for dX (over up to kMlpBwdDxSteps steps each), and grouped launches for the 3 n
 // weight gradients (each [F/D, h], contracting over the M tokens).
@@ -475,9 +509,10 @@ tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
                        const uint16_t* const* wg, const uint16_t* const* wu,
                        const uint16_t* const* wd, float* dx, int accumulate,
                        float* const* dwg, float* const* dwu, float* const* dwd, char* ws,
-                       hipStream_t st) {
-  const MlpBwdWs w = mlp_bwd_ws(d);
-  const int group = mlp_bwd_group(d);
+                       int ws_group, hipStream_t st) {
+  const MlpBwdWs w = mlp_bwd_ws(d, ws_group);
+  const int group = group_shards(ws_group);
+  float* part = ws_group != kLeanGroup ? reinterpret_cast<float*>(ws + w.part) : nullptr;
   uint16_t* dg = reinterpret_cast<uint16_t*>(ws + w.dg);
   uint16_t* du = reinterpret_cast<uint16_t*>(ws + w.du);
   uint16_t* tr[3] = {reinterpret_cast<uint16_t*>(ws + w.dgt),
@@ -539,8 +574,7 @@ tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
       p.Y = dx;
       p.ldy = d.h;
       p.accumulate = (t0 + i0 > 0 || accumulate) ? 1 : 0;
-      TSP_LAUNCH(TSP_KERNEL_BWD_DX, st,
-                 tsp::launch_gemm_nn_acc(p, reinterpret_cast<float*>(ws + w.part), st));
+      TSP_LAUNCH(TSP_KERNEL_BWD_DX, st, tsp::launch_gemm_nn_acc(p, part, st));
     }
     // dW (+)= (dG^T | dU^T | Hs^T) (X | X | dY): [F/D, M] x [M, h], padded rows are zero.
     float* const* const out[3] = {dwg, dwu, dwd};
@@ -714,17 +748,17 @@ GemmParams nt_params(const Dims& d, const uint16_t* a, const uint16_t* b, int n,
   return g;
 }
 
-// Backward of run_attn, first stage (see tsp_attn_rank_bwd), in groups of attn_bwd_group
-// shards: every kernel takes a group's n H_s heads (or its n products) in one launch.
+// Backward of run_attn, first stage (see tsp_attn_rank_bwd), in groups of ws_group shards: every
+// kernel takes a group's n H_s heads (or its n products) in one launch.
 tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
                         const uint16_t* const* wa, const uint16_t* kb, const uint16_t* vb,
                         float* dx, int accumulate, float* const* dw, float* dk, float* dv,
-                        char* ws, hipStream_t st, const uint16_t* a_saved = nullptr,
+                        char* ws, int ws_group, hipStream_t st, const uint16_t* a_saved = nullptr,
                         const float* lse_saved = nullptr) {
   const int qd = d.hs * d.d, kd = d.ks * d.d;
   const size_t wo = (size_t)(qd + 2 * kd) * d.h;  // W_O^(r)^T block [H_s d, h] of a shard
-  const AttnBwdWs w = attn_bwd_ws(d);
-  const int group = attn_bwd_group(d);
+  const AttnBwdWs w = attn_bwd_ws(d, ws_group);
+  const int group = group_shards(ws_group);
   uint16_t* q_ws = reinterpret_cast<uint16_t*>(ws + w.q);
   uint16_t* a_ws = reinterpret_cast<uint16_t*>(ws + w.a);
   uint16_t* da_ws = reinterpret_cast<uint16_t*>(ws + w.da);
@@ -790,7 +824,7 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     bp.scale = d.scale;
     bp.dq_split = tsp::attn_bwd_dq_split(bp, &bp.dq_split_len);
     bp.dq_part = part;
-    bp.kv_split = tsp::attn_bwd_kv_split(bp);
+    bp.kv_split = ws_group != kLeanGroup ? tsp::attn_bwd_kv_split(bp) : 1;
     bp.kv_part = part;
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st, tsp::launch_attn_bwd_prep(bp, st));
     TSP_LAUNCH(TSP_KERNEL_ABWD_KV, st, tsp::launch_attn_bwd_dkdv(bp, st));
@@ -815,7 +849,8 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     p.Y = dx;
     p.ldy = d.h;
     p.accumulate = (r0 > 0 || accumulate) ? 1 : 0;
-    TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st, tsp::launch_gemm_nn_acc(p, part, st));
+    TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st,
+               tsp::launch_gemm_nn_acc(p, ws_group != kLeanGroup ? part : nullptr, st));
 
     // W_Q blocks (+)= dQ^T X;  W_O^T blocks (+)= A^T dY: [H_s d, M] x [M, h] per shard.
     TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
@@ -832,54 +867,60 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
   return TSP_OK;
 }
 
-// Second stage (see tsp_attn_kv_rank_bwd): the dX products over kKvBwdDxShards shards each,
-// both gradients transposed whole, and grouped launches for the weight gradients.
+// Second stage (see tsp_attn_kv_rank_bwd), in groups of ws_group shards: the dX products over
+// kKvBwdDxShards shards each, both gradients transposed, and grouped launches for the weight
+// gradients.
 tsp_status run_attn_kv_bwd(const Dims& d, const uint16_t* x, const uint16_t* const* wa,
                            const uint16_t* dkl, const uint16_t* dvl, float* dx, int accumulate,
-                           float* const* dw, char* ws, hipStream_t st) {
+                           float* const* dw, char* ws, int ws_group, hipStream_t st) {
   const int qd = d.hs * d.d, kd = d.ks * d.d, ld = d.nkv * d.d;
-  const AttnKvBwdWs w = attn_kv_bwd_ws(d);
+  const AttnKvBwdWs w = attn_kv_bwd_ws(d, ws_group);
+  const int group = group_shards(ws_group);
+  float* part = ws_group != kLeanGroup ? reinterpret_cast<float*>(ws + w.part) : nullptr;
   const uint16_t* const grad[2] = {dkl, dvl};  // [M, n_kv d], shard r's columns at r K_s d
   uint16_t* const tr[2] = {reinterpret_cast<uint16_t*>(ws + w.kt),
                            reinterpret_cast<uint16_t*>(ws + w.vt)};
-  // dX (+)= sum of dK_r W_K^(r) + dV_r W_V^(r), one product over the shards' operand pairs.
-  for (int r0 = 0; r0 < d.D; r0 += kKvBwdDxShards) {
-    const int n = d.D - r0 < kKvBwdDxShards ? d.D - r0 : kKvBwdDxShards;
-    GemmParams p = {};
-    for (int i = 0; i < 2 * n; ++i) {
-      const int r = r0 + i / 2, k = i % 2;
-      p.A_part[i] = grad[k] + (size_t)r * kd;
-      p.B_part[i] = wa[r] + (size_t)(qd + k * kd) * d.h;
+  for (int g0 = 0; g0 < d.D; g0 += group) {
+    const int g1 = std::min(g0 + group, d.D);
+    // dX (+)= sum of dK_r W_K^(r) + dV_r W_V^(r), one product over the shards' operand pairs.
+    for (int r0 = g0; r0 < g1; r0 += kKvBwdDxShards) {
+      const int n = std::min(g1 - r0, kKvBwdDxShards);
+      GemmParams p = {};
+      for (int i = 0; i < 2 * n; ++i) {
+        const int r = r0 + i / 2, k = i % 2;
+        p.A_part[i] = grad[k] + (size_t)r * kd;
+        p.B_part[i] = wa[r] + (size_t)(qd + k * kd) * d.h;
+      }
+      p.A = p.A_part[0];
+      p.lda = ld;
+      p.B = p.B_part[0];
+      p.ldb = d.h;
+      p.n_parts = 2 * n;
+      p.k_part = kd;
+      p.K = 2 * n * kd;
+      p.Kb_rows = kd;
+      p.M = (int)d.M;
+      p.N = d.h;
+      p.Y = dx;
+      p.ldy = d.h;
+      p.accumulate = (r0 > 0 || accumulate) ? 1 : 0;
+      TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st, tsp::launch_gemm_nn_acc(p, part, st));
     }
-    p.A = p.A_part[0];
-    p.lda = ld;
-    p.B = p.B_part[0];
-    p.ldb = d.h;
-    p.n_parts = 2 * n;
-    p.k_part = kd;
-    p.K = 2 * n * kd;
-    p.Kb_rows = kd;
-    p.M = (int)d.M;
-    p.N = d.h;
-    p.Y = dx;
-    p.ldy = d.h;
-    p.accumulate = (r0 > 0 || accumulate) ? 1 : 0;
-    TSP_LAUNCH(TSP_KERNEL_ABWD_DX, st,
-               tsp::launch_gemm_nn_acc(p, reinterpret_cast<float*>(ws + w.part), st));
-  }
-  // W_K blocks (+)= dK^T X;  W_V blocks (+)= dV^T X: [K_s d, M] x [M, h] per shard.
-  TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
-             tsp::launch_transpose2_bf16(grad[0], ld, tr[0], grad[1], ld, tr[1], (int)d.M, ld,
-                                         w.m_pad, st));
-  GemmParams q[tsp::kGemmGroupMax] = {};
-  int n = 0;
-  for (int i = 0; i < 2 * d.D; ++i) {
-    const int r = i / 2, k = i % 2;
-    q[n++] = dw_params(d, tr[k] + (size_t)r * kd * w.m_pad, w.m_pad, x, kd,
-                       dw[r] + (size_t)(qd + k * kd) * d.h, accumulate);
-    if (n == tsp::kGemmGroupMax || i + 1 == 2 * d.D) {
-      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(q, n, st));
-      n = 0;
+    // W_K blocks (+)= dK^T X;  W_V blocks (+)= dV^T X: [K_s d, M] x [M, h] per shard.
+    TSP_LAUNCH(TSP_KERNEL_ABWD_AUX, st,
+               tsp::launch_transpose2_bf16(grad[0] + (size_t)g0 * kd, ld, tr[0],
+                                           grad[1] + (size_t)g0 * kd, ld, tr[1], (int)d.M,
+                                           (g1 - g0) * kd, w.m_pad, st));
+    GemmParams q[tsp::kGemmGroupMax] = {};
+    int n = 0;
+    for (int i = 2 * g0; i < 2 * g1; ++i) {
+      const int r = i / 2, k = i % 2;
+      q[n++] = dw_params(d, tr[k] + (size_t)(r - g0) * kd * w.m_pad, w.m_pad, x, kd,
+                         dw[r] + (size_t)(qd + k * kd) * d.h, accumulate);
+      if (n == tsp::kGemmGroupMax || i + 1 == 2 * g1) {
+        TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(q, n, st));
+        n = 0;
+      }
     }
   }
   return TSP_OK;
@@ -957,13 +998,20 @@ tsp_status tsp_workspace_bytes(const tsp_shape* shape, int op, size_t* bytes) {
   Dims d;
   TSP_TRY(check_shape(shape, &d));
   if (!bytes) return TSP_ERR_NULL;
-  switch (op) {
+  const bool least = (op & TSP_WS_MIN) != 0;
+  switch (op & ~TSP_WS_MIN) {
     case TSP_OP_MLP: *bytes = ws_mlp(d); return TSP_OK;
     case TSP_OP_ATTN: *bytes = ws_attn(d); return TSP_OK;
     case TSP_OP_LAYER: *bytes = ws_layer(d); return TSP_OK;
-    case TSP_OP_MLP_BWD: *bytes = mlp_bwd_ws(d).total; return TSP_OK;
-    case TSP_OP_ATTN_BWD: *bytes = attn_bwd_ws(d).total; return TSP_OK;
-    case TSP_OP_ATTN_KV_BWD: *bytes = attn_kv_bwd_ws(d).total; return TSP_OK;
+    case TSP_OP_MLP_BWD:
+      *bytes = bwd_query(d, mlp_bwd_group(d), mlp_bwd_bytes, least);
+      return TSP_OK;
+    case TSP_OP_ATTN_BWD:
+      *bytes = bwd_query(d, attn_bwd_group(d), attn_bwd_bytes, least);
+      return TSP_OK;
+    case TSP_OP_ATTN_KV_BWD:
+      *bytes = bwd_query(d, attn_kv_bwd_group(d), attn_kv_bwd_bytes, least);
+      return TSP_OK;
     default: return TSP_ERR_SHAPE;
   }
 }
@@ -1004,10 +1052,11 @@ tsp_status tsp_mlp_rank_bwd(const tsp_shape* shape, const uint16_t* x_loc,
   TSP_TRY(check_shards(dw_up, d.D));
   TSP_TRY(check_shards(dw_down, d.D));
   TSP_TRY(check_ptr(ws));
-  if (ws_bytes < mlp_bwd_ws(d).total) return TSP_ERR_WORKSPACE;
+  const int group = fitting_group(d, mlp_bwd_group(d), mlp_bwd_bytes, ws_bytes);
+  if (group < 0) return TSP_ERR_WORKSPACE;
   if (d.M == 0) return TSP_OK;
   return run_mlp_bwd(d, x_loc, dy_loc, w_gate, w_up, w_down, dx_loc, accumulate, dw_gate,
-                     dw_up, dw_down, static_cast<char*>(ws), stream);
+                     dw_up, dw_down, static_cast<char*>(ws), group, stream);
 }
 
 tsp_status tsp_kv_rank_fwd(const tsp_shape* shape, const uint16_t* x_loc,
@@ -1086,10 +1135,11 @@ tsp_status tsp_attn_rank_bwd(const tsp_shape* shape, const uint16_t* x_loc,
   TSP_TRY(check_ptr(dk_buf));
   TSP_TRY(check_ptr(dv_buf));
   TSP_TRY(check_ptr(ws));
-  if (ws_bytes < attn_bwd_ws(d).total) return TSP_ERR_WORKSPACE;
+  const int group = fitting_group(d, attn_bwd_group(d), attn_bwd_bytes, ws_bytes);
+  if (group < 0) return TSP_ERR_WORKSPACE;
   if (d.M == 0) return TSP_OK;
   return run_attn_bwd(d, x_loc, dy_loc, w_attn, k_buf, v_buf, dx_loc, accumulate, dw_attn,
-                      dk_buf, dv_buf, static_cast<char*>(ws), stream);
+                      dk_buf, dv_buf, static_cast<char*>(ws), group, stream);
 }
 
 tsp_status tsp_attn_rank_bwd_saved(const tsp_shape* shape, const uint16_t* x_loc,
@@ -1113,10 +1163,11 @@ tsp_status tsp_attn_rank_bwd_saved(const tsp_shape* shape, const uint16_t* x_loc
   TSP_TRY(check_ptr(dk_buf));
   TSP_TRY(check_ptr(dv_buf));
   TSP_TRY(check_ptr(ws));
-  if (ws_bytes < attn_bwd_ws(d).total) return TSP_ERR_WORKSPACE;
+  const int group = fitting_group(d, attn_bwd_group(d), attn_bwd_bytes, ws_bytes);
+  if (group < 0) return TSP_ERR_WORKSPACE;
   if (d.M == 0) return TSP_OK;
   return run_attn_bwd(d, x_loc, dy_loc, w_attn, k_buf, v_buf, dx_loc, accumulate, dw_attn,
-                      dk_buf, dv_buf, static_cast<char*>(ws), stream, a_saved, lse_saved);
+                      dk_buf, dv_buf, static_cast<char*>(ws), group, stream, a_saved, lse_saved);
 }
 
 tsp_status tsp_attn_kv_rank_bwd(const tsp_shape* shape, const uint16_t* x_loc,
@@ -1133,10 +1184,11 @@ tsp_status tsp_attn_kv_rank_bwd(const tsp_shape* shape, const uint16_t* x_loc,
   TSP_TRY(check_ptr(dx_loc));
   TSP_TRY(check_shards(dw_attn, d.D));
   TSP_TRY(check_ptr(ws));
-  if (ws_bytes < attn_kv_bwd_ws(d).total) return TSP_ERR_WORKSPACE;
+  const int group = fitting_group(d, attn_kv_bwd_group(d), attn_kv_bwd_bytes, ws_bytes);
+  if (group < 0) return TSP_ERR_WORKSPACE;
   if (d.M == 0) return TSP_OK;
   return run_attn_kv_bwd(d, x_loc, w_attn, dk_loc, dv_loc, dx_loc, accumulate, dw_attn,
-                         static_cast<char*>(ws), stream);
+                         static_cast<char*>(ws), group, stream);
 }
 
 tsp_status tsp_layer_rank_fwd(const tsp_shape* shape, const uint16_t* x_loc,

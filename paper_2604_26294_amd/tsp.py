@@ -20,6 +20,7 @@ STATUS_NAMES = {0: "TSP_OK", 1: "TSP_ERR_NULL", 2: "TSP_ERR_SHAPE", 3: "TSP_ERR_
                 4: "TSP_ERR_ALIGN", 5: "TSP_ERR_WORKSPACE", 6: "TSP_ERR_UNSUPPORTED",
                 7: "TSP_ERR_HIP"}
 OP_MLP, OP_ATTN, OP_LAYER, OP_MLP_BWD, OP_ATTN_BWD, OP_ATTN_KV_BWD = 0, 1, 2, 3, 4, 5
+WS_MIN = 0x100  # TSP_WS_MIN, or'ed to an op of workspace_bytes
 LAYOUT_CONTIGUOUS, LAYOUT_ZIGZAG = 0, 1
 KERNELS = ("gate_up", "down", "qkv", "attn", "oproj",  # TSP_KERNEL_* order
            "bwd_gate", "bwd_dx", "bwd_dw",

@@ -304,6 +304,31 @@ def test_attention_poll_limit_hook_validates():
     assert T.lib.tsp_test_set_attn_poll_limit(0) == T.TSP_OK
 
 
+def test_backward_workspace_can_be_bounded():
+    """group_steps = n > 0 lets the backward run in a workspace for groups of n shards: at most
+    two shards' operands and no partial sums for n = 1 (the sizes of a schedule that takes one or
+    two shards at a time, in MiB), in between for others; refused below it."""
+    wl = BY_NAME["7b-h4096-S65536-D8"]
+    full, one, two = (T.shape_of(wl, group_steps=n) for n in (0, 1, 2))
+    ops = (T.OP_MLP_BWD, T.OP_ATTN_BWD, T.OP_ATTN_KV_BWD)
+    for op, most in zip(ops, (173, 121, 16)):
+        size = T.workspace_bytes(full, op)
+        assert T.workspace_bytes(full, op | T.WS_MIN) == size  # no bound set
+        assert T.workspace_bytes(one, op) == T.workspace_bytes(two, op) == size
+        least = T.workspace_bytes(one, op | T.WS_MIN)
+        assert least <= most << 20 and least % 256 == 0
+        assert least < T.workspace_bytes(two, op | T.WS_MIN) < size
+    for op in (T.OP_MLP, T.OP_ATTN, T.OP_LAYER):
+        assert T.workspace_bytes(one, op | T.WS_MIN) == T.workspace_bytes(one, op)
+    g8, _k = _arr(8)
+    sh, (mlp, attn, kv) = ctypes.byref(one), (T.workspace_bytes(one, o | T.WS_MIN) - 1 for o in ops)
+    assert T.lib.tsp_mlp_rank_bwd(sh, FAKE, FAKE, g8, g8, g8, FAKE, 0, g8, g8, g8, FAKE, mlp,
+                                  None) == 5
+    assert T.lib.tsp_attn_rank_bwd(sh, FAKE, FAKE, g8, FAKE, FAKE, FAKE, 0, g8, FAKE, FAKE, FAKE,
+                                   attn, None) == 5
+    assert T.lib.tsp_attn_kv_rank_bwd(sh, FAKE, g8, FAKE, FAKE, FAKE, 1, g8, FAKE, kv, None) == 5
+
+
 def test_planning_attention_launches_is_cheap():
     """The attention launch plan of a new shape is priced on the host by simulating its
     dispatch, in the workspace query and before the first launch: 0.1 ms for these shapes (13B

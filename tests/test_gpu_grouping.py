@@ -11,10 +11,11 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+from paper_2604_26294_amd import inputs as I  # noqa: E402
 from paper_2604_26294_amd import tsp as T  # noqa: E402
-from paper_2604_26294_amd.harness import RankProblem  # noqa: E402
-from tests.gpu_common import (DEG16, MID_GQA64, MID_MHA128, ODD3, SUBL, WIDE,  # noqa: E402
-                              assert_close, gen, oracle_blocks)
+from paper_2604_26294_amd.harness import RankProblem, local_rows, to_device_bf16  # noqa: E402
+from tests.gpu_common import (DEG12, DEG16, MID_GQA64, MID_MHA128, ODD3, SUBL,  # noqa: E402
+                              WIDE, assert_close, gen, oracle_blocks)
 
 # (workload, rank, group_steps values); 0 is the library default, min(D, 8)
 CASES = [(MID_GQA64, 3, (1, 2, 3)), (MID_GQA64.with_layout(1), 1, (1, 3)),
@@ -97,3 +98,41 @@ def test_paired_launch_over_more_shards_than_fill_the_gpu(wl, p):
     assert_close(outs[0], oracle_blocks(wl, x_bits, w_bits, p, blocks=("attn",))["attn"],
                  f"{wl.name} r{p}")
     assert np.max(np.abs(outs[0] - outs[1])) <= 1e-2 * np.max(np.abs(outs[1]))
+
+
+@pytest.mark.parametrize("wl,p,steps", [(MID_GQA64, 2, 1), (MID_MHA128.with_layout(1), 0, 1),
+                                        (ODD3, 2, 2), (DEG12, 7, 1), (DEG12, 7, 5)],
+                         ids=["gqa64-1", "mha128-zigzag-1", "odd3-2", "deg12-1", "deg12-5"])
+def test_backward_in_the_smallest_workspace(wl, p, steps):
+    """Every backward call in the smallest workspace that group_steps allows (one shard at a
+    time without partial sums, groups that leave a smaller last one) gives the gradients of the
+    default groups, which the oracle checks elsewhere, and writes nothing past it."""
+    print(f"[bounded bwd] {wl.name} {wl.layout_name} rank {p} group_steps={steps}", flush=True)
+    x_bits, w_bits = _inputs(wl)
+    dy = to_device_bf16(local_rows(I.make_dy_full(wl), wl, p))
+    dkl, dvl = (to_device_bf16(t) for t in I.make_dkv_own(wl, p))
+    outs = []
+    for g in (0, steps):
+        prob = RankProblem(wl, x_bits, w_bits, p, group_steps=g)
+        prob.prefill_kv()
+        prob.attn_fwd_train()
+        calls = {"mlp": (T.OP_MLP_BWD, "ws_bwd", lambda: prob.mlp_bwd(dy)),
+                 "attn": (T.OP_ATTN_BWD, "ws_abwd", lambda: prob.attn_bwd(dy)),
+                 "saved": (T.OP_ATTN_BWD, "ws_abwd", lambda: prob.attn_bwd_saved(dy)),
+                 "kv": (T.OP_ATTN_KV_BWD, "ws_abwd", lambda: prob.attn_kv_bwd(dkl, dvl, False))}
+        got = {}
+        for name, (op, buf, call) in calls.items():
+            call()  # allocates the gradients and a full workspace
+            if g:
+                n = T.workspace_bytes(prob.shape, op | T.WS_MIN)
+                assert n < T.workspace_bytes(prob.shape, op)
+                held = torch.full((n + 4096,), 255, dtype=torch.uint8, device="cuda")
+                setattr(prob, buf, held[:n])
+            flat = [t for o in call() for t in (o if isinstance(o, list) else [o])]
+            got[name] = [t.double().cpu().numpy() for t in flat]
+            if g:
+                assert bool((held[n:] == 255).all()), f"{name} past the workspace"
+        outs.append(got)
+    for name, ref in outs[0].items():
+        for a, b in zip(outs[1][name], ref):
+            assert_close(a, b, f"{wl.name} r{p} {name} G={steps}")
