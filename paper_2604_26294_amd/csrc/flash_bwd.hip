@@ -854,6 +854,12 @@ bool bwd_empty(const AttnBwdParams& p) { return p.batch <= 0 || p.s_loc <= 0 || 
 
 }  // namespace
 
+bool attn_bwd_launches_fit(const AttnBwdParams& p) {
+  long long kv = (p.seq + kKvTile - 1) / kKvTile * (p.heads / p.group) * p.batch * kKvThreads, q = 0;
+  for (int k = 0; k < p.n_seg; ++k) q += (p.seg_rows[k] + kDqTile - 1) / kDqTile;
+  return std::max(kv, q * p.heads * p.batch * kBwdThreads) < (1LL << 32);
+}
+
 hipError_t launch_attn_bwd_prep(const AttnBwdParams& p, hipStream_t s) {
   if (bwd_empty(p)) return hipSuccess;
   const hipError_t e = check_bwd(p);

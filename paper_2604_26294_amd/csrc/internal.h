@@ -255,6 +255,10 @@ int attn_bwd_dq_split(const AttnBwdParams& p, int* split_len);
 // segments of p).
 int attn_bwd_kv_split(const AttnBwdParams& p);
 
+// Whether the dK / dV and dQ kernels over p's heads stay below the 2^32 threads of a launch (uses
+// the fields above; the splits only cut launches of a few hundred workgroups).
+bool attn_bwd_launches_fit(const AttnBwdParams& p);
+
 // The three kernels of the backward, in this order: delta; dK / dV; dQ.
 hipError_t launch_attn_bwd_prep(const AttnBwdParams& p, hipStream_t s);
 hipError_t launch_attn_bwd_dkdv(const AttnBwdParams& p, hipStream_t s);

@@ -246,10 +246,6 @@ struct AttnBwdWs {
   size_t q, a, da, dq, lse, delta, at, dqt, part, pml, total;
   int m_pad;
 };
-// Shards per group of the attention backward.  A shard alone leaves most of the GPU idle at
-// short sequences (7B, S_loc = 1024: 32 tiles in its Q product, 128 key tiles), so a group
-// holds as many as one grouped launch takes.
-int attn_bwd_group(const Dims& d) { return d.D < kGroupMax ? d.D : kGroupMax; }
 void attn_bwd_segments(const Dims& d, int n, AttnBwdParams* bp) {
   AttnParams ap = {};
   attn_segments(d, &ap);
@@ -264,6 +260,19 @@ void attn_bwd_segments(const Dims& d, int n, AttnBwdParams* bp) {
     bp->seg_rows[k] = ap.seg_rows[k];
     bp->seg_pos0[k] = ap.seg_pos0[k];
   }
+}
+// Shards per group of the attention backward.  A shard alone leaves most of the GPU idle at
+// short sequences (7B, S_loc = 1024: 32 tiles in its Q product, 128 key tiles), so a group
+// holds as many as one grouped launch takes (fewer for batches of millions of entries, whose
+// launches would pass 2^32 threads).
+int attn_bwd_group(const Dims& d) {
+  AttnBwdParams bp = {};
+  int n = d.D < kGroupMax ? d.D : kGroupMax;
+  for (; n > 1; --n) {
+    attn_bwd_segments(d, n, &bp);
+    if (tsp::attn_bwd_launches_fit(bp)) break;
+  }
+  return n;
 }
 AttnBwdWs attn_bwd_ws(const Dims& d, int group) {
   AttnBwdWs w;

@@ -329,6 +329,18 @@ def test_backward_workspace_can_be_bounded():
     assert T.lib.tsp_attn_kv_rank_bwd(sh, FAKE, g8, FAKE, FAKE, FAKE, 1, g8, FAKE, kv, None) == 5
 
 
+def test_attention_backward_groups_stay_launchable():
+    """A launch holds fewer than 2^32 threads: 1.2 million batch entries, one key tile of 512
+    threads per entry and shard, leave room for 6 of 8 shards in a group (seen in its workspace:
+    Q, A, dA, dQ, the two transposes, lse and delta of each of the group's heads)."""
+    b = 1_200_000
+    sh = T.make_shape(b, 8, 512, 512, 8, 8, 64, 8, 0)
+    per_shard = b * (6 * 64 * 2 + 2 * 4)
+    assert 6 * per_shard <= T.workspace_bytes(sh, T.OP_ATTN_BWD) < 7 * per_shard
+    few = T.make_shape(1000, 8, 512, 512, 8, 8, 64, 8, 0)
+    assert T.workspace_bytes(few, T.OP_ATTN_BWD) >= 8 * 1000 * (6 * 64 * 2 + 2 * 4)
+
+
 def test_planning_attention_launches_is_cheap():
     """The attention launch plan of a new shape is priced on the host by simulating its
     dispatch, in the workspace query and before the first launch: 0.1 ms for these shapes (13B
