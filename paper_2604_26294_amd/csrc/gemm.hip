@@ -1417,9 +1417,15 @@ hipError_t launch_gemm_nn_acc(const GemmParams& p, float* part, hipStream_t s) {
 }
 
 // SwiGLU backward (M = S_loc, N = F/D).  Long launches are cut in two: over many rounds the
-// workgroups of an XCD drift apart and share fewer operand panels in its L2 (7B, S_loc = 8192:
-// 8 products, 22 rounds, 2290 us; two launches of 4, 11 rounds each, 2075), while short ones
-// need all products to fill the chip (S_loc = 1024: 704 tiles, 332 us).
+// workgroups of an XCD drift apart and share fewer operand panels in its L2, while short ones
+// need all products to fill the chip (S_loc = 1024: 704 tiles, 332 us).  One launch of 8
+// products against two of 4, us, by the rounds of the one (a card, two runs within 1 %):
+//   7B   5.5: 695, 665   8.3: 964, 971   11: 1219, 1192   12.4: 1374, 1287   13.8: 1449, 1373
+//        16.5: 1796, 1721   19.3: 2088, 1942   22: 2350, 2140
+//   13B  7: 1043, 1071   14: 2023, 1899   21: 3001, 2861
+//   70B  7: 1429, 1533   10.5: 2167, 2334   14: 2819, 2723   21: 4216, 4192
+// so beyond 12 rounds two win everywhere (1 to 9 %); up to 11 it depends on how full each half's
+// last round is.
 int gemm_swiglu_bwd_per_launch(const GemmParams* ps, int n) {
   return n > 4 && rounds(tiles_of(ps, n, 128, 128)) > 12 ? (n + 1) / 2 : n;
 }

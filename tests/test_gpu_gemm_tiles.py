@@ -51,25 +51,52 @@ def test_mlp_tiles(m, h, f):
     assert _rel(y, ref) < BOUND
 
 
+def _mlp_backward(m, h, f, degree):
+    """One call over `degree` shards of f / degree rows, every gradient against 64 bits."""
+    fs = f // degree
+    sh = T.make_shape(1, m * degree, h, f, h // 64, h // 64, 64, degree, degree - 1)
+    x, dy = _normal(1, m, h), _normal(5, m, h)
+    w = [[_normal(10 * k + j, fs, h, std=h ** -0.5) for j in range(degree)] for k in (2, 3, 4)]
+    dx = torch.full((m, h), float("nan"), device="cuda")
+    dw = [[torch.full((fs, h), float("nan"), device="cuda") for _ in range(degree)]
+          for _ in range(3)]
+    ws = torch.empty(T.workspace_bytes(sh, T.OP_MLP_BWD), dtype=torch.uint8, device="cuda")
+    T.tsp_mlp_rank_bwd(sh, x, dy, w[0], w[1], w[2], dx, False, dw[0], dw[1], dw[2], ws)
+    xd, dyd, ref_dx = x.double(), dy.double(), torch.zeros(m, h, dtype=torch.float64, device="cuda")
+    for j in range(degree):
+        gd, ud, dd = (w[k][j].double() for k in range(3))
+        gg, uu, dh = xd @ gd.T, xd @ ud.T, dyd @ dd.T
+        sg = torch.sigmoid(gg)
+        dg, du = dh * uu * sg * (1 + gg * (1 - sg)), dh * gg * sg
+        ref_dx += dg @ gd + du @ ud
+        for k, ref in enumerate((dg.T @ xd, du.T @ xd, (gg * sg * uu).T @ dyd)):
+            assert _rel(dw[k][j], ref) < BOUND, (k, j)
+    assert _rel(dx, ref_dx) < BOUND
+
+
 # Weight gradients on the alternating tiles (2 x 33 x 16 tiles of 128) with a contraction of 3
-# stages, and dX on few rows.
-@pytest.mark.parametrize("m,h,f", [(130, 2048, 4104)])
+# stages, and dX on few rows.  The gate tiles with contractions of 1, 2, 3 and 5 stages, each
+# with waits and a slot order of its own, and ragged rows and columns.
+@pytest.mark.parametrize("m,h,f", [(130, 2048, 4104), (130, 64, 72), (130, 128, 136),
+                                   (257, 192, 200), (257, 320, 648)])
 def test_mlp_backward_tiles(m, h, f):
     print(f"[mlp bwd tiles] {m} x {h} x {f}", flush=True)
-    sh = T.make_shape(1, m, h, f, h // 64, h // 64, 64, 1, 0)
-    x, dy = _normal(1, m, h), _normal(5, m, h)
-    g, u, d = (_normal(k, f, h, std=h ** -0.5) for k in (2, 3, 4))
-    dx = torch.full((m, h), float("nan"), device="cuda")
-    dw = [torch.full((f, h), float("nan"), device="cuda") for _ in range(3)]
-    ws = torch.empty(T.workspace_bytes(sh, T.OP_MLP_BWD), dtype=torch.uint8, device="cuda")
-    T.tsp_mlp_rank_bwd(sh, x, dy, [g], [u], [d], dx, False, [dw[0]], [dw[1]], [dw[2]], ws)
-    xd, dyd, gd, ud, dd = (t.double() for t in (x, dy, g, u, d))
-    gg, uu, dh = xd @ gd.T, xd @ ud.T, dyd @ dd.T
-    sg = torch.sigmoid(gg)
-    dg, du = dh * uu * sg * (1 + gg * (1 - sg)), dh * gg * sg
-    assert _rel(dx, dg @ gd + du @ ud) < BOUND
-    for got, ref in zip(dw, (dg.T @ xd, du.T @ xd, (gg * sg * uu).T @ dyd)):
-        assert _rel(got, ref) < BOUND
+    _mlp_backward(m, h, f, 1)
+
+
+@pytest.mark.parametrize("degree,launches", [(5, 2), (13, 4)], ids=["3-2", "8-then-5"])
+def test_mlp_backward_gate_launches_of_unequal_size(degree, launches):
+    """A group whose gate products take more than 12 rounds of the chip (129 x 5 tiles each)
+    runs them in two launches: 3 and 2 products of a group of 5, also where it is the last of
+    two groups (8 in 4 and 4, then 5)."""
+    print(f"[mlp bwd gate launches] D = {degree}", flush=True)
+    T.tsp_profile_enable(True)
+    try:
+        _mlp_backward(16400, 64 * degree, 600 * degree, degree)
+        torch.cuda.synchronize()
+        assert T.tsp_profile_read(T.KERNELS.index("bwd_gate"))[1] == launches
+    finally:
+        T.tsp_profile_enable(False)
 
 
 @pytest.mark.parametrize("m,heads", [(16387, 16), (2100, 16), (1000, 16), (130, 2), (1, 1)])
