@@ -28,7 +28,10 @@ ODD3 = Workload("odd-degree-d3", 1, 768, 384, 1152, 6, 3, 64, 3, 2, w_std=0.05)
 DEG16 = Workload("degree-d16", 1, 1024, 1024, 2048, 16, 16, 64, 16, 13, w_std=0.04)
 # Twelve shards: the backward takes groups of 8 and 4; ragged 120 rows per rank, F/D = 72.
 DEG12 = Workload("degree-d12", 1, 1440, 768, 864, 12, 12, 64, 12, 7, w_std=0.05)
-# More than 4096 rows per rank: the MLP backward takes groups of 4 ring steps (4 and 2 here).
+# Twelve shards with query tiles enough for the dK/dV kernel to cut them into ranges (8 per kv
+# head: two ranges), in the backward's first group of 8 and in its second of 4.
+DEG12_SPLIT = Workload("degree-d12-split", 1, 3072, 1536, 864, 24, 12, 64, 12, 7, w_std=0.035)
+# Six ring steps of 4160 rows: one group, whose dX product is cut into 4 and 2 steps.
 MLP_LONG = Workload("mlp-long-d6", 1, 24960, 384, 432, 6, 6, 64, 6, 2, w_std=0.05)
 # Many attention work items per shard (5 query tiles x 2 heads x 10 batch entries): the
 # launch plan pairs query tiles (5 tiles: pairs (0, 4), (1, 3) and tile 2 alone; in the

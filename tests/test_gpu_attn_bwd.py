@@ -18,14 +18,14 @@ from oracle import tsp_oracle as O  # noqa: E402
 from paper_2604_26294_amd import inputs as I  # noqa: E402
 from paper_2604_26294_amd.harness import RankProblem, local_rows, to_device_bf16  # noqa: E402
 from paper_2604_26294_amd.workloads import TINY, Workload  # noqa: E402
-from tests.gpu_common import (DEG12, MID_GQA64, MID_GQA8, MID_MHA128, ODD3, SINGLE,  # noqa: E402
-                              assert_close, f64)
+from tests.gpu_common import (DEG12, DEG12_SPLIT, MID_GQA64, MID_GQA8, MID_MHA128,  # noqa: E402
+                              ODD3, SINGLE, assert_close, f64)
 
 # Ragged tails: S_loc = 128 / 192 / 640 / 256 / 320 against the 64-query stage and
 # 128-query tile; the zigzag shard's two segments of 96 rows; GQA group 2 and 8.
 CASES = [(TINY, 1), (MID_GQA64, 3), (MID_GQA64, 0), (MID_MHA128, 1), (MID_GQA8, 1),
          (SINGLE, 0), (MID_GQA64.with_layout(1), 2), (MID_MHA128.with_layout(1), 0),
-         (ODD3, 2), (DEG12, 7)]  # groups of 3 shards; of 8 and 4
+         (ODD3, 2), (DEG12, 7), (DEG12_SPLIT, 7)]  # groups of 3 shards; of 8 and 4
 _cache = {}
 
 

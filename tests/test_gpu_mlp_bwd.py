@@ -18,7 +18,7 @@ from tests.gpu_common import (DEG12, MID_GQA64, MID_MHA128, MLP_LONG, ODD3,  # n
 # Ragged tails: M = B S_loc = 384 / 640 / 320 against 128-row tiles, F/D = 344 / 1384 /
 # 1024 against 128-column tiles and the 64-wide contraction step.
 CASES = [(TINY, 1), (MID_GQA64, 3), (MID_MHA128, 0), (SINGLE, 0), (MID_GQA64.with_layout(1), 2),
-         (ODD3, 1), (DEG12, 7), (MLP_LONG, 2)]  # one group; 8 and 4 steps; 4 and 2
+         (ODD3, 1), (DEG12, 7), (MLP_LONG, 2)]  # one group; groups of 8 and 4; dX 4 and 2
 _cache = {}
 
 
