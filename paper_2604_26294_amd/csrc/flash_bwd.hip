@@ -8,11 +8,11 @@
 //   dV = P^T dO,  dK = scale dS^T Q   (contributions to every key of the prefix)
 //   dQ = scale dS K.
 // Two kernels share the work without atomics: one is key-stationary (a workgroup owns
-// 128 keys of one kv head, keeps their K and V in registers and streams the queries of
-// the g query heads that read them: dK, dV accumulate in registers and are written
-// once), the other query-stationary (a workgroup owns 128 queries of one head and
-// streams the keys: dQ accumulates in registers).  Both recompute the scores; only
-// the query-stationary one needs dP's row sums, which delta already holds.
+// 256 keys of one kv head, keeps their K in registers and their V in LDS and streams the
+// queries of the g query heads that read them: dK, dV accumulate in registers and are
+// written once), the other query-stationary (a workgroup owns 128 queries of one head and
+// streams the keys: dQ accumulates in registers).  Both form the scores and dP again; the
+// row sums that dS needs are in delta.
 //
 // The logits are formed exactly as the forward formed them, from the queries scaled by
 // scale * log2(e) and rounded to bf16 once (Qs, written so by the projection), so that

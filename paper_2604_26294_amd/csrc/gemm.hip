@@ -704,7 +704,6 @@ __device__ __forceinline__ void PpTile<NN_, EPI_, MULTI>::run(const GemmParams& 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, hh = lane >> 5;
 
   // Contraction steps [kb, kb + nk); step kt of the tile lives in slot kt mod 2.
   int kb = 0, nk = P.K / BK;
@@ -1246,39 +1245,43 @@ hipError_t check_params(const GemmParams& p) {
   return hipSuccess;
 }
 
+// The products of one grouped launch, and the number of their tiles.  A grouped product has one
+// part and one contraction range (the grouped tiles read neither).
 template <class K>
-hipError_t launch_group(const GemmParams* ps, int n, hipStream_t s) {
+hipError_t fill_group(const GemmParams* ps, int n, GemmGroup* g, long long* tiles) {
   if (n < 1 || n > kGemmGroupMax) return hipErrorInvalidValue;
-  GemmGroup g = {};
-  long long total = 0;
+  *tiles = 0;
   for (int i = 0; i < n; ++i) {
     const GemmParams& p = ps[i];
-    if (p.M <= 0 || p.N <= 0) return hipErrorInvalidValue;
+    if (p.M <= 0 || p.N <= 0 || p.n_parts > 1 || p.k_splits > 1) return hipErrorInvalidValue;
     const hipError_t e = check_params<K>(p);
     if (e != hipSuccess) return e;
-    g.p[i] = p;
-    total += (long long)((p.M + K::BM - 1) / K::BM) * ((p.N + K::BN - 1) / K::BN);
+    g->p[i] = p;
+    *tiles += (long long)((p.M + K::BM - 1) / K::BM) * ((p.N + K::BN - 1) / K::BN);
   }
-  g.n = n;
-  if (total > INT32_MAX) return hipErrorInvalidValue;
+  g->n = n;
+  return *tiles > INT32_MAX / 2 ? hipErrorInvalidValue : hipSuccess;
+}
+
+template <class K>
+hipError_t launch_group(const GemmParams* ps, int n, hipStream_t s) {
+  GemmGroup g = {};
+  long long total = 0;
+  const hipError_t e = fill_group<K>(ps, n, &g, &total);
+  if (e != hipSuccess) return e;
   void* args[] = {&g};
   return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_group_kernel<K>),
                          dim3((unsigned)total), dim3(K::THREADS), args, 0, s);
 }
 
-// n_big tiles of Big, the rest halved (gemm_mixed_group_kernel); n products with M, N > 0.
+// n_big tiles of Big, the rest halved (gemm_mixed_group_kernel).
 template <class Big, class Small>
-hipError_t launch_mixed_group(const GemmParams* ps, int n, long long total, long long n_big,
-                              hipStream_t s) {
-  if (n < 1 || n > kGemmGroupMax) return hipErrorInvalidValue;
+hipError_t launch_mixed_group(const GemmParams* ps, int n, long long n_big, hipStream_t s) {
   GemmGroup g = {};
-  for (int i = 0; i < n; ++i) {
-    if (ps[i].M <= 0 || ps[i].N <= 0) return hipErrorInvalidValue;
-    const hipError_t e = check_params<Big>(ps[i]);
-    if (e != hipSuccess) return e;
-    g.p[i] = ps[i];
-  }
-  g.n = n;
+  long long total = 0;
+  const hipError_t e = fill_group<Big>(ps, n, &g, &total);
+  if (e != hipSuccess) return e;
+  if (n_big > total) return hipErrorInvalidValue;
   int nb = (int)n_big;
   void* args[] = {&g, &nb};
   return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_mixed_group_kernel<Big, Small>),
@@ -1340,7 +1343,7 @@ hipError_t launch_gemm_swiglu_group(const GemmParams* ps, int n, hipStream_t s) 
   if (full > 0 && rest > 0 && 2 * rest <= kCus &&
       155 * full + 100 < std::min(155 * rounds(big), 100 * rounds(t128)))
     return launch_mixed_group<PpTile<false, EPI_SWIGLU>,
-                              Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, big, full * kCus, s);
+                              Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, full * kCus, s);
   if (155 * rounds(big) <= 100 * rounds(t128))
     return launch_group<PpTile<false, EPI_SWIGLU>>(ps, n, s);
   return launch_group<Tile<128, 128, 2, 4, false, EPI_SWIGLU, 3>>(ps, n, s);

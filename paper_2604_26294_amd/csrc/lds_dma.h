@@ -22,12 +22,15 @@ __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" :
 // LDS-destination load writes, so after one it puts a full vmcnt(0) wait in front of
 // the next LDS read it cannot prove disjoint, which would stall every step of a
 // pipelined loop on the load of the NEXT tile.  Hidden in asm, the load is ordered only
-// by the kernel's own waits: a kernel using it reads a slot only after a vmcnt(0) wait
-// that follows the slot's loads and a barrier (or an LDS counter that every loading
-// wavefront raises after that wait), and refills a slot only after a barrier (or a
-// counter that every reader raises after its last read) that follows its last read.  The compiler's own waits stay correct because loads
-// complete in issue order.  Kernels using this helper use M0 nowhere else (a reserved
-// register the compiler does not track through asm).
+// by the kernel's own waits.  A kernel using it reads a slot only after every wavefront
+// that loaded it has waited for its loads -- a vmcnt(N) with at most N loads issued after
+// the slot's, as loads complete in issue order -- and then passed a barrier (or raised an
+// LDS counter that the reader waits for).  It refills a slot only after every reader has
+// its last read in registers (lgkmcnt(0), or the use of the value) and has then passed a
+// barrier, or has raised a counter after that read (LDS operations of a wavefront complete
+// in issue order).  The compiler's own waits stay correct, again because loads complete in
+// issue order.  Kernels using this helper use M0 nowhere else (a reserved register the
+// compiler does not track through asm).
 typedef u32x4 rsrc_t;
 __device__ __forceinline__ void dma16(const rsrc_t& rsrc, uint32_t voff, uint32_t soff,
                                       lds_char* lds) {
