@@ -1,6 +1,6 @@
 // Backward of the causal flash attention of one TSP rank (gfx950, bf16 MFMA).
 //
-// For one shard's heads, given the rank's queries Q, the upstream gradient dO = dA of
+// For the heads of a group of shards, given the rank's queries Q, the upstream gradient dO = dA of
 // the attention output, the resident gathered K / V (sequence order), the base-2
 // log-sum-exp of every query's logits (from the forward recomputation) and
 // delta = rowsum(dO * O), the chain rule through O = P V, P = softmax(scale Q K^T)

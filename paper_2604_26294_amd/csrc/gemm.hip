@@ -2,8 +2,8 @@
 //
 //   gate+up+SwiGLU  Hs = bf16( SiLU(X W1^T) * (X W3^T) )          Algorithm 2, gate/up
 //   down / O-proj   Y (+)= Hs W2   or   Y (+)= Flatten(A) W_O^T    Algorithm 2 / 1, "+="
-//                   (optionally over two shards at once: the contraction then runs over
-//                   [A A'] and [B; B'], two operand pairs held in separate buffers)
+//                   (over up to eight operand pairs at once: the contraction then runs
+//                   over [A A' ..] and [B; B'; ..], held in separate buffers)
 //   SwiGLU backward G = X W1^T, U = X W3^T, dHs = dY W2^T in one pass; dG, dU and the
 //                   transposes of dG, dU, Hs for the weight-gradient products
 //   Q/K/V proj      Q = X W_Q^T (times a factor, then rounded) -> workspace, K, V ->

@@ -107,11 +107,12 @@ int gemm_nn_acc_splits(int M, int N, int K);
 hipError_t launch_gemm_nn_acc_group(const GemmParams* ps, int n, hipStream_t s);
 hipError_t launch_gemm_qkv_group(const GemmParams* ps, int n, hipStream_t s);
 
-// Causal flash attention of one rank's queries for the heads of one shard.
+// Causal flash attention of one rank's queries for H_s heads: those of one shard or of several
+// consecutive ones.
 //   Q [B, S_loc, H_s, d] bf16, the queries times softmax scale * log2(e) (rounded to
 //   bf16 once, by the projection's epilogue), so that Q K^T are base-2 logits;
 //   K/V buffers [B, S, n_kv, d] bf16 (heads
-//   kv_head0 .. kv_head0 + H_s/g - 1 are this shard's);  O [B, S_loc, H_s, d] bf16.
+//   kv_head0 .. kv_head0 + H_s/g - 1 are theirs);  O [B, S_loc, H_s, d] bf16.
 //   Q and O rows may be wider than H_s d (a launch over some of the heads of a wider
 //   buffer): token row t of Q starts ld elements after row t - 1, of O ld_o.
 //   The local rows form n_seg segments of consecutive global positions: rows
@@ -130,7 +131,7 @@ struct AttnParams {
   int head_dim;     // d
   long long seq;    // S (K/V buffer rows per batch)
   int n_kv;         // kv heads in the buffer
-  int kv_head0;     // first kv head of this shard
+  int kv_head0;     // first kv head of the launch
   int n_seg;        // 1 or 2
   int seg_row0[2];
   int seg_rows[2];
@@ -189,7 +190,7 @@ void set_attn_poll_limit(int polls);
 int attn_poll_limit();
 hipError_t launch_flash_attn(const AttnParams& p, hipStream_t s);
 
-// Backward of launch_flash_attn for one shard's heads (same segments and buffers).
+// Backward of launch_flash_attn for H_s heads (same segments and buffers).
 //   Qs   [B, S_loc, H_s, d] bf16   the recomputed queries, scaled as for the forward
 //                                  (bf16(softmax scale * log2(e) * q));
 //   O    [B, S_loc, H_s, d] bf16   the recomputed attention output;

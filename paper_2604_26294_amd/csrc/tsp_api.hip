@@ -124,8 +124,6 @@ size_t split_part_bytes(const Dims& d, int k_step) {
 }
 size_t ws_mlp_hs(const Dims& d) { return align_up((size_t)d.M * d.G * d.fs_pad * 2); }
 size_t ws_mlp(const Dims& d) { return ws_mlp_hs(d) + split_part_bytes(d, d.fs_pad); }
-// Attention workspace: Q of the current shard and the attention output A (bf16
-// [M, H_s d] each), then the key-range partials when the shard's attention is split.
 // The rank's query rows as segments of consecutive global positions (Algorithm 1):
 // contiguous chunks are one segment starting at p S_loc; a zigzag shard is chunk p
 // (first s1 = (p+1) S_c keys) followed by chunk 2D-1-p (first s2 = (2D-p) S_c keys).
