@@ -508,6 +508,27 @@ GemmParams dw_params(const Dims& d, const uint16_t* t, int m_pad, const uint16_t
   return q;
 }
 
+// Whether two products write common elements of Y.
+bool outputs_overlap(const GemmParams& a, const GemmParams& b) {
+  const float* const a1 = a.Y + (size_t)(a.M - 1) * a.ldy + a.N;
+  const float* const b1 = b.Y + (size_t)(b.M - 1) * b.ldy + b.N;
+  return a.Y < b1 && b.Y < a1;
+}
+// Weight-gradient products in launches of up to `per_launch`.  A caller may give several shards
+// one buffer (their sum, with accumulate): products whose outputs overlap go in launches of their
+// own, in order, as the products of a launch run at the same time.
+tsp_status launch_dw(int kind, const GemmParams* g, int n, int per_launch, hipStream_t st) {
+  for (int i = 0, m; i < n; i += m) {
+    for (m = 1; m < per_launch && i + m < n; ++m) {
+      bool apart = true;
+      for (int k = i; k < i + m; ++k) apart = apart && !outputs_overlap(g[k], g[i + m]);
+      if (!apart) break;
+    }
+    TSP_LAUNCH(kind, st, tsp::launch_gemm_nn_acc_group(g + i, m, st));
+  }
+  return TSP_OK;
+}
+
 // Backward of run_mlp (same ring order), in groups of ws_group steps.  Per group: one or
 // two grouped launches for G, U, dHs and the SwiGLU backward of its shards, the accumulating
 // products for dX (over up to kMlpBwdDxSteps steps each), and grouped launches for the 3 n
@@ -585,15 +606,12 @@ tsp_status run_mlp_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
     }
     // dW (+)= (dG^T | dU^T | Hs^T) (X | X | dY): [F/D, M] x [M, h], padded rows are zero.
     float* const* const out[3] = {dwg, dwu, dwd};
-    for (int q = 0, m = 0; q < 3 * n; ++q) {
-      const int k = q / n, i = q % n;
-      g[m++] = dw_params(d, tr[k] + (size_t)i * d.fs * w.m_pad, w.m_pad, k < 2 ? x : dy, d.fs,
-                         out[k][shard[i]], accumulate);
-      if (m == tsp::kGemmGroupMax || q + 1 == 3 * n) {
-        TSP_LAUNCH(TSP_KERNEL_BWD_DW, st, tsp::launch_gemm_nn_acc_group(g, m, st));
-        m = 0;
-      }
-    }
+    GemmParams q[3 * kGroupMax];
+    for (int k = 0; k < 3; ++k)
+      for (int i = 0; i < n; ++i)
+        q[k * n + i] = dw_params(d, tr[k] + (size_t)i * d.fs * w.m_pad, w.m_pad, k < 2 ? x : dy,
+                                 d.fs, out[k][shard[i]], accumulate);
+    TSP_TRY(launch_dw(TSP_KERNEL_BWD_DW, q, 3 * n, tsp::kGemmGroupMax, st));
   }
   return TSP_OK;
 }
@@ -868,8 +886,7 @@ tsp_status run_attn_bwd(const Dims& d, const uint16_t* x, const uint16_t* dy,
       g[i] = dw_params(d, dqt_ws + at, w.m_pad, x, qd, dw[r0 + i], accumulate);
       g[n + i] = dw_params(d, at_ws + at, w.m_pad, dy, qd, dw[r0 + i] + wo, accumulate);
     }
-    for (int i = 0; i < 2 * n; i += per_launch)
-      TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(g + i, per_launch, st));
+    TSP_TRY(launch_dw(TSP_KERNEL_ABWD_DW, g, 2 * n, per_launch, st));
   }
   return TSP_OK;
 }
@@ -918,14 +935,14 @@ tsp_status run_attn_kv_bwd(const Dims& d, const uint16_t* x, const uint16_t* con
                tsp::launch_transpose2_bf16(grad[0] + (size_t)g0 * kd, ld, tr[0],
                                            grad[1] + (size_t)g0 * kd, ld, tr[1], (int)d.M,
                                            (g1 - g0) * kd, w.m_pad, st));
-    GemmParams q[tsp::kGemmGroupMax] = {};
+    GemmParams q[tsp::kGemmGroupMax];
     int n = 0;
     for (int i = 2 * g0; i < 2 * g1; ++i) {
       const int r = i / 2, k = i % 2;
       q[n++] = dw_params(d, tr[k] + (size_t)(r - g0) * kd * w.m_pad, w.m_pad, x, kd,
                          dw[r] + (size_t)(qd + k * kd) * d.h, accumulate);
       if (n == tsp::kGemmGroupMax || i + 1 == 2 * g1) {
-        TSP_LAUNCH(TSP_KERNEL_ABWD_DW, st, tsp::launch_gemm_nn_acc_group(q, n, st));
+        TSP_TRY(launch_dw(TSP_KERNEL_ABWD_DW, q, n, n, st));
         n = 0;
       }
     }

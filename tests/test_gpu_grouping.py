@@ -136,3 +136,37 @@ def test_backward_in_the_smallest_workspace(wl, p, steps):
     for name, ref in outs[0].items():
         for a, b in zip(outs[1][name], ref):
             assert_close(a, b, f"{wl.name} r{p} {name} G={steps}")
+
+
+@pytest.mark.parametrize("wl,p", [(MID_GQA64, 2), (DEG12, 7)], ids=["one-group", "two-groups"])
+def test_shards_that_share_a_gradient_buffer(wl, p):
+    """One weight-gradient buffer given for every shard: with accumulate it ends as the sum of
+    the shards' gradients, without as the last shard's in the schedule's order (the products of
+    a launch run at the same time, so these go in launches of their own).  Same products as with
+    a buffer each, so only the fp32 order of the running sums differs."""
+    print(f"[shared dw] {wl.name} rank {p}", flush=True)
+    x_bits, w_bits = _inputs(wl)
+    prob = RankProblem(wl, x_bits, w_bits, p)
+    prob.prefill_kv(include_self=True)
+    dy = to_device_bf16(local_rows(I.make_dy_full(wl), wl, p))
+    dkl, dvl = (to_device_bf16(t) for t in I.make_dkv_own(wl, p))
+    calls = {"mlp": lambda acc: prob.mlp_bwd(dy, acc), "attn": lambda acc: prob.attn_bwd(dy, acc),
+             "kv": lambda acc: prob.attn_kv_bwd(dkl, dvl, acc)}
+    prob.mlp_bwd(dy), prob.attn_bwd(dy)  # (allocate the gradient buffers)
+    own = {"dw": [list(t) for t in prob.dw], "adw": list(prob.adw)}
+    for name, call in calls.items():
+        prob.dw, prob.adw = own["dw"], own["adw"]
+        for t in prob.adw + [t for ts in prob.dw for t in ts]:
+            t.zero_()
+        call(False)
+        each = [list(ts) for ts in prob.dw] if name == "mlp" else [prob.adw]
+        each = [[t.double() for t in ts] for ts in each]
+        last = (p + 1) % wl.degree if name == "mlp" else wl.degree - 1  # of ring step D - 1
+        for acc in (True, False):
+            prob.dw = [[torch.zeros_like(ts[0])] * wl.degree for ts in own["dw"]]
+            prob.adw = [torch.zeros_like(own["adw"][0])] * wl.degree
+            call(acc)
+            shared = [ts[0] for ts in prob.dw] if name == "mlp" else [prob.adw[0]]
+            for got, ts in zip(shared, each):
+                ref = sum(ts) if acc else ts[last]
+                assert torch.allclose(got.double(), ref, rtol=1e-5, atol=1e-6 * ref.abs().max().item())
